@@ -106,14 +106,16 @@ typedef struct {
  * kernel: 0 = tiled face-once kernel, 1 = simple per-cell kernel,
  *   2 = plane-ring face-once kernel (a ring of three primitive planes in LDS,
  *   two barriers per plane; tile_j = 4 or 8).
- * tile_j, tile_k: tile extent in j and k (tile_i is 64, one wavefront);
- *   the tiled kernel takes tile_j = 2, 4 or 8.  Defaults (set by
- *   cfd_create_blocks): kernel 2, tile_j 8, tile_k 32 (16 for FP32-flux
- *   Euler, whose kernels hold two workgroups per CU), use_graph 1, order 1;
- *   tile_k is halved (down to 4) while the grid gives fewer tiles than CUs,
- *   and a grid with fewer tiles than CUs even then gets the tiled kernel
- *   with tile_j 4 and tile_k halved (down to 1) until it has four tiles per
- *   CU.
+ * tile_j, tile_k: a tile has 64 tile_j columns and at most tile_k planes (a
+ *   block's k range is cut into runs of nearly equal length).  The tiled
+ *   kernel (tile_j = 2, 4 or 8) takes 64 x tile_j columns; the plane-ring
+ *   kernel 64 x 8 or 32 x 16 (tile_j 8), 32 x 8 or 16 x 16 (tile_j 4),
+ *   whichever pads the blocks less.  Defaults (set by cfd_create_blocks):
+ *   kernel 2, tile_j 8 (4 for FP32 fluxes, and where it pads an FP64 grid
+ *   that much less), tile_k the depth in [4, 32] of least estimated cost for
+ *   the grid, use_graph 1, order 1; a grid with fewer 64 x 8 x 4 tiles than
+ *   CUs gets the tiled kernel with tile_j 4 and tile_k halved from 4 (down to
+ *   1) until it has four tiles per CU.
  * use_graph: 1 captures one time step in a hipGraph and replays it.
  * order: tile work-list order.  0 = largest tiles first (balances uneven
  *   blocks); 1 = XCD-aware: the tiles are cut into 8 spatially contiguous

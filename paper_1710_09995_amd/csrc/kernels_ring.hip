@@ -1,4 +1,6 @@
-// Plane-ring face-once residual / stage kernel (64 x 8 or 64 x 4 tiles).
+// Plane-ring face-once residual / stage kernel.  Tiles of TI x TJ columns,
+// one thread each: 64 x 8 and 32 x 16 (tile_j 8), 32 x 8 and 16 x 16
+// (tile_j 4), chosen by how the blocks' extents fill them.
 //
 // Same tile decomposition and per-face arithmetic as the tiled kernel, with a
 // different plane pipeline.  LDS holds a ring of three primitive planes
@@ -35,61 +37,63 @@
 
 namespace cfd {
 
-template <typename T, bool VISC, int TJ_>
+template <typename T, bool VISC, int TI_, int TJ_>
 struct RingLds {
-  static constexpr int TJ = TJ_;
-  static constexpr int WI = 68, WJ = TJ + 4;   // halo 2
+  static constexpr int TI = TI_, TJ = TJ_;
+  static constexpr int WI = TI + 4, WJ = TJ + 4;   // halo 2
   static constexpr int NW = VISC ? 6 : 5;
   static constexpr int PLANE = NW * WJ * WI;   // elements of one plane
   static constexpr int W_BYTES = (3 * PLANE * (int)sizeof(T) + 15) / 16 * 16;
-  static constexpr int FJ = 5 * (TJ + 1) * 64;  // doubles: lower j-faces, TJ+1 rows
-  static constexpr int FE = 5 * TJ;             // doubles: i-faces at i0+64
+  static constexpr int FJ = 5 * (TJ + 1) * TI;  // doubles: lower j-faces, TJ+1 rows
+  static constexpr int FE = 5 * TJ;             // doubles: i-faces at i0+TI
   static constexpr int TOTAL = W_BYTES + (FJ + FE) * 8;
   // stage 3 also keeps the area vectors of those faces for the time step
-  static constexpr int SJ = 3 * (TJ + 1) * 64;  // doubles: S_j of the lower j-faces
-  static constexpr int SE = 3 * TJ;             // doubles: S_i at i0+64
+  static constexpr int SJ = 3 * (TJ + 1) * TI;  // doubles: S_j of the lower j-faces
+  static constexpr int SE = 3 * TJ;             // doubles: S_i at i0+TI
   static constexpr int TOTAL_DT = TOTAL + (SJ + SE) * 8;
 };
 
 // Minimum waves per SIMD asked of the register allocator: the FP32 Euler
-// variants fit 128 VGPRs (4 waves per SIMD; LDS allows two 64x8 or three
-// 64x4 workgroups per CU), the others take what they need.
+// variants fit 128 VGPRs (4 waves per SIMD), FP64 needs all 256 of two waves
+// (without the bound its 256-column variants took 257 and ran one wave per
+// SIMD: 256 x 128 x 128 NS 2.18 ms a step against 1.75), FP32 NS takes what it
+// needs (two waves).
 template <typename T, bool VISC>
 constexpr int ring_min_waves() {
-  return (sizeof(T) == 4 && !VISC) ? 4 : 1;
+  return sizeof(T) == 8 ? 2 : VISC ? 1 : 4;
 }
 
-template <typename T, bool VISC, int MODE, int TJ>
-__global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_ring(
+template <typename T, bool VISC, int MODE, int TI, int TJ>
+__global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_ring(
     StageArgs A, const BlockDesc* __restrict__ blocks, const TileDesc* __restrict__ tiles, Gas<T> gas) {
-  using LD = RingLds<T, VISC, TJ>;
-  constexpr int NT = 64 * TJ;
+  using LD = RingLds<T, VISC, TI, TJ>;
+  constexpr int NT = TI * TJ;
   constexpr int WI = LD::WI, WJ = LD::WJ;
   __shared__ __attribute__((aligned(16))) char smem[MODE == 3 ? LD::TOTAL_DT : LD::TOTAL];
   T* sW = reinterpret_cast<T*>(smem);                                   // [3][NW][WJ][WI]
-  double* sFj = reinterpret_cast<double*>(smem + LD::W_BYTES);          // [5][TJ+1][64]
+  double* sFj = reinterpret_cast<double*>(smem + LD::W_BYTES);          // [5][TJ+1][TI]
   double* sFe = sFj + LD::FJ;                                           // [5][TJ]
-  double* sSj = sFe + LD::FE;                                           // mode 3: [3][TJ+1][64]
+  double* sSj = sFe + LD::FE;                                           // mode 3: [3][TJ+1][TI]
   double* sSe = sSj + LD::SJ;                                           // mode 3: [3][TJ]
 
-  auto W = [&](int slot, int v, int pj, int pi) -> T& { return sW[slot * LD::PLANE + (v * WJ + pj) * WI + pi]; };
-  auto wprim = [&](int slot, int pj, int pi) {
+  auto W = [&](int slot, int v, int p) -> T& { return sW[slot * LD::PLANE + v * (WJ * WI) + p]; };
+  auto wprim = [&](int slot, int p) {
     Prim<T> w;
-    w.r = W(slot, 0, pj, pi);
-    w.u = W(slot, 1, pj, pi);
-    w.v = W(slot, 2, pj, pi);
-    w.w = W(slot, 3, pj, pi);
-    w.p = W(slot, 4, pj, pi);
+    w.r = W(slot, 0, p);
+    w.u = W(slot, 1, p);
+    w.v = W(slot, 2, p);
+    w.w = W(slot, 3, p);
+    w.p = W(slot, 4, p);
     return w;
   };
-  auto wphi = [&](int slot, int pj, int pi, T o[4]) {
-    o[0] = W(slot, 1, pj, pi);
-    o[1] = W(slot, 2, pj, pi);
-    o[2] = W(slot, 3, pj, pi);
-    o[3] = W(slot, VISC ? 5 : 4, pj, pi);
+  auto wphi = [&](int slot, int p, T o[4]) {
+    o[0] = W(slot, 1, p);
+    o[1] = W(slot, 2, p);
+    o[2] = W(slot, 3, p);
+    o[3] = W(slot, VISC ? 5 : 4, p);
   };
 
-  const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
+  const int tid = threadIdx.x, tx = tid & (TI - 1), ty = tid / TI;
   // partials: stage 1 (mode 1) sum R^2, max |R_rho|, non-finite count;
   // stage 3 (mode 3) minimum time step of the new state
   double acc[NPART];
@@ -99,14 +103,18 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
     const TileDesc td = tiles[tile];
     const BlockDesc B = blocks[td.blk];
     const int ni = B.n[0], nj = B.n[1], nk = B.n[2];
-    const int i0 = td.i0, j0 = td.j0, k0 = td.k0;
-    const int kend = min(k0 + A.tile_k, nk);
+    const int i0 = td.i0, j0 = td.j0;
+    int k0, kend;
+    tile_run(nk, A.tile_k, td.kp, k0, kend);
     const int i = i0 + tx, j = j0 + ty;
     const bool act = i < ni && j < nj;
     const bool fi_ok = i <= ni && j < nj;
     const bool fj_ok = j <= nj && i < ni;
-    const bool has_xj = j0 + TJ <= nj && i0 + tx < ni;              // wave 0: j-faces of row j0+TJ
-    const bool has_xi = tx < TJ && i0 + 64 <= ni && j0 + tx < nj;  // wave 1: i-faces at column i0+64
+    // faces on the tile's high edges: lanes [0, TI) the j-faces of row j0+TJ,
+    // lanes [TI, TI+TJ) the i-faces of column i0+TI
+    const bool e_j = tid < TI;
+    const int e_ci = e_j ? tid : TI, e_rj = e_j ? TJ : tid - TI;
+    const bool e_ok = tid < TI + TJ && (e_j ? j0 + TJ <= nj && i0 + e_ci < ni : i0 + TI <= ni && j0 + e_rj < nj);
     const double* qb = A.qs + B.qoff;
     const double* mb = A.met + B.moff;
     const double* vb = VISC ? A.vmet + B.voff : nullptr;
@@ -127,12 +135,12 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
         Prim<T> w;
         w.r = T(1); w.u = T(0); w.v = T(0); w.w = T(0); w.p = T(1);
         if (gi <= ni + 1 && gj <= nj + 1) w = ld_prim<T>(qb, off(gi, gj, kk), sv, gas.gm1);
-        W(slot, 0, pj, pi) = w.r;
-        W(slot, 1, pj, pi) = w.u;
-        W(slot, 2, pj, pi) = w.v;
-        W(slot, 3, pj, pi) = w.w;
-        W(slot, 4, pj, pi) = w.p;
-        if (VISC) W(slot, 5, pj, pi) = temp_of(w);
+        W(slot, 0, s) = w.r;
+        W(slot, 1, s) = w.u;
+        W(slot, 2, s) = w.v;
+        W(slot, 3, s) = w.w;
+        W(slot, 4, s) = w.p;
+        if (VISC) W(slot, 5, s) = temp_of(w);
       }
     };
 
@@ -156,91 +164,78 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
       CellIn cin;
       if (act) load_cell<MODE>(A, B, off(i, j, k), cin);
       // ---- A. faces of plane k
-      // lower i-face of cell (i0+ci, j0+rj): flux F, area vector S
-      auto face_i = [&](int ci, int rj, double F[5], double S[3]) {
-        const int pi = ci + 2, pj = rj + 2;
+      // lower face, along direction d = 0 (i) or 1 (j), of cell (i0+ci, j0+rj):
+      // flux F, area vector S.  One expression for both directions, so that
+      // the tile-edge faces of either run in the same lanes.
+      auto face = [&](int d, int ci, int rj, double F[5], double S[3]) {
+        const int p = (rj + 2) * WI + ci + 2;             // the cell above the face
+        const int st = d == 0 ? 1 : WI, tr = d == 0 ? WI : 1;   // along the face normal, across
         const int64_t c = off(i0 + ci, j0 + rj, k);
-        const double sx = mb[c], sy = mb[sv + c], sz = mb[2 * sv + c];
+        const double* ms = mb + (int64_t)(3 * d) * sv + c;
+        const double sx = ms[0], sy = ms[sv], sz = ms[2 * sv];
         S[0] = sx;
         S[1] = sy;
         S[2] = sz;
         T f[5], n[3];
-        const double area = face_inviscid<T>(wprim(s0, pj, pi - 2), wprim(s0, pj, pi - 1), wprim(s0, pj, pi),
-                                             wprim(s0, pj, pi + 1), sx, sy, sz, gas, f, n);
+        const double area = face_inviscid<T>(wprim(s0, p - 2 * st), wprim(s0, p - st), wprim(s0, p),
+                                             wprim(s0, p + st), sx, sy, sz, gas, f, n);
         if (VISC) {
           T pl[4], pr[4], d1[4], d2[4], a[4], b[4], e[4], g[4];
-          wphi(s0, pj, pi - 1, pl);
-          wphi(s0, pj, pi, pr);
-          wphi(s0, pj + 1, pi - 1, a); wphi(s0, pj + 1, pi, b); wphi(s0, pj - 1, pi - 1, e); wphi(s0, pj - 1, pi, g);
+          wphi(s0, p - st, pl);
+          wphi(s0, p, pr);
+          wphi(s0, p - st + tr, a); wphi(s0, p + tr, b); wphi(s0, p - st - tr, e); wphi(s0, p - tr, g);
           tdiff(a, b, e, g, d1);
-          wphi(sp, pj, pi - 1, a); wphi(sp, pj, pi, b); wphi(sm, pj, pi - 1, e); wphi(sm, pj, pi, g);
+          wphi(sp, p - st, a); wphi(sp, p, b); wphi(sm, p - st, e); wphi(sm, p, g);
           tdiff(a, b, e, g, d2);
           double St[2][3], vf;
-          face_vmetrics(vb, sv, c, 0, St, vf);
+          face_vmetrics(vb, sv, c, d, St, vf);
           face_viscous<T>(pl, pr, sx, sy, sz, n, d1, d2, St, vf, gas, f);
         }
         scale_flux_f64(f, area, F);
       };
-      auto face_j = [&](int ci, int rj) {   // lower j-face of cell (i0+ci, j0+rj) -> sFj
-        const int pi = ci + 2, pj = rj + 2;
-        const int64_t c = off(i0 + ci, j0 + rj, k);
-        const double sx = mb[3 * sv + c], sy = mb[4 * sv + c], sz = mb[5 * sv + c];
-        if (MODE == 3) {
-          sSj[(0 * (TJ + 1) + rj) * 64 + ci] = sx;
-          sSj[(1 * (TJ + 1) + rj) * 64 + ci] = sy;
-          sSj[(2 * (TJ + 1) + rj) * 64 + ci] = sz;
-        }
-        T f[5], n[3];
-        const double area = face_inviscid<T>(wprim(s0, pj - 2, pi), wprim(s0, pj - 1, pi), wprim(s0, pj, pi),
-                                             wprim(s0, pj + 1, pi), sx, sy, sz, gas, f, n);
-        if (VISC) {
-          T pl[4], pr[4], d1[4], d2[4], a[4], b[4], e[4], g[4];
-          wphi(s0, pj - 1, pi, pl);
-          wphi(s0, pj, pi, pr);
-          wphi(s0, pj - 1, pi + 1, a); wphi(s0, pj, pi + 1, b); wphi(s0, pj - 1, pi - 1, e); wphi(s0, pj, pi - 1, g);
-          tdiff(a, b, e, g, d1);
-          wphi(sp, pj - 1, pi, a); wphi(sp, pj, pi, b); wphi(sm, pj - 1, pi, e); wphi(sm, pj, pi, g);
-          tdiff(a, b, e, g, d2);
-          double St[2][3], vf;
-          face_vmetrics(vb, sv, c, 1, St, vf);
-          face_viscous<T>(pl, pr, sx, sy, sz, n, d1, d2, St, vf, gas, f);
-        }
-        double F[5];
-        scale_flux_f64(f, area, F);
-        for (int q = 0; q < 5; ++q) sFj[(q * (TJ + 1) + rj) * 64 + ci] = F[q];
+      auto keep_j = [&](int ci, int rj, const double F[5], const double S[3]) {   // a j-face -> LDS
+        for (int q = 0; q < 5; ++q) sFj[(q * (TJ + 1) + rj) * TI + ci] = F[q];
+        if (MODE == 3)
+          for (int x = 0; x < 3; ++x) sSj[(x * (TJ + 1) + rj) * TI + ci] = S[x];
       };
       double Fi[5] = {0, 0, 0, 0, 0};
       if (fi_ok) {
         double Si[3];
-        face_i(tx, ty, Fi, Si);
+        face(0, tx, ty, Fi, Si);
       }
       CFD_FACE_FENCE_RING();
-      if (fj_ok) face_j(tx, ty);
+      if (fj_ok) {
+        double Fj[5], Sj[3];
+        face(1, tx, ty, Fj, Sj);
+        keep_j(tx, ty, Fj, Sj);
+      }
       CFD_FACE_FENCE_RING();
-      if (ty == 0 && has_xj) face_j(tx, TJ);
-      if (ty == 1 && has_xi) {
+      if (e_ok) {
         double Fe[5], Se[3];
-        face_i(64, tx, Fe, Se);
-        for (int q = 0; q < 5; ++q) sFe[q * TJ + tx] = Fe[q];
-        if (MODE == 3)
-          for (int x = 0; x < 3; ++x) sSe[x * TJ + tx] = Se[x];
+        face(e_j ? 1 : 0, e_ci, e_rj, Fe, Se);
+        if (e_j) {
+          keep_j(e_ci, TJ, Fe, Se);
+        } else {
+          for (int q = 0; q < 5; ++q) sFe[q * TJ + e_rj] = Fe[q];
+          if (MODE == 3)
+            for (int x = 0; x < 3; ++x) sSe[x * TJ + e_rj] = Se[x];
+        }
       }
       CFD_FACE_FENCE_RING();
       double Fku[5] = {0, 0, 0, 0, 0};
       if (act) {   // upper k-face between (i, j, k) and (i, j, k+1)
-        const int pi = tx + 2, pj = ty + 2;
+        const int p = (ty + 2) * WI + tx + 2;
         const int64_t cu = off(i, j, k) + sk;
         const double sx = mb[6 * sv + cu], sy = mb[7 * sv + cu], sz = mb[8 * sv + cu];
         T f[5], n[3];
-        const double area = face_inviscid<T>(wprim(sm, pj, pi), wprim(s0, pj, pi), wprim(sp, pj, pi), q3,
-                                             sx, sy, sz, gas, f, n);
+        const double area = face_inviscid<T>(wprim(sm, p), wprim(s0, p), wprim(sp, p), q3, sx, sy, sz, gas, f, n);
         if (VISC) {
           T pl[4], pr[4], d1[4], d2[4], a[4], b[4], e[4], g[4];
-          wphi(s0, pj, pi, pl);
-          wphi(sp, pj, pi, pr);
-          wphi(s0, pj, pi + 1, a); wphi(sp, pj, pi + 1, b); wphi(s0, pj, pi - 1, e); wphi(sp, pj, pi - 1, g);
+          wphi(s0, p, pl);
+          wphi(sp, p, pr);
+          wphi(s0, p + 1, a); wphi(sp, p + 1, b); wphi(s0, p - 1, e); wphi(sp, p - 1, g);
           tdiff(a, b, e, g, d1);
-          wphi(s0, pj + 1, pi, a); wphi(sp, pj + 1, pi, b); wphi(s0, pj - 1, pi, e); wphi(sp, pj - 1, pi, g);
+          wphi(s0, p + WI, a); wphi(sp, p + WI, b); wphi(s0, p - WI, e); wphi(sp, p - WI, g);
           tdiff(a, b, e, g, d2);
           double St[2][3], vf;
           face_vmetrics(vb, sv, cu, 2, St, vf);
@@ -278,9 +273,9 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
         for (int x = 0; x < 3; ++x) Siu[x] = __shfl_down(Si[x], 1, 64);
         if (act)
           for (int x = 0; x < 3; ++x) {
-            const double su = tx == 63 ? sSe[x * TJ + ty] : Siu[x];
+            const double su = tx == TI - 1 ? sSe[x * TJ + ty] : Siu[x];
             bdt[0][x] = 0.5 * (Si[x] + su);
-            bdt[1][x] = 0.5 * (sSj[(x * (TJ + 1) + ty) * 64 + tx] + sSj[(x * (TJ + 1) + ty + 1) * 64 + tx]);
+            bdt[1][x] = 0.5 * (sSj[(x * (TJ + 1) + ty) * TI + tx] + sSj[(x * (TJ + 1) + ty + 1) * TI + tx]);
             bdt[2][x] = 0.5 * (Sk[x] + Sku[x]);
           }
       }
@@ -288,9 +283,9 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
       if (act) {
         double Di[5], Dj[5], Dk[5];
         for (int q = 0; q < 5; ++q) {
-          const double fu = tx == 63 ? sFe[q * TJ + ty] : Fiu[q];
+          const double fu = tx == TI - 1 ? sFe[q * TJ + ty] : Fiu[q];
           Di[q] = fu - Fi[q];
-          Dj[q] = sFj[(q * (TJ + 1) + ty + 1) * 64 + tx] - sFj[(q * (TJ + 1) + ty) * 64 + tx];
+          Dj[q] = sFj[(q * (TJ + 1) + ty + 1) * TI + tx] - sFj[(q * (TJ + 1) + ty) * TI + tx];
           Dk[q] = Fku[q] - Fklo[q];
         }
         double Rc[5], Qo[5];
@@ -326,40 +321,36 @@ __global__ void __launch_bounds__(64 * TJ, (ring_min_waves<T, VISC>())) k_stage_
 
 // ---------------------------------------------------------------- launchers
 
-template <typename T, bool VISC, int MODE, int TJ>
-static void launch_ring_t(const StageArgs& A, const BlockDesc* blocks, const TileDesc* tiles, const Gas<T>& gas,
-                          int nwg, hipStream_t s) {
-  hipLaunchKernelGGL((k_stage_ring<T, VISC, MODE, TJ>), dim3(nwg), dim3(64 * TJ), 0, s, A, blocks, tiles, gas);
-}
-
-template <typename T, bool VISC, int MODE, int TJ>
-static int occ_ring_t() {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_stage_ring<T, VISC, MODE, TJ>, 64 * TJ, 0) != hipSuccess)
-    return 1;
-  return n > 0 ? n : 1;
-}
-
-template <typename T, bool VISC, int TJ>
-static void ring_mode(const StageArgs& A, int mode, const BlockDesc* blocks, const TileDesc* tiles,
-                      const Gas<T>& gas, int nwg, hipStream_t s, int* occ) {
+template <typename T, bool VISC, int MODE, int TI, int TJ>
+static void ring_launch(const StageArgs& A, const BlockDesc* blocks, const TileDesc* tiles, const Gas<T>& gas,
+                        int nwg, hipStream_t s, int* occ) {
   if (occ) {
-    *occ = mode == 0 ? occ_ring_t<T, VISC, 0, TJ>()
-                     : (mode == 1 ? occ_ring_t<T, VISC, 1, TJ>()
-                                  : (mode == 2 ? occ_ring_t<T, VISC, 2, TJ>() : occ_ring_t<T, VISC, 3, TJ>()));
+    int n = 0;
+    *occ = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_stage_ring<T, VISC, MODE, TI, TJ>, TI * TJ, 0) ==
+                       hipSuccess && n > 0
+               ? n
+               : 1;
     return;
   }
-  if (mode == 0) launch_ring_t<T, VISC, 0, TJ>(A, blocks, tiles, gas, nwg, s);
-  else if (mode == 1) launch_ring_t<T, VISC, 1, TJ>(A, blocks, tiles, gas, nwg, s);
-  else if (mode == 2) launch_ring_t<T, VISC, 2, TJ>(A, blocks, tiles, gas, nwg, s);
-  else launch_ring_t<T, VISC, 3, TJ>(A, blocks, tiles, gas, nwg, s);
+  hipLaunchKernelGGL((k_stage_ring<T, VISC, MODE, TI, TJ>), dim3(nwg), dim3(TI * TJ), 0, s, A, blocks, tiles, gas);
+}
+
+template <typename T, bool VISC, int TI, int TJ>
+static void ring_mode(const StageArgs& A, int mode, const BlockDesc* blocks, const TileDesc* tiles,
+                      const Gas<T>& gas, int nwg, hipStream_t s, int* occ) {
+  if (mode == 0) ring_launch<T, VISC, 0, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
+  else if (mode == 1) ring_launch<T, VISC, 1, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
+  else if (mode == 2) ring_launch<T, VISC, 2, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
+  else ring_launch<T, VISC, 3, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
 }
 
 template <typename T, bool VISC>
-static bool ring_tj(const StageArgs& A, int mode, const BlockDesc* blocks, const TileDesc* tiles, const Gas<T>& gas,
-                    int nwg, hipStream_t s, int* occ) {
-  if (A.tile_j == 8) ring_mode<T, VISC, 8>(A, mode, blocks, tiles, gas, nwg, s, occ);
-  else if (A.tile_j == 4) ring_mode<T, VISC, 4>(A, mode, blocks, tiles, gas, nwg, s, occ);
+static bool ring_shape(const StageArgs& A, int mode, const BlockDesc* blocks, const TileDesc* tiles, const Gas<T>& gas,
+                       int nwg, hipStream_t s, int* occ) {
+  if (A.tile_j == 8 && A.tile_i == 64) ring_mode<T, VISC, 64, 8>(A, mode, blocks, tiles, gas, nwg, s, occ);
+  else if (A.tile_j == 8 && A.tile_i == 32) ring_mode<T, VISC, 32, 16>(A, mode, blocks, tiles, gas, nwg, s, occ);
+  else if (A.tile_j == 4 && A.tile_i == 32) ring_mode<T, VISC, 32, 8>(A, mode, blocks, tiles, gas, nwg, s, occ);
+  else if (A.tile_j == 4 && A.tile_i == 16) ring_mode<T, VISC, 16, 16>(A, mode, blocks, tiles, gas, nwg, s, occ);
   else return false;
   return true;
 }
@@ -369,11 +360,11 @@ static bool ring_tj(const StageArgs& A, int mode, const BlockDesc* blocks, const
 bool stage_ring(const StageArgs& A, int mode, bool visc, bool fp32, const BlockDesc* blocks, const TileDesc* tiles,
                 const Gas<double>& g64, const Gas<float>& g32, int nwg, hipStream_t s, int* occ) {
   if (fp32) {
-    return visc ? ring_tj<float, true>(A, mode, blocks, tiles, g32, nwg, s, occ)
-                : ring_tj<float, false>(A, mode, blocks, tiles, g32, nwg, s, occ);
+    return visc ? ring_shape<float, true>(A, mode, blocks, tiles, g32, nwg, s, occ)
+                : ring_shape<float, false>(A, mode, blocks, tiles, g32, nwg, s, occ);
   }
-  return visc ? ring_tj<double, true>(A, mode, blocks, tiles, g64, nwg, s, occ)
-              : ring_tj<double, false>(A, mode, blocks, tiles, g64, nwg, s, occ);
+  return visc ? ring_shape<double, true>(A, mode, blocks, tiles, g64, nwg, s, occ)
+              : ring_shape<double, false>(A, mode, blocks, tiles, g64, nwg, s, occ);
 }
 
 }  // namespace cfd

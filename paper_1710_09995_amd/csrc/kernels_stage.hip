@@ -34,13 +34,14 @@ __global__ void __launch_bounds__(256) k_stage_simple(StageArgs A, const BlockDe
     const TileDesc td = tiles[tile];
     const BlockDesc B = blocks[td.blk];
     const int i = td.i0 + tx;
-    const int kend = min(td.k0 + A.tile_k, B.n[2]);
+    int k0, kend;
+    tile_run(B.n[2], A.tile_k, td.kp, k0, kend);
     const double* qb = A.qs + B.qoff;
     const double* mb = A.met + B.moff;
     const double* vb = VISC ? A.vmet + B.voff : nullptr;
     for (int j = td.j0 + ty; j < min(td.j0 + A.tile_j, B.n[1]); j += nty) {
       if (i >= B.n[0]) break;
-      for (int k = td.k0; k < kend; ++k) {
+      for (int k = k0; k < kend; ++k) {
         const int64_t c = (int64_t)(k + NG) * B.sk + (int64_t)(j + NG) * B.sj + (i + NG);
         double Fl[5], Fu[5], D[3][5];
         for (int d = 0; d < 3; ++d) {

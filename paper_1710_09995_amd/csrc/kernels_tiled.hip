@@ -100,8 +100,9 @@ __global__ void CFD_TILED_BOUNDS(64 * TJ) k_stage_tiled(StageArgs A, const Block
     const TileDesc td = tiles[tile];
     const BlockDesc B = blocks[td.blk];
     const int ni = B.n[0], nj = B.n[1], nk = B.n[2];
-    const int i0 = td.i0, j0 = td.j0, k0 = td.k0;
-    const int kend = min(k0 + A.tile_k, nk);
+    const int i0 = td.i0, j0 = td.j0;
+    int k0, kend;
+    tile_run(nk, A.tile_k, td.kp, k0, kend);
     const int i = i0 + tx, j = j0 + ty;
     const bool act = i < ni && j < nj;
     const bool fi_ok = i <= ni && j < nj;   // this thread's lower i-face is needed

@@ -147,7 +147,7 @@ size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 int64_t max_tiles_for(int nblk, const cfd_dims* dims) {
   int64_t t = 0;
   for (int b = 0; b < nblk; ++b)
-    t += (int64_t)((dims[b].ni + TILE_I - 1) / TILE_I) * dims[b].nj * dims[b].nk;
+    t += (int64_t)((dims[b].ni + 31) / 32) * dims[b].nj * dims[b].nk;
   return t;
 }
 
@@ -339,6 +339,7 @@ struct cfd_ctx {
   int pm_off = 0, pm_count = 0, pm_threads = 0;
   TileDesc* dtiles = nullptr;
   int ntiles = 0;
+  int tile_i = 64;       // width of the stage kernel's tiles
   int64_t ncells = 0;
   int64_t nchunks = 0;   // 64-cell row chunks of the grid (time-step and norms kernels)
   cfd_tuning tun{2, 8, 32, 1, 1};   // replaced by default_tuning() when the blocks are created
@@ -503,8 +504,100 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
   return t;
 }
 
+// Cell columns that a launch computes with tiles of ti x tj columns, padding
+// included, times their planes; and the tiles' count.
+int64_t padded_cells(const std::vector<cfd_dims>& dims, int ti, int tj, int tk, int64_t* tiles) {
+  int64_t cells = 0, n = 0;
+  for (const auto& d : dims) {
+    const int64_t t = (int64_t)((d.ni + ti - 1) / ti) * ((d.nj + tj - 1) / tj);
+    cells += t * ti * tj * d.nk;
+    n += t * tile_runs(d.nk, tk);
+  }
+  if (tiles) *tiles = n;
+  return cells;
+}
+
+// Width of the plane-ring kernel's tiles of 64 tile_j columns: 32 or 64 wide
+// for tile_j 8 (32 x 16, 64 x 8), 32 or 16 for tile_j 4 (32 x 8, 16 x 16),
+// whichever pads the blocks' i and j extents less, and 32 wide where they pad
+// alike: it loads 1.41 (32 x 16) halo cells per cell instead of 1.59 (64 x 8),
+// and its 48 tile-edge faces take one pass of one wave instead of two waves'.
+// 256 x 128 x 128 NS, FP64: 1.774 ms a step against 1.791; 192 x 96 x 96
+// multigrid, FP64: 2.52 against 2.55 ms.
+int ring_tile_i(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t max_tiles) {
+  const int wide = t.tile_j == 8 ? 64 : 32, narrow = wide / 2, cols = 64 * t.tile_j;
+  int64_t nw = 0, nn = 0;
+  const int64_t pw = padded_cells(dims, wide, cols / wide, t.tile_k, &nw);
+  const int64_t pn = padded_cells(dims, narrow, cols / narrow, t.tile_k, &nn);
+  const bool take = t.tile_j == 8 ? pn <= pw : pn < pw;
+  if (nw > max_tiles) return narrow;
+  return take && nn <= max_tiles ? narrow : wide;
+}
+
+// Estimated cost of a plane-ring launch, in plane times of one compute unit's
+// worth of workgroups: rounds of the persistent grid x (planes of a tile + its
+// start, whose three plane fills and gathered k-face take about 1.5 planes),
+// the last round with the deepest tile.
+// per_cu: workgroups resident per compute unit.
+double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t max_tiles, int num_cu, int per_cu) {
+  const int ti = ring_tile_i(dims, t, max_tiles);
+  int64_t n = 0, planes = 0;
+  int deepest = 0;
+  for (const auto& d : dims) {
+    int k0, k1;
+    tile_run(d.nk, t.tile_k, 0, k0, k1);
+    deepest = std::max(deepest, k1);
+    const int64_t cols = (int64_t)((d.ni + ti - 1) / ti) * ((d.nj + 64 * t.tile_j / ti - 1) / (64 * t.tile_j / ti));
+    n += cols * tile_runs(d.nk, t.tile_k);
+    planes += cols * d.nk;
+  }
+  const int64_t resident = (int64_t)num_cu * per_cu;
+  return (double)((n + resident - 1) / resident - 1) * ((double)planes / (double)n + 1.5) + (deepest + 1.5);
+}
+
+// Default tuning for the grid: the plane-ring kernel, its tiles' depth (4 to
+// 32 planes) the one of least estimated cost, which weighs each tile's start
+// against the last round of the persistent grid.  FP32-flux kernels take
+// 256-column tiles (tile_j 4): chain of 40 uneven Euler blocks 4.42 ms a step
+// against 4.64 with 512 columns, 2 x 2 blocks of 250 x 203 x 72 NS 5.37
+// against 5.47.  FP64 kernels take 512 columns (256 x 128 x 128 NS 1.774
+// against 1.787 ms) unless 256-column tiles pad the blocks that much less
+// (128 blocks of 48 x 24 x 24, multigrid, 5.87 against 6.60 ms); both keep two
+// waves per SIMD.
+// A grid too small to give every CU a 64 x 8 x 4 tile gets the tiled kernel
+// with 4-row tiles, tile_k halved (down to 1) until there are 4 tiles per CU:
+// on such small grids the launch's latency, not the halo planes each shallow
+// tile reloads, bounds the stage (measured on the 96x48x48 and 48x24x24 levels
+// of a multigrid cycle: 64x4x1 tiles took the cycle from 1.45 to 1.26 ms
+// against 64x4x4 and 64x2x4).
+cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p, int64_t max_tiles) {
+  cfd_tuning best{2, 8, 32, 1, 1};
+  int64_t small = 0;
+  padded_cells(dims, TILE_I, 8, 4, &small);
+  if (small < num_cu) {
+    cfd_tuning t{0, 4, 4, 1, 1};
+    int64_t n = 0;
+    while (t.tile_k > 1 && (padded_cells(dims, TILE_I, t.tile_j, t.tile_k, &n), n < 4 * (int64_t)num_cu)) t.tile_k /= 2;
+    return t;
+  }
+  double least = 0.0;
+  for (int tj = p.flux_fp32 ? 4 : 8; tj >= 4; tj /= 2)
+    for (int tk = 32; tk >= 4; --tk) {
+      const cfd_tuning t{2, tj, tk, 1, 1};
+      const int per_cu = (8 / tj) * (p.flux_fp32 && !p.viscous ? 2 : 1);
+      const double cost = ring_cost(dims, t, max_tiles, num_cu, per_cu) * (tj == 8 ? 1.0 : 1.05);
+      if (least == 0.0 || cost < least) {
+        least = cost;
+        best = t;
+      }
+    }
+  return best;
+}
+
 void build_tiles(cfd_ctx* c, hipStream_t s) {
-  const int tj = c->tun.tile_j, tk = c->tun.tile_k;
+  const int tk = c->tun.tile_k;
+  c->tile_i = c->tun.kernel == 2 ? ring_tile_i(c->dims, c->tun, c->W.max_tiles) : TILE_I;
+  const int ti = c->tile_i, tj = c->tun.tile_j * TILE_I / ti;
   struct T2 {
     TileDesc t;
     int64_t work;
@@ -512,12 +605,15 @@ void build_tiles(cfd_ctx* c, hipStream_t s) {
   std::vector<T2> v;
   for (int b = 0; b < c->nblk; ++b) {
     const cfd_dims& d = c->dims[b];
-    for (int k0 = 0; k0 < d.nk; k0 += tk)
+    for (int kp = 0; kp < tile_runs(d.nk, tk); ++kp) {
+      int k0, k1;
+      tile_run(d.nk, tk, kp, k0, k1);
       for (int j0 = 0; j0 < d.nj; j0 += tj)
-        for (int i0 = 0; i0 < d.ni; i0 += TILE_I) {
-          const int64_t w = (int64_t)std::min(TILE_I, d.ni - i0) * std::min(tj, d.nj - j0) * std::min(tk, d.nk - k0);
-          v.push_back({{b, i0, j0, k0}, w});
+        for (int i0 = 0; i0 < d.ni; i0 += ti) {
+          const int64_t w = (int64_t)std::min(ti, d.ni - i0) * std::min(tj, d.nj - j0) * (k1 - k0);
+          v.push_back({{b, i0, j0, kp}, w});
         }
+    }
   }
   if ((int64_t)v.size() > c->W.max_tiles) fail(CFD_EINTERNAL, "tile list overflow");
   std::vector<TileDesc> h;
@@ -595,6 +691,7 @@ StageArgs stage_args(cfd_ctx* c) {
   A.local_dt = c->params.local_dt;
   A.dt = c->params.local_dt ? c->scal() : c->d_dt();
   A.ntiles = c->ntiles;
+  A.tile_i = c->tile_i;
   A.tile_j = c->tun.tile_j;
   A.tile_k = c->tun.tile_k;
   A.sp = c->SP;
@@ -606,13 +703,14 @@ StageArgs stage_args(cfd_ctx* c) {
 int stage_nwg(cfd_ctx* c, int mode) {
   if (c->tun.kernel == 1) return nwg_for(c, 8);
   const int key = (c->params.viscous ? 1 : 0) | (c->params.flux_fp32 ? 2 : 0) | (mode << 2) |
-                  ((c->tun.tile_j == 2 ? 0 : c->tun.tile_j == 4 ? 1 : 2) << 4) | (c->tun.kernel << 6);
+                  ((c->tun.tile_j == 2 ? 0 : c->tun.tile_j == 4 ? 1 : 2) << 4) | (c->tun.kernel << 6) | (c->tile_i << 8);
   auto it = c->occ_cache.find(key);
   int occ;
   if (it != c->occ_cache.end()) {
     occ = it->second;
   } else {
     StageArgs A{};
+    A.tile_i = c->tile_i;
     A.tile_j = c->tun.tile_j;
     const bool ok = c->tun.kernel == 2
                         ? stage_ring(A, mode, c->params.viscous != 0, c->params.flux_fp32 != 0, nullptr, nullptr,
@@ -1009,7 +1107,7 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
       HIPCHK(hipMemcpyAsync(c->d_cell_start(), cs.data(), sizeof(int64_t) * cs.size(), hipMemcpyHostToDevice,
                             stream));
     }
-    c->tun = default_tuning(c->dims, c->num_cu, c->params);
+    c->tun = default_tuning(c->dims, c->num_cu, c->params, c->W.max_tiles);
     build_tiles(c, stream);
     *out = c;
   });
