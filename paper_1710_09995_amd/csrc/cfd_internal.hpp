@@ -80,6 +80,7 @@ struct Gas {
 constexpr int MLP_KIN = 16;          // input features padded to one MFMA k-step
 constexpr int MLP_NOUT = 16;         // outputs padded to one MFMA tile
 constexpr int MLP_MAX_LAYERS = 9;
+constexpr int MLP_SPLITS = 64;       // most point splits of the weight gradients
 struct MlpDims {
   int d_in, d_hidden, n_hidden, d_out;
   int nlayer;                        // n_hidden + 1 weight matrices

@@ -50,7 +50,9 @@ void mlp_forward(const MlpDims& D, const uint16_t* P, const float* x, const int3
 int mlp_mse(const float* y, const float* t, const int32_t* idx, int64_t n, int d_out, float* dy, double* partials,
             int max_rows, double* loss, hipStream_t s);
 void mlp_backward(const MlpDims& D, const uint16_t* P, const float* cache, const float* dy, int64_t n, float* grad,
-                  float* dz, float* da, float* part, int nchunk, hipStream_t s);
+                  float* dzT, float* part, hipStream_t s);
+int mlp_splits(int64_t n);
+int64_t mlp_dz_floats(const MlpDims& D, int64_t n);
 void mlp_adam(int64_t np, float* master, float* m, float* v, const float* g, uint16_t* pbf, float lr, float b1,
               float b2, float eps, int t, hipStream_t s);
 void mlp_to_bf16(int64_t np, const float* master, uint16_t* pbf, hipStream_t s);
@@ -1505,7 +1507,6 @@ cfd_status cfd_copy_metrics(cfd_ctx* c, int32_t blk, double* out, hipStream_t s)
 
 namespace {
 
-constexpr int MLP_CHUNKS = 32;       // point chunks of the weight-gradient reduction
 constexpr int MLP_MSE_ROWS = 1024;   // loss partial rows
 
 MlpDims mlp_dims(const cfd_mlp_desc* d) {
@@ -1540,11 +1541,17 @@ MlpDims mlp_dims(const cfd_mlp_desc* d) {
   return D;
 }
 
-size_t mlp_work_bytes(const MlpDims& D, int64_t n) {
-  const size_t act = align256((size_t)n * D.d_hidden * sizeof(float));
-  int64_t maxw = 0;
-  for (int l = 0; l < D.nlayer; ++l) maxw = std::max<int64_t>(maxw, (int64_t)D.N[l] * D.K[l] + D.N[l]);
-  return 2 * act + align256((size_t)MLP_CHUNKS * maxw * sizeof(float)) + align256(MLP_MSE_ROWS * sizeof(double));
+// Work buffer of the loss and the backward pass: dZ of every layer, the
+// weight-gradient splits, the loss partials.
+struct MlpWork {
+  size_t part, mse, total;
+};
+MlpWork mlp_work(const MlpDims& D, int64_t n) {
+  MlpWork W;
+  W.part = align256((size_t)mlp_dz_floats(D, n) * sizeof(float));
+  W.mse = W.part + align256((size_t)mlp_splits(n) * D.nparam * sizeof(float));
+  W.total = W.mse + align256(MLP_MSE_ROWS * sizeof(double));
+  return W;
 }
 
 }  // namespace
@@ -1556,7 +1563,7 @@ cfd_status cfd_mlp_sizes(const cfd_mlp_desc* desc, int64_t n, int64_t* n_params,
     if (n < 0) fail(CFD_EINVAL, "n must be >= 0");
     if (n_params) *n_params = D.nparam;
     if (cache_per_point) *cache_per_point = D.cache_per_point;
-    if (work_bytes) *work_bytes = mlp_work_bytes(D, n);
+    if (work_bytes) *work_bytes = mlp_work(D, n).total;
   });
 }
 
@@ -1576,12 +1583,9 @@ cfd_status cfd_mlp_mse(const cfd_mlp_desc* desc, const float* y, const float* t,
   return guard(nullptr, [&] {
     const MlpDims D = mlp_dims(desc);
     if (!y || !t || !dy || !loss || n <= 0 || !work) fail(CFD_EINVAL, "bad mse arguments");
-    if (work_bytes < mlp_work_bytes(D, n)) fail(CFD_ENOMEM, "mlp workspace too small");
-    const size_t act = align256((size_t)n * D.d_hidden * sizeof(float));
-    int64_t maxw = 0;
-    for (int l = 0; l < D.nlayer; ++l) maxw = std::max<int64_t>(maxw, (int64_t)D.N[l] * D.K[l] + D.N[l]);
-    double* part = reinterpret_cast<double*>(static_cast<char*>(work) + 2 * act +
-                                             align256((size_t)MLP_CHUNKS * maxw * sizeof(float)));
+    const MlpWork W = mlp_work(D, n);
+    if (work_bytes < W.total) fail(CFD_ENOMEM, "mlp workspace too small");
+    double* part = reinterpret_cast<double*>(static_cast<char*>(work) + W.mse);
     mlp_mse(y, t, idx, n, D.d_out, dy, part, MLP_MSE_ROWS, loss, s);
     check_launch();
   });
@@ -1592,13 +1596,10 @@ cfd_status cfd_mlp_backward(const cfd_mlp_desc* desc, const uint16_t* params, co
   return guard(nullptr, [&] {
     const MlpDims D = mlp_dims(desc);
     if (!params || !cache || !dy || !grad || n <= 0 || !work) fail(CFD_EINVAL, "bad backward arguments");
-    if (work_bytes < mlp_work_bytes(D, n)) fail(CFD_ENOMEM, "mlp workspace too small");
-    const size_t act = align256((size_t)n * D.d_hidden * sizeof(float));
+    const MlpWork W = mlp_work(D, n);
+    if (work_bytes < W.total) fail(CFD_ENOMEM, "mlp workspace too small");
     char* w = static_cast<char*>(work);
-    float* dz = reinterpret_cast<float*>(w);
-    float* da = reinterpret_cast<float*>(w + act);
-    float* part = reinterpret_cast<float*>(w + 2 * act);
-    mlp_backward(D, params, cache, dy, n, grad, dz, da, part, MLP_CHUNKS, s);
+    mlp_backward(D, params, cache, dy, n, grad, reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + W.part), s);
     check_launch();
   });
 }
