@@ -349,15 +349,16 @@ struct cfd_ctx {
   Gas<double> g64{};
   Gas<float> g32{};
   hipStream_t cap_stream = nullptr;
-  // Captured time steps, for the state pointer graph_q: one step, and
-  // STEPS_PER_GRAPH steps for runs without a history (one graph launch, and
-  // its start-up gap, per STEPS_PER_GRAPH steps).
+  // Captured time steps, for the state pointer graph_q: by step count (one, or
+  // STEPS_PER_GRAPH for runs without a history: one graph launch, and its
+  // start-up gap, per STEPS_PER_GRAPH steps) and StepKind.
   static constexpr int STEPS_PER_GRAPH = 8;
+  struct StepGraph {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+  };
   const void* graph_q = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  hipGraph_t graph_n = nullptr;
-  hipGraphExec_t gexec_n = nullptr;
+  std::map<int, StepGraph> step_graphs;
   // A captured multigrid cycle led by this context (the finest level), valid
   // for the hierarchy and arguments in mg_key; id is unique per context and
   // gen counts its retunings, so a cycle over a level since retuned or
@@ -417,15 +418,12 @@ struct cfd_ctx {
   CellMap cell_map() const { return CellMap{dblocks, d_cell_start(), nblk}; }
 
   void drop_graph() {
-    if (gexec) hipGraphExecDestroy(gexec);
-    if (graph) hipGraphDestroy(graph);
-    if (gexec_n) hipGraphExecDestroy(gexec_n);
-    if (graph_n) hipGraphDestroy(graph_n);
-    gexec = nullptr;
-    graph = nullptr;
+    for (auto& g : step_graphs) {
+      if (g.second.exec) hipGraphExecDestroy(g.second.exec);
+      if (g.second.graph) hipGraphDestroy(g.second.graph);
+    }
+    step_graphs.clear();
     graph_q = nullptr;
-    gexec_n = nullptr;
-    graph_n = nullptr;
     drop_mg_graph();
   }
   void drop_mg_graph() {
@@ -759,25 +757,37 @@ void time_step_pass(cfd_ctx* c, const double* q, hipStream_t s, bool min_dt = tr
 // slower on inviscid flow, whose stage kernel is cheap next to it).
 bool fused_dt(const cfd_ctx* c) { return c->tun.kernel == 2 && c->params.viscous; }
 
+// What a step does besides its stages.  first / last: of a run of steps over
+// which stage 3 hands the next step its time step (fused_dt).
+struct StepKind {
+  bool history = false, first = true, last = true;
+  int key() const { return history + 2 * first + 4 * last; }
+};
+
 // One full RK3 step: 3 x (ghost fill + stage), the time step of Q^n and the
 // history row (dt, L2(R(Q^n)), sum V Q^n, max |R_rho|).
 //  - Time step: with fused_dt, left in d_dt (and the per-cell arena) by the
-//    previous step's stage 3, or by the time-step pass cfd_step runs before
-//    its first step; otherwise a time-step pass first (k_dt writes partial
-//    rows [0, nwg_dt) of part_dt: min dt, sum V Q^n).
+//    previous step's stage 3, except in the first step of a run (the state may
+//    have changed since) and not evaluated in the last (nobody reads it);
+//    otherwise a time-step pass first (k_dt writes partial rows [0, nwg_dt) of
+//    part_dt: min dt, sum V Q^n).
 //  - History: the plane-ring kernel's stage 1 reduces the norm partials of
 //    R(Q^n) itself; the other kernels write R(Q^n) to qb (free until stage 2
 //    overwrites it) and the norms kernel adds the R rows after k_dt's (only
-//    when the step keeps a history: without one they skip both).
+//    when the step keeps a history: without one they skip both, and the
+//    finalize).
 //  - Totals sum V Q^n: always from rows [0, nwg_dt) of a row-chunk kernel
-//    (k_dt, or with the plane-ring kernel k_norms over Q^n, only when the
-//    step keeps a history), whose cut of the grid does not depend on the
-//    tiles; the rows after them carry zeros in those slots, so the fixed-order
-//    finalize gives the same totals for every tuning and stage kernel.
+//    (k_dt where the step runs it, else k_norms over Q^n), whose cut of the
+//    grid does not depend on the tiles; the rows after them carry zeros in
+//    those slots, so the fixed-order finalize gives the same totals for every
+//    tuning and stage kernel.
+// One step of 256 x 128 x 128 NS with its history row: the totals from k_dt
+// save 42 us of k_norms, the time step not evaluated in the last stage 64 us.
 // (Taking dt of the new state inside the tiled kernel's third stage was
 // measured slower: its extra metric loads cost more than the separate pass.)
-void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, bool history, const double* force = nullptr,
+void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, const double* force = nullptr,
                   bool no_fuse = false) {
+  const bool history = kind.history;
   const bool ring = c->tun.kernel == 2;
   const bool fuse = fused_dt(c) && !no_fuse && !force;
   const int nwg_f = dt_nwg(c);
@@ -795,7 +805,8 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, bool history, const doub
   ghost_fill(c, q, s);
   // Local steps without a history row read no minimum step: every stage and
   // the forcing take the per-cell steps.
-  if (!fuse) time_step_pass(c, q, s, history || !c->params.local_dt);
+  const bool pass = !fuse || kind.first;
+  if (pass) time_step_pass(c, q, s, history || !c->params.local_dt);
   StageArgs A = stage_args(c);
   A.qs = q;
   A.qn = q;
@@ -803,14 +814,16 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, bool history, const doub
   A.force = force_in_stage;
   A.fb = 1.0;
   if (ring) {
+    double* rows = pass ? c->part_dt() : c->part_nrm();
     const int ntot = history ? nwg_dt : 0;
-    if (history)
+    if (history && !pass)
       timed(c, 3, s, [&] {
-        launch_norms(q, nullptr, c->met(), c->part_nrm(), c->dblocks, c->nblk, c->nchunks, nwg_dt, s);
+        launch_norms(q, nullptr, c->met(), rows, c->dblocks, c->nblk, c->nchunks, nwg_dt, s);
       });
-    A.partials = c->part_nrm() + (int64_t)ntot * NPART;
+    A.partials = rows + (int64_t)ntot * NPART;
     launch_stage(c, A, 1, s);
-    launch_finalize(c->part_nrm(), ntot + stage_nwg(c, 1), 1, inv_n, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
+    if (history)
+      launch_finalize(rows, ntot + stage_nwg(c, 1), 1, inv_n, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
   } else if (history) {
     A.rout = c->qb();
     launch_stage(c, A, 1, s);
@@ -839,7 +852,7 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, bool history, const doub
   A.a = 1.0 / 3.0;
   A.b = 2.0 / 3.0;
   A.fb = 2.0 / 3.0;
-  if (fuse) {
+  if (fuse && !kind.last) {
     A.partials = c->part_dt();
     A.dt_out = c->params.local_dt ? c->scal() : nullptr;
     launch_stage(c, A, 3, s);
@@ -1226,50 +1239,50 @@ cfd_status cfd_step(cfd_ctx* c, double* q, int32_t nsteps, double* hist, hipStre
   return guard(c, [&] {
     if (!c || !q) fail(CFD_EINVAL, "NULL argument");
     if (nsteps < 0) fail(CFD_EINVAL, "nsteps must be >= 0");
-    // with fused_dt a step takes the time step of Q^n from the step before;
-    // the state may have changed since, so the first one is computed here
-    if (nsteps > 0 && fused_dt(c)) time_step_pass(c, q, s);
-    if (c->tun.use_graph && !c->profiling) {
-      if (c->graph_q != q) {
-        c->drop_graph();
-        c->graph_q = q;
-      }
-      // the one-step graph keeps the history (totals pass included); the
-      // multi-step graph serves runs without one
-      auto capture = [&](int steps, bool history, hipGraph_t& g, hipGraphExec_t& ge) {
-        HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-        try {
-          for (int n = 0; n < steps; ++n) enqueue_step(c, q, c->cap_stream, history);
-        } catch (...) {
-          hipGraph_t gg = nullptr;
-          hipStreamEndCapture(c->cap_stream, &gg);
-          if (gg) hipGraphDestroy(gg);
-          throw;
+    const bool graph = c->tun.use_graph && !c->profiling;
+    if (graph && c->graph_q != q) {
+      c->drop_graph();
+      c->graph_q = q;
+    }
+    const bool fused = fused_dt(c);
+    for (int n = 0; n < nsteps;) {
+      const int run = graph && !hist && nsteps - n >= cfd_ctx::STEPS_PER_GRAPH ? cfd_ctx::STEPS_PER_GRAPH : 1;
+      StepKind kind;
+      kind.history = hist != nullptr;
+      kind.first = !fused || n == 0;
+      kind.last = !fused || n + run == nsteps;
+      auto enqueue = [&](hipStream_t st) {
+        for (int m = 0; m < run; ++m) {
+          StepKind k = kind;
+          k.first = !fused || (kind.first && m == 0);
+          k.last = !fused || (kind.last && m == run - 1);
+          enqueue_step(c, q, st, k);
         }
-        HIPCHK(hipStreamEndCapture(c->cap_stream, &g));
-        HIPCHK(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
       };
-      int n0 = 0;
-      if (!hist && nsteps >= cfd_ctx::STEPS_PER_GRAPH) {
-        if (!c->gexec_n) capture(cfd_ctx::STEPS_PER_GRAPH, false, c->graph_n, c->gexec_n);
-        for (; n0 + cfd_ctx::STEPS_PER_GRAPH <= nsteps; n0 += cfd_ctx::STEPS_PER_GRAPH)
-          HIPCHK(hipGraphLaunch(c->gexec_n, s));
-      }
-      if (n0 < nsteps && !c->gexec) capture(1, true, c->graph, c->gexec);
-      for (int n = n0; n < nsteps; ++n) {
-        HIPCHK(hipGraphLaunch(c->gexec, s));
-        if (hist)
-          HIPCHK(hipMemcpyAsync(hist + (int64_t)n * NHIST, c->d_hist(), sizeof(double) * NHIST,
-                                hipMemcpyDeviceToDevice, s));
-      }
-    } else {
-      for (int n = 0; n < nsteps; ++n) {
-        enqueue_step(c, q, s, hist != nullptr);
+      if (graph) {
+        cfd_ctx::StepGraph& g = c->step_graphs[run * 8 + kind.key()];
+        if (!g.exec) {
+          HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
+          try {
+            enqueue(c->cap_stream);
+          } catch (...) {
+            hipGraph_t gg = nullptr;
+            hipStreamEndCapture(c->cap_stream, &gg);
+            if (gg) hipGraphDestroy(gg);
+            throw;
+          }
+          HIPCHK(hipStreamEndCapture(c->cap_stream, &g.graph));
+          HIPCHK(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
+        }
+        HIPCHK(hipGraphLaunch(g.exec, s));
+      } else {
+        enqueue(s);
         check_launch();
-        if (hist)
-          HIPCHK(hipMemcpyAsync(hist + (int64_t)n * NHIST, c->d_hist(), sizeof(double) * NHIST,
-                                hipMemcpyDeviceToDevice, s));
       }
+      if (hist)
+        HIPCHK(hipMemcpyAsync(hist + (int64_t)n * NHIST, c->d_hist(), sizeof(double) * NHIST,
+                              hipMemcpyDeviceToDevice, s));
+      n += run;
     }
   });
 }
@@ -1355,7 +1368,9 @@ void enqueue_mg_cycle(cfd_ctx* const* lv, double* const* q, int L, int pre, int 
     const int steps = l == L - 1 ? coarse : pre;
     for (int n = 0; n < steps; ++n) {
       const bool rec = record && l == 0 && n == 0;
-      enqueue_step(c, q[l], s, rec, l ? F[l] : nullptr, true);
+      StepKind kind;
+      kind.history = rec;
+      enqueue_step(c, q[l], s, kind, l ? F[l] : nullptr, true);
       if (rec && hist)
         HIPCHK(hipMemcpyAsync(hist, c->d_hist(), sizeof(double) * NHIST, hipMemcpyDeviceToDevice, s));
     }
