@@ -110,13 +110,15 @@ typedef struct {
  *   block's k range is cut into runs of nearly equal length).  The tiled
  *   kernel (tile_j = 2, 4 or 8) takes 64 x tile_j columns; the plane-ring
  *   kernel 64 x 8 or 32 x 16 (tile_j 8), 32 x 8 or 16 x 16 (tile_j 4),
- *   whichever pads the blocks less.  Defaults (set by cfd_create_blocks):
- *   kernel 2, tile_j 8 (4 for FP32 fluxes, and where it pads an FP64 grid
- *   that much less), tile_k the depth in [4, 32] of least estimated cost for
- *   the grid, use_graph 1, order 1; a grid with fewer 64 x 8 x 4 tiles than
- *   CUs gets the tiled kernel with tile_j 4 and tile_k halved from 4 (down to
- *   1) until it has four tiles per CU.
- * use_graph: 1 captures one time step in a hipGraph and replays it.
+ *   whichever pads the blocks less.  The tiled kernel's one-plane tiles
+ *   (tile_k 1) run as bricks of 8 x 4 x 4 cells, one face a thread, which for
+ *   inviscid flow form their ghost states as they read them.  Defaults (set by
+ *   cfd_create_blocks): up to seven bricks a CU, kernel 0, tile_j 4, tile_k 1;
+ *   above, kernel 2 with tile_j 8 (4 for FP32 fluxes, and where it pads or
+ *   splits an FP64 grid that much better) and tile_k the depth in [4, 32] of
+ *   least estimated cost for the grid; use_graph 1, order 1.
+ * use_graph: 1 captures time steps in hipGraphs and replays them (single steps
+ *   of inviscid bricks are launched as they are: five short kernels).
  * order: tile work-list order.  0 = largest tiles first (balances uneven
  *   blocks); 1 = XCD-aware: the tiles are cut into 8 spatially contiguous
  *   chunks and interleaved so that every workgroup of the persistent grid on

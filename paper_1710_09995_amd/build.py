@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcfd.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["runtime.hip", "kernels_grid.hip", "kernels_stage.hip", "kernels_tiled.hip", "kernels_ring.hip",
+SOURCES = ["runtime.hip", "kernels_grid.hip", "kernels_stage.hip", "kernels_tiled.hip", "kernels_ring.hip", "kernels_brick.hip",
            "kernels_mlp.hip", "kernels_highorder.hip", "kernels_implicit.hip", "kernels_mg.hip", "partition.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

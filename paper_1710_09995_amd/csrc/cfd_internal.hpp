@@ -58,6 +58,9 @@ struct TileDesc {
   int32_t blk, i0, j0, kp;
 };
 
+// Cells of the brick kernel's tiles (their kp counts whole bricks along k).
+constexpr int BRICK_I = 8, BRICK_J = 4, BRICK_K = 4;
+
 __host__ __device__ inline int tile_runs(int nk, int tile_k) { return (nk + tile_k - 1) / tile_k; }
 
 // planes [k0, k1) of run kp
@@ -127,11 +130,21 @@ struct StageArgs {
   int32_t ntiles;
   int32_t tile_i, tile_j, tile_k;   // plane-ring kernel: tiles of tile_i x (64 tile_j / tile_i) columns
   StepParams sp;      // flow and CFL parameters (mode 3)
-  // A multigrid level's forcing, applied by the tiled and simple kernels in
+  // A multigrid level's forcing, applied by the tiled, brick and simple kernels in
   // modes 1-2 (null: none): out = out - (fb dt) F, rounded as the separate
   // forcing pass rounds it.
   const double* force;
   double fb;
+  // Brick kernel.  rows, nrows: the time-step kernel's partial rows, whose
+  // minimum (slot 12) every workgroup of stage 1 takes itself and workgroup 0
+  // leaves in dt_min (null: dt holds the step).  patches, patch_first: the
+  // faces' patches by block and face, for inviscid flow, whose ghost states the
+  // kernel then forms as it reads them (null: it reads qs's ghost cells).
+  const double* rows;
+  int32_t nrows;
+  double* dt_min;
+  const PatchDesc* patches;
+  const int32_t* patch_first;
 };
 
 

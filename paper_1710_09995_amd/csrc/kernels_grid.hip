@@ -10,21 +10,12 @@
 #include "cfd_internal.hpp"
 #include "physics.hpp"
 #include "stage_common.hpp"
+#include "ghosts.hpp"
 
 namespace cfd {
 
 __device__ __forceinline__ int64_t stride_of(int d, int64_t sj, int64_t sk) {
   return d == 0 ? 1 : (d == 1 ? sj : sk);
-}
-
-// Offset (relative to the padded origin) of logical index (a along d, p1
-// along t1, p2 along t2) with t1 < t2 the transverse directions.
-__device__ __forceinline__ int64_t pos3(int d, int a, int p1, int p2, int64_t sj, int64_t sk) {
-  int i, j, k;
-  if (d == 0) { i = a; j = p1; k = p2; }
-  else if (d == 1) { j = a; i = p1; k = p2; }
-  else { k = a; i = p1; j = p2; }
-  return (int64_t)(k + NG) * sk + (int64_t)(j + NG) * sj + (i + NG);
 }
 
 __global__ void k_copy_nodes(const double* __restrict__ src, double* __restrict__ x, BlockDesc B) {
@@ -161,139 +152,11 @@ __global__ void k_metric_ghosts(double* __restrict__ met, const BlockDesc* __res
   }
 }
 
-// Ghost fill of the conserved state (one sweep, all patches of all blocks).
-// One thread per transverse point, except on i-faces: there the NG ghost
-// cells of a row are adjacent in memory while neighbouring points are a row
-// apart, so a thread per (point, layer) puts a row's layers on adjacent lanes
-// and halves the memory segments each access touches.
-// With delta set, q is an update (the implicit step's dQ): connections copy it
-// as they copy the state, and the ghost cells of physical patches get zero.
+// Ghost fill of the conserved state: one sweep, all patches of all blocks.
 __global__ void k_ghost_q(double* __restrict__ q, const double* __restrict__ met,
                           const BlockDesc* __restrict__ blocks,
                           const PatchDesc* __restrict__ patches, StepParams SP, int delta) {
-  const PatchDesc& P = patches[blockIdx.y];
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int d = P.face >> 1, side = P.face & 1;
-  const int per = ghost_threads_per_point(P.kind, d);
-  if (t >= P.count * per) return;
-  const int pt = t / per;
-  // transverse directions t1 < t2, selected without indexing (keeps P out of scratch)
-  const int lo1 = d == 0 ? P.lo[1] : P.lo[0], hi1 = d == 0 ? P.hi[1] : P.hi[0];
-  const int lo2 = d == 2 ? P.lo[1] : P.lo[2];
-  const int w1 = hi1 - lo1;
-  const int p1 = lo1 + pt % w1, p2 = lo2 + pt / w1;
-  const BlockDesc& B = blocks[P.blk];
-  const int n = d == 0 ? B.n[0] : (d == 1 ? B.n[1] : B.n[2]);
-  double* qb = q + B.qoff;
-  if (P.kind == 0) {
-    const BlockDesc& N = blocks[P.nbr];
-    const double* qn = q + N.qoff;
-    const int nn = d == 0 ? N.n[0] : (d == 1 ? N.n[1] : N.n[2]);
-    const int o1 = d == 0 ? P.noff[1] : P.noff[0], o2 = d == 2 ? P.noff[1] : P.noff[2];
-    // Every load before the first store: source and destination share one
-    // arena, so a load issued after a store would wait for it.
-    if (per != 1) {     // this thread's layer only
-      const int m = 1 + t % per;
-      const int64_t od = pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk);
-      const int64_t os = pos3(d, side == 0 ? nn - m : m - 1, p1 + o1, p2 + o2, N.sj, N.sk);
-      double val[NV];
-      for (int v = 0; v < NV; ++v) val[v] = qn[v * N.sv + os];
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od] = val[v];
-      return;
-    }
-    double val[NG][NV];
-    int64_t od[NG];
-    for (int m = 1; m <= NG; ++m) {
-      const int gm = side == 0 ? -m : n - 1 + m;
-      const int sm = side == 0 ? nn - m : m - 1;
-      od[m - 1] = pos3(d, gm, p1, p2, B.sj, B.sk);
-      const int64_t os = pos3(d, sm, p1 + o1, p2 + o2, N.sj, N.sk);
-      for (int v = 0; v < NV; ++v) val[m - 1][v] = qn[v * N.sv + os];
-    }
-    for (int m = 0; m < NG; ++m)
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od[m]] = val[m][v];
-    return;
-  }
-  if (delta) {
-    if (per != 1) {     // this thread's layer only
-      const int m = 1 + t % per;
-      const int64_t od = pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk);
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od] = 0.0;
-      return;
-    }
-    for (int m = 1; m <= NG; ++m) {
-      const int64_t od = pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk);
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od] = 0.0;
-    }
-    return;
-  }
-  // boundary face vector at this transverse position
-  const int fa = side == 0 ? 0 : n;
-  const int64_t of = pos3(d, fa, p1, p2, B.sj, B.sk);
-  const double* mb = met + B.moff;
-  const double sx = mb[(3 * d) * B.sv + of], sy = mb[(3 * d + 1) * B.sv + of],
-               sz = mb[(3 * d + 2) * B.sv + of];
-  const double nrm = sqrt(sx * sx + sy * sy + sz * sz);
-  const double nx = sx / nrm, ny = sy / nrm, nz = sz / nrm;
-  const int a0 = side == 0 ? 0 : n - 1;
-  if (P.kind == CFD_BC_KIND_FARFIELD || P.kind == CFD_BC_KIND_EXTRAP) {
-    const int64_t o0 = pos3(d, a0, p1, p2, B.sj, B.sk);
-    double qi[5], qg[5];
-    for (int v = 0; v < NV; ++v) qi[v] = qb[v * B.sv + o0];
-    if (P.kind == CFD_BC_KIND_FARFIELD) {
-      const double s = side == 0 ? -1.0 : 1.0;
-      farfield_state(qi, s * nx, s * ny, s * nz, SP.gamma, P.uinf, qg);
-    } else {
-      for (int v = 0; v < NV; ++v) qg[v] = qi[v];
-    }
-    if (per != 1) {     // this thread's layer only
-      const int m = 1 + t % per;
-      const int64_t od = pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk);
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od] = qg[v];
-      return;
-    }
-    for (int m = 1; m <= NG; ++m) {
-      const int gm = side == 0 ? -m : n - 1 + m;
-      const int64_t od = pos3(d, gm, p1, p2, B.sj, B.sk);
-      for (int v = 0; v < NV; ++v) qb[v * B.sv + od] = qg[v];
-    }
-    return;
-  }
-  // walls: ghost layer m mirrors interior cell m - 1
-  auto wall = [&](const double w[NV], int64_t od) {
-    const double mx = w[1], my = w[2], mz = w[3];
-    double gx, gy, gz;
-    if (P.kind == CFD_BC_KIND_SLIPWALL) {
-      const double mn = mx * nx + my * ny + mz * nz;
-      gx = mx - 2.0 * mn * nx;
-      gy = my - 2.0 * mn * ny;
-      gz = mz - 2.0 * mn * nz;
-    } else {  // no-slip adiabatic
-      gx = -mx;
-      gy = -my;
-      gz = -mz;
-    }
-    qb[od] = w[0];
-    qb[B.sv + od] = gx;
-    qb[2 * B.sv + od] = gy;
-    qb[3 * B.sv + od] = gz;
-    qb[4 * B.sv + od] = w[4];
-  };
-  if (per != 1) {       // this thread's layer only
-    const int m = 1 + t % per;
-    const int64_t oi = pos3(d, side == 0 ? m - 1 : n - m, p1, p2, B.sj, B.sk);
-    double w[NV];
-    for (int v = 0; v < NV; ++v) w[v] = qb[v * B.sv + oi];
-    wall(w, pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk));
-    return;
-  }
-  double wv[NG][NV];       // the mirrored interior cells, all loaded before any store
-  for (int m = 1; m <= NG; ++m) {
-    const int im = side == 0 ? m - 1 : n - m;
-    const int64_t oi = pos3(d, im, p1, p2, B.sj, B.sk);
-    for (int v = 0; v < NV; ++v) wv[m - 1][v] = qb[v * B.sv + oi];
-  }
-  for (int m = 1; m <= NG; ++m) wall(wv[m - 1], pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk));
+  ghost_fill_point(q, met, blocks, patches[blockIdx.y], blockIdx.x * blockDim.x + threadIdx.x, SP, delta);
 }
 
 // Viscous face metrics of one block: for every cell position (i, j, k) in

@@ -59,7 +59,8 @@ __global__ void __launch_bounds__(256) k_stage_simple(StageArgs A, const BlockDe
 // dt_c = CFL V / (sum_d L_d + 4 sum_d Lv_d) with S_d averaged over the cell's
 // two d-faces; per-workgroup partials: minimum dt (slot 12), sum V Q
 // (slots 5-9) and the count of non-finite Q values (slot 11); local steps
-// stored.
+// stored.  Without TOTALS the minimum alone (a step without a history).
+template <bool TOTALS>
 __global__ void __launch_bounds__(256) k_dt(const double* __restrict__ q, const double* __restrict__ met,
                                             double* __restrict__ dtcell, double* __restrict__ partials,
                                             const BlockDesc* __restrict__ blocks, int nblk, int64_t nchunks,
@@ -83,13 +84,25 @@ __global__ void __launch_bounds__(256) k_dt(const double* __restrict__ q, const 
     const double dtc = cell_dt(qc, mb, c, B.sv, B.sj, B.sk, P);
     if (P.local_dt) dtcell[B.soff + c] = dtc;
     acc[12] = fmin(acc[12], dtc);
+    if (TOTALS) {
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      acc[5 + v] += vol * qc[v];
-      if (!finite(qc[v])) acc[11] += 1.0;
+      for (int v = 0; v < 5; ++v) {
+        acc[5 + v] += vol * qc[v];
+        if (!finite(qc[v])) acc[11] += 1.0;
+      }
     }
   }
-  wg_reduce_partials(acc, partials + (int64_t)blockIdx.x * NPART);
+  if (TOTALS) {
+    wg_reduce_partials(acc, partials + (int64_t)blockIdx.x * NPART);
+  } else {
+    __shared__ double red[4];
+    double m = acc[12];
+    for (int off = 32; off > 0; off >>= 1) m = fmin(m, __shfl_xor(m, off, 64));
+    if (lane == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      partials[(int64_t)blockIdx.x * NPART + 12] = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
+  }
 }
 
 // ------------------------------------------------------------- norms
@@ -143,8 +156,10 @@ __global__ void __launch_bounds__(256) k_norms(const double* __restrict__ q, con
 // L2 x5, sum VQ x5, max|R_rho|] and nonfinite count): 64 threads a slot read
 // the rows as one array (thread t holds slot t % 13 of rows t / 13 + 64 m:
 // coalesced), then a fixed tree over the 64.  A row's place in the order does
-// not depend on the number of rows.  mode 0: the minimum of slot 12 -> dt.
-// 2304 rows: 4.2 us; 7.9 us with a thread per row and 13 trees of 256.
+// not depend on the number of rows.  mode 2: the same with the minimum of slot
+// 12 for dt.  mode 0: the minimum of slot 12 -> dt.
+// Twelve loads of a thread are in flight (2304 rows: 9 to 12 us; 20 with them
+// one after the other).
 constexpr int FIN_T = 64 * NPART;
 
 __device__ __forceinline__ double fin_op(int q, double a, double b) {
@@ -172,15 +187,25 @@ __global__ void __launch_bounds__(FIN_T) k_finalize(const double* __restrict__ p
   const int q = t % NPART;
   double acc = q == 12 ? __builtin_inf() : 0.0;
   const int total = nrows * NPART;
-#pragma unroll 4
-  for (int e = t; e < total; e += FIN_T) acc = fin_op(q, acc, partials[e]);
+  const double none = acc;
+  for (int e0 = t; e0 < total; e0 += 12 * FIN_T) {      // twelve loads in flight
+    double v[12];
+#pragma unroll
+    for (int u = 0; u < 12; ++u) {
+      const int e = e0 + u * FIN_T;
+      v[u] = partials[e < total ? e : t];
+      if (e >= total) v[u] = none;
+    }
+#pragma unroll
+    for (int u = 0; u < 12; ++u) acc = fin_op(q, acc, v[u]);
+  }
   sh[t] = acc;
   __syncthreads();
   for (int s = 32; s > 0; s >>= 1) {
     if (t < s * NPART) sh[t] = fin_op(q, sh[t], sh[t + s * NPART]);
     __syncthreads();
   }
-  if (t == 0) hist[0] = dt ? dt[0] : 0.0;
+  if (t == 0) hist[0] = mode == 2 ? sh[12] : dt ? dt[0] : 0.0;
   if (t < 5) hist[1 + t] = sqrt(sh[t] * inv_ncells);
   else if (t < 10) hist[1 + t] = sh[t];
   else if (t == 10) hist[11] = sh[10];
@@ -212,8 +237,11 @@ void launch_stage_simple(const StageArgs& A, int mode, bool visc, bool fp32, con
 }
 
 void launch_dt(const double* q, const double* met, double* dtcell, double* partials, const BlockDesc* blocks,
-               int nblk, int64_t nchunks, const StepParams& P, int nwg, hipStream_t s) {
-  hipLaunchKernelGGL(k_dt, dim3(nwg), dim3(256), 0, s, q, met, dtcell, partials, blocks, nblk, nchunks, P);
+               int nblk, int64_t nchunks, const StepParams& P, int nwg, bool totals, hipStream_t s) {
+  if (totals)
+    hipLaunchKernelGGL(k_dt<true>, dim3(nwg), dim3(256), 0, s, q, met, dtcell, partials, blocks, nblk, nchunks, P);
+  else
+    hipLaunchKernelGGL(k_dt<false>, dim3(nwg), dim3(256), 0, s, q, met, dtcell, partials, blocks, nblk, nchunks, P);
 }
 
 void launch_norms(const double* q, const double* r, const double* met, double* partials, const BlockDesc* blocks,

@@ -38,11 +38,13 @@ bool stage_ring(const StageArgs& A, int mode, bool visc, bool fp32, const BlockD
 bool stage_tiled(const StageArgs& A, int mode, bool visc, bool fp32, const BlockDesc* blocks,
                  const TileDesc* tiles, const Gas<double>& g64, const Gas<float>& g32, int nwg,
                  hipStream_t s, int* occ);
+void stage_brick(const StageArgs& A, int mode, bool visc, bool fp32, const BlockDesc* blocks, const TileDesc* tiles,
+                 const Gas<double>& g64, const Gas<float>& g32, int nwg, hipStream_t s, int* occ);
 void launch_stage_simple(const StageArgs& A, int mode, bool visc, bool fp32, const BlockDesc* blocks,
                          const TileDesc* tiles, const Gas<double>& g64, const Gas<float>& g32, int nwg,
                          hipStream_t s);
 void launch_dt(const double* q, const double* met, double* dtcell, double* partials, const BlockDesc* blocks,
-               int nblk, int64_t nchunks, const StepParams& P, int nwg, hipStream_t s);
+               int nblk, int64_t nchunks, const StepParams& P, int nwg, bool totals, hipStream_t s);
 void launch_norms(const double* q, const double* r, const double* met, double* partials, const BlockDesc* blocks,
                   int nblk, int64_t nchunks, int nwg, hipStream_t s);
 void mlp_forward(const MlpDims& D, const uint16_t* P, const float* x, const int32_t* idx, int64_t n, float* y,
@@ -70,6 +72,7 @@ using namespace cfd;
 namespace {
 
 constexpr int TILE_I = 64;
+constexpr int PATCHES_PER_BLOCK = 3 * 6 * 64;   // reserved: 64 patches per face on average
 constexpr int NWG_MAX = 4096;   // persistent grid cap (rows of the partials buffers)
 
 thread_local std::string g_last_error;
@@ -339,9 +342,13 @@ struct cfd_ctx {
   // directions in one launch (no stencil of the inviscid stage reads an edge
   // or corner ghost cell, the only cells the sweep order exists for)
   int pm_off = 0, pm_count = 0, pm_threads = 0;
+  // those patches grouped by block and face: ranges [6 nblk + 1] (device), for
+  // the brick kernel (null: viscous flow, or no room in the workspace)
+  const int32_t* dpatch_first = nullptr;
   TileDesc* dtiles = nullptr;
   int ntiles = 0;
   int tile_i = 64;       // width of the stage kernel's tiles
+  bool brick = false;    // the tile list holds bricks (kernels_brick.hip)
   int64_t ncells = 0;
   int64_t nchunks = 0;   // 64-cell row chunks of the grid (time-step and norms kernels)
   cfd_tuning tun{2, 8, 32, 1, 1};   // replaced by default_tuning() when the blocks are created
@@ -534,58 +541,61 @@ int ring_tile_i(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t 
   return take && nn <= max_tiles ? narrow : wide;
 }
 
-// Estimated cost of a plane-ring launch, in plane times of one compute unit's
-// worth of workgroups: rounds of the persistent grid x (planes of a tile + its
-// start, whose three plane fills and gathered k-face take about 1.5 planes),
-// the last round with the deepest tile.
-// per_cu: workgroups resident per compute unit.
-double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t max_tiles, int num_cu, int per_cu) {
-  const int ti = ring_tile_i(dims, t, max_tiles);
+int64_t brick_count(const std::vector<cfd_dims>& dims) {
+  int64_t n = 0;
+  for (const auto& d : dims)
+    n += (int64_t)((d.ni + BRICK_I - 1) / BRICK_I) * ((d.nj + BRICK_J - 1) / BRICK_J) * ((d.nk + BRICK_K - 1) / BRICK_K);
+  return n;
+}
+
+// Estimated cost of a plane-ring launch, in plane times of a compute unit full
+// of workgroups: rounds of the persistent grid x (planes of a tile + its start,
+// whose three plane fills and gathered k-face take about 1.5 planes), the last
+// round with the deepest tile.  A plane of 256-column tiles takes 1.05 with
+// every CU full and 0.75 with one tile a CU (FP64, two waves and one a SIMD:
+// 96 x 48 x 48 Euler 136 us a step with 216 such tiles of 4 planes, 168 with
+// 108 tiles of 512 columns).
+double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t max_tiles, int num_cu, bool fp32,
+                 bool viscous) {
+  const int ti = ring_tile_i(dims, t, max_tiles), tj = 64 * t.tile_j / ti;
   int64_t n = 0, planes = 0;
   int deepest = 0;
   for (const auto& d : dims) {
     int k0, k1;
     tile_run(d.nk, t.tile_k, 0, k0, k1);
     deepest = std::max(deepest, k1);
-    const int64_t cols = (int64_t)((d.ni + ti - 1) / ti) * ((d.nj + 64 * t.tile_j / ti - 1) / (64 * t.tile_j / ti));
+    const int64_t cols = (int64_t)((d.ni + ti - 1) / ti) * ((d.nj + tj - 1) / tj);
     n += cols * tile_runs(d.nk, t.tile_k);
     planes += cols * d.nk;
   }
-  const int64_t resident = (int64_t)num_cu * per_cu;
-  return (double)((n + resident - 1) / resident - 1) * ((double)planes / (double)n + 1.5) + (deepest + 1.5);
+  const int64_t resident = (int64_t)num_cu * (8 / t.tile_j) * (fp32 && !viscous ? 2 : 1);
+  const int64_t full = (n - 1) / resident;
+  const double plane = t.tile_j == 8 ? 1.0 : 1.05;
+  const double last = t.tile_j == 4 && !fp32 && n - full * resident <= num_cu ? 0.75 : plane;
+  return (double)full * ((double)planes / (double)n + 1.5) * plane + (deepest + 1.5) * last;
 }
 
-// Default tuning for the grid: the plane-ring kernel, its tiles' depth (4 to
-// 32 planes) the one of least estimated cost, which weighs each tile's start
-// against the last round of the persistent grid.  FP32-flux kernels take
-// 256-column tiles (tile_j 4): chain of 40 uneven Euler blocks 4.42 ms a step
-// against 4.64 with 512 columns, 2 x 2 blocks of 250 x 203 x 72 NS 5.37
-// against 5.47.  FP64 kernels take 512 columns (256 x 128 x 128 NS 1.774
-// against 1.787 ms) unless 256-column tiles pad the blocks that much less
-// (128 blocks of 48 x 24 x 24, multigrid, 5.87 against 6.60 ms); both keep two
-// waves per SIMD.
-// A grid too small to give every CU a 64 x 8 x 4 tile gets the tiled kernel
-// with 4-row tiles, tile_k halved (down to 1) until there are 4 tiles per CU:
-// on such small grids the launch's latency, not the halo planes each shallow
-// tile reloads, bounds the stage (measured on the 96x48x48 and 48x24x24 levels
-// of a multigrid cycle: 64x4x1 tiles took the cycle from 1.45 to 1.26 ms
-// against 64x4x4 and 64x2x4).
+// Default tuning for the grid: bricks (the tiled kernel's one-plane tiles) up
+// to seven bricks a CU, else the plane-ring kernel, its tiles' depth (4 to 32
+// planes) and, in FP64, size the ones of least estimated cost.
+// Bricks against the best ring or tiled tiles, us a step: Euler 32^3 32 / 73,
+// 64 x 32 x 32 54 / 79, 96 x 48 x 48 (1728 bricks) 129 / 136, 128 x 64 x 64
+// (4096) 332 / 188; 128 blocks of 12 x 8 x 8 (1024) 119 / 143, of 24 x 12 x 12
+// (3456) 271 / 245; NS 64 x 32 x 32 83 / 134, 96 x 48 x 48 173 / 202.
+// FP32-flux kernels take 256-column tiles (tile_j 4): chain of 40 uneven Euler
+// blocks 4.42 ms a step against 4.64 with 512 columns, 2 x 2 blocks of 250 x
+// 203 x 72 NS 5.37 against 5.47.  FP64 kernels take 512 columns on grids that
+// fill the chip (256 x 128 x 128 NS 1.774 against 1.787 ms) unless 256-column
+// tiles pad the blocks that much less (2 x 2 blocks of 130 x 260 x 100 NS 6.46
+// against 7.16 ms); both keep two waves per SIMD.
 cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p, int64_t max_tiles) {
+  if (brick_count(dims) <= 7 * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
   cfd_tuning best{2, 8, 32, 1, 1};
-  int64_t small = 0;
-  padded_cells(dims, TILE_I, 8, 4, &small);
-  if (small < num_cu) {
-    cfd_tuning t{0, 4, 4, 1, 1};
-    int64_t n = 0;
-    while (t.tile_k > 1 && (padded_cells(dims, TILE_I, t.tile_j, t.tile_k, &n), n < 4 * (int64_t)num_cu)) t.tile_k /= 2;
-    return t;
-  }
   double least = 0.0;
   for (int tj = p.flux_fp32 ? 4 : 8; tj >= 4; tj /= 2)
     for (int tk = 32; tk >= 4; --tk) {
       const cfd_tuning t{2, tj, tk, 1, 1};
-      const int per_cu = (8 / tj) * (p.flux_fp32 && !p.viscous ? 2 : 1);
-      const double cost = ring_cost(dims, t, max_tiles, num_cu, per_cu) * (tj == 8 ? 1.0 : 1.05);
+      const double cost = ring_cost(dims, t, max_tiles, num_cu, p.flux_fp32 != 0, p.viscous != 0);
       if (least == 0.0 || cost < least) {
         least = cost;
         best = t;
@@ -594,10 +604,20 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
   return best;
 }
 
+// The tiled kernel's one-plane tiles (tile_k 1) run as bricks: nothing marches
+// there, and a brick's faces run side by side where a one-plane tile computes
+// five or six one after the other.
+bool use_bricks(const cfd_ctx* c) {
+  if (c->tun.kernel != 0 || c->tun.tile_k != 1) return false;
+  if (!c->params.viscous && !c->dpatch_first) return false;
+  return brick_count(c->dims) <= c->W.max_tiles;
+}
+
 void build_tiles(cfd_ctx* c, hipStream_t s) {
   const int tk = c->tun.tile_k;
   c->tile_i = c->tun.kernel == 2 ? ring_tile_i(c->dims, c->tun, c->W.max_tiles) : TILE_I;
-  const int ti = c->tile_i, tj = c->tun.tile_j * TILE_I / ti;
+  c->brick = use_bricks(c);
+  const int ti = c->brick ? BRICK_I : c->tile_i, tj = c->brick ? BRICK_J : c->tun.tile_j * TILE_I / ti;
   struct T2 {
     TileDesc t;
     int64_t work;
@@ -605,9 +625,9 @@ void build_tiles(cfd_ctx* c, hipStream_t s) {
   std::vector<T2> v;
   for (int b = 0; b < c->nblk; ++b) {
     const cfd_dims& d = c->dims[b];
-    for (int kp = 0; kp < tile_runs(d.nk, tk); ++kp) {
-      int k0, k1;
-      tile_run(d.nk, tk, kp, k0, k1);
+    for (int kp = 0; kp < tile_runs(d.nk, c->brick ? BRICK_K : tk); ++kp) {
+      int k0 = kp * BRICK_K, k1 = std::min(k0 + BRICK_K, d.nk);
+      if (!c->brick) tile_run(d.nk, tk, kp, k0, k1);
       for (int j0 = 0; j0 < d.nj; j0 += tj)
         for (int i0 = 0; i0 < d.ni; i0 += ti) {
           const int64_t w = (int64_t)std::min(ti, d.ni - i0) * std::min(tj, d.nj - j0) * (k1 - k0);
@@ -698,12 +718,26 @@ StageArgs stage_args(cfd_ctx* c) {
   return A;
 }
 
+// Whether the stage kernel forms its ghost states itself (bricks, inviscid
+// flow): the steps then fill no ghost cells.
+bool own_ghosts(const cfd_ctx* c) { return c->brick && !c->params.viscous; }
+
+// Ghost cells of q before a stage of a step or a cycle: filled, or left to the stage.
+void stage_ghosts(cfd_ctx* c, double* q, StageArgs& A, hipStream_t s) {
+  if (own_ghosts(c)) {
+    A.patches = c->dpatches + c->pm_off;
+    A.patch_first = c->dpatch_first;
+  } else {
+    ghost_fill(c, q, s);
+  }
+}
+
 // Persistent grid of the stage kernel: resident workgroups per CU (occupancy
 // query, cached per variant) times the CU count, capped by the tile count.
 int stage_nwg(cfd_ctx* c, int mode) {
   if (c->tun.kernel == 1) return nwg_for(c, 8);
   const int key = (c->params.viscous ? 1 : 0) | (c->params.flux_fp32 ? 2 : 0) | (mode << 2) |
-                  ((c->tun.tile_j == 2 ? 0 : c->tun.tile_j == 4 ? 1 : 2) << 4) | (c->tun.kernel << 6) | (c->tile_i << 8);
+                  ((c->tun.tile_j == 2 ? 0 : c->tun.tile_j == 4 ? 1 : 2) << 4) | (c->tun.kernel << 6) | (c->tile_i << 8) | ((c->brick ? 1 : 0) << 16);
   auto it = c->occ_cache.find(key);
   int occ;
   if (it != c->occ_cache.end()) {
@@ -712,7 +746,10 @@ int stage_nwg(cfd_ctx* c, int mode) {
     StageArgs A{};
     A.tile_i = c->tile_i;
     A.tile_j = c->tun.tile_j;
-    const bool ok = c->tun.kernel == 2
+    bool ok = true;
+    if (c->brick) stage_brick(A, mode, c->params.viscous != 0, c->params.flux_fp32 != 0, nullptr, nullptr, c->g64,
+                              c->g32, 0, nullptr, &occ);
+    else ok = c->tun.kernel == 2
                         ? stage_ring(A, mode, c->params.viscous != 0, c->params.flux_fp32 != 0, nullptr, nullptr,
                                      c->g64, c->g32, 0, nullptr, &occ)
                         : stage_tiled(A, mode, c->params.viscous != 0, c->params.flux_fp32 != 0, nullptr, nullptr,
@@ -726,7 +763,9 @@ int stage_nwg(cfd_ctx* c, int mode) {
 void launch_stage(cfd_ctx* c, const StageArgs& A, int mode, hipStream_t s) {
   const bool visc = c->params.viscous != 0, fp32 = c->params.flux_fp32 != 0;
   const int nwg = stage_nwg(c, mode);
-  if (c->tun.kernel == 0) {
+  if (c->brick) {
+    timed(c, 0, s, [&] { stage_brick(A, mode, visc, fp32, c->dblocks, c->dtiles, c->g64, c->g32, nwg, s, nullptr); });
+  } else if (c->tun.kernel == 0) {
     timed(c, 0, s, [&] {
       if (!stage_tiled(A, mode, visc, fp32, c->dblocks, c->dtiles, c->g64, c->g32, nwg, s, nullptr))
         fail(CFD_EINVAL, "tiled kernel has no variant for tile_j = %d", c->tun.tile_j);
@@ -742,12 +781,11 @@ void launch_stage(cfd_ctx* c, const StageArgs& A, int mode, hipStream_t s) {
 }
 
 // CFL time step of q: per-cell steps (local stepping) and, with min_dt, the
-// minimum into d_dt (read by global-step stages and forcing, and by the
-// history row).
-void time_step_pass(cfd_ctx* c, const double* q, hipStream_t s, bool min_dt = true) {
+// minimum into d_dt (read by global-step stages and forcing).
+void time_step_pass(cfd_ctx* c, const double* q, hipStream_t s, bool min_dt, bool totals) {
   const int nwg = dt_nwg(c);
   timed(c, 2, s, [&] {
-    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, c->SP, nwg, s);
+    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, c->SP, nwg, totals, s);
   });
   if (min_dt) launch_finalize(c->part_dt(), nwg, 0, 0.0, c->d_dt(), nullptr, nullptr, s);
 }
@@ -785,8 +823,9 @@ struct StepKind {
 // save 42 us of k_norms, the time step not evaluated in the last stage 64 us.
 // (Taking dt of the new state inside the tiled kernel's third stage was
 // measured slower: its extra metric loads cost more than the separate pass.)
-void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, const double* force = nullptr,
-                  bool no_fuse = false) {
+// row: where the history row goes.
+void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, double* row,
+                  const double* force = nullptr, bool no_fuse = false) {
   const bool history = kind.history;
   const bool ring = c->tun.kernel == 2;
   const bool fuse = fused_dt(c) && !no_fuse && !force;
@@ -802,43 +841,46 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, co
   };
   const double inv_n = 1.0 / (double)c->ncells;
   const int nwg_dt = dt_nwg(c);
-  ghost_fill(c, q, s);
-  // Local steps without a history row read no minimum step: every stage and
-  // the forcing take the per-cell steps.
-  const bool pass = !fuse || kind.first;
-  if (pass) time_step_pass(c, q, s, history || !c->params.local_dt);
   StageArgs A = stage_args(c);
+  stage_ghosts(c, q, A, s);
+  // Nobody reads the minimum of local steps but the history row, whose
+  // finalize takes it from the rows; stage 1 of the brick kernel takes it from
+  // the rows itself.
+  const bool pass = !fuse || kind.first, global = !c->params.local_dt;
+  if (pass) time_step_pass(c, q, s, global && !c->brick, history);
   A.qs = q;
   A.qn = q;
   A.out = c->qa();
   A.force = force_in_stage;
   A.fb = 1.0;
-  if (ring) {
-    double* rows = pass ? c->part_dt() : c->part_nrm();
-    const int ntot = history ? nwg_dt : 0;
-    if (history && !pass)
-      timed(c, 3, s, [&] {
-        launch_norms(q, nullptr, c->met(), rows, c->dblocks, c->nblk, c->nchunks, nwg_dt, s);
-      });
-    A.partials = rows + (int64_t)ntot * NPART;
-    launch_stage(c, A, 1, s);
-    if (history)
-      launch_finalize(rows, ntot + stage_nwg(c, 1), 1, inv_n, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
-  } else if (history) {
-    A.rout = c->qb();
-    launch_stage(c, A, 1, s);
-    timed(c, 3, s, [&] {
-      launch_norms(nullptr, c->qb(), nullptr, c->part_dt() + (int64_t)nwg_dt * NPART, c->dblocks, c->nblk,
-                   c->nchunks, nwg_dt, s);
-    });
-    launch_finalize(c->part_dt(), 2 * nwg_dt, 1, inv_n, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
-  } else {
-    launch_stage(c, A, 1, s);
+  if (pass && global && c->brick) {
+    A.rows = c->part_dt();
+    A.nrows = nwg_dt;
+    A.dt_min = c->d_dt();
   }
+  // rows of the history: the time-step (or totals) kernel's, then the norms'
+  double* rows = pass ? c->part_dt() : c->part_nrm();
+  double* nrm = rows + (history ? (int64_t)nwg_dt * NPART : 0);
+  const bool in_stage = ring || c->brick;      // stage 1 reduces the norms
+  if (history && !pass)
+    timed(c, 3, s, [&] {
+      launch_norms(q, nullptr, c->met(), rows, c->dblocks, c->nblk, c->nchunks, nwg_dt, s);
+    });
+  if (ring || (c->brick && history)) A.partials = nrm;
+  if (history && !in_stage) A.rout = c->qb();
+  launch_stage(c, A, 1, s);
+  if (history && !in_stage)
+    timed(c, 3, s, [&] {
+      launch_norms(nullptr, c->qb(), nullptr, nrm, c->dblocks, c->nblk, c->nchunks, nwg_dt, s);
+    });
+  if (history)
+    launch_finalize(rows, nwg_dt + (in_stage ? stage_nwg(c, 1) : nwg_dt), pass ? 2 : 1, inv_n, c->d_dt(), row,
+                    c->d_nonfinite(), s);
   forced(c->qa(), 1.0);
   A.rout = nullptr;
   A.partials = nullptr;
-  ghost_fill(c, c->qa(), s);
+  A.rows = nullptr;
+  stage_ghosts(c, c->qa(), A, s);
   A.qs = c->qa();
   A.out = c->qb();
   A.a = 0.75;
@@ -846,7 +888,7 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, co
   A.fb = 0.25;
   launch_stage(c, A, 2, s);
   forced(c->qb(), 0.25);
-  ghost_fill(c, c->qb(), s);
+  stage_ghosts(c, c->qb(), A, s);
   A.qs = c->qb();
   A.out = q;
   A.a = 1.0 / 3.0;
@@ -905,7 +947,7 @@ void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* 
   const int nwg = dt_nwg(c);
   ghost_fill(c, q, s);
   timed(c, 2, s, [&] {
-    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, P, nwg, s);
+    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, P, nwg, false, s);
   });
   launch_finalize(c->part_dt(), nwg, 0, 0.0, c->d_dt(), nullptr, nullptr, s);
   StageArgs A = stage_args(c);
@@ -991,7 +1033,6 @@ cfd_status cfd_layout(int32_t nblk, const cfd_dims* dims, int32_t ghost_layers, 
 
 // node sweeps, cell sweeps and the one-launch face set
 static int count_patches(int nconn, int nbc) { return 3 * (nconn + nbc); }
-constexpr int PATCHES_PER_BLOCK = 3 * 6 * 64;   // reserved: 64 patches per face on average
 
 cfd_status cfd_workspace_size(const cfd_params* params, int32_t nblk, const cfd_dims* dims,
                               size_t* workspace_bytes) {
@@ -1087,6 +1128,18 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
           c->pm_threads = std::max(c->pm_threads, all[p].count * ghost_threads_per_point(all[p].kind, d));
       }
       c->pm_count = (int)all.size() - c->pm_off;
+      std::stable_sort(all.begin() + c->pm_off, all.end(), [](const PatchDesc& a, const PatchDesc& b) {
+        return a.blk != b.blk ? a.blk < b.blk : a.face < b.face;
+      });
+      std::vector<int32_t> first(6 * nblk + 1, 0);
+      for (int p = c->pm_off; p < (int)all.size(); ++p) ++first[6 * all[p].blk + all[p].face + 1];
+      for (int f = 0; f < 6 * nblk; ++f) first[f + 1] += first[f];
+      const size_t slots = (first.size() * sizeof(int32_t) + sizeof(PatchDesc) - 1) / sizeof(PatchDesc);
+      if (all.size() + slots <= (size_t)PATCHES_PER_BLOCK * nblk) {
+        c->dpatch_first = reinterpret_cast<const int32_t*>(c->dpatches + all.size());
+        all.resize(all.size() + slots);
+        std::memcpy(all.data() + (all.size() - slots), first.data(), first.size() * sizeof(int32_t));
+      }
     }
     HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     {
@@ -1229,7 +1282,7 @@ cfd_status cfd_time_step(cfd_ctx* c, const double* q, double* dt_dev, hipStream_
   return guard(c, [&] {
     if (!c || !q || !dt_dev) fail(CFD_EINVAL, "NULL argument");
     const int nwg = dt_nwg(c);
-    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, c->SP, nwg, s);
+    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, c->SP, nwg, false, s);
     launch_finalize(c->part_dt(), nwg, 0, 0.0, dt_dev, nullptr, nullptr, s);
     check_launch();
   });
@@ -1251,20 +1304,22 @@ cfd_status cfd_step(cfd_ctx* c, double* q, int32_t nsteps, double* hist, hipStre
       kind.history = hist != nullptr;
       kind.first = !fused || n == 0;
       kind.last = !fused || n + run == nsteps;
-      auto enqueue = [&](hipStream_t st) {
+      auto enqueue = [&](hipStream_t st, double* row) {
         for (int m = 0; m < run; ++m) {
           StepKind k = kind;
           k.first = !fused || (kind.first && m == 0);
           k.last = !fused || (kind.last && m == run - 1);
-          enqueue_step(c, q, st, k);
+          enqueue_step(c, q, st, k, row);
         }
       };
-      if (graph) {
+      // a step of bricks is five short launches (four without a history): as a
+      // graph of its own it takes 54 us on 32^3 cells, launched one by one 43
+      if (graph && (run > 1 || !own_ghosts(c))) {
         cfd_ctx::StepGraph& g = c->step_graphs[run * 8 + kind.key()];
         if (!g.exec) {
           HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
           try {
-            enqueue(c->cap_stream);
+            enqueue(c->cap_stream, c->d_hist());
           } catch (...) {
             hipGraph_t gg = nullptr;
             hipStreamEndCapture(c->cap_stream, &gg);
@@ -1275,13 +1330,13 @@ cfd_status cfd_step(cfd_ctx* c, double* q, int32_t nsteps, double* hist, hipStre
           HIPCHK(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
         }
         HIPCHK(hipGraphLaunch(g.exec, s));
+        if (hist)
+          HIPCHK(hipMemcpyAsync(hist + (int64_t)n * NHIST, c->d_hist(), sizeof(double) * NHIST,
+                                hipMemcpyDeviceToDevice, s));
       } else {
-        enqueue(s);
+        enqueue(s, hist ? hist + (int64_t)n * NHIST : nullptr);
         check_launch();
       }
-      if (hist)
-        HIPCHK(hipMemcpyAsync(hist + (int64_t)n * NHIST, c->d_hist(), sizeof(double) * NHIST,
-                              hipMemcpyDeviceToDevice, s));
       n += run;
     }
   });
@@ -1370,22 +1425,22 @@ void enqueue_mg_cycle(cfd_ctx* const* lv, double* const* q, int L, int pre, int 
       const bool rec = record && l == 0 && n == 0;
       StepKind kind;
       kind.history = rec;
-      enqueue_step(c, q[l], s, kind, l ? F[l] : nullptr, true);
+      enqueue_step(c, q[l], s, kind, c->d_hist(), l ? F[l] : nullptr, true);
       if (rec && hist)
         HIPCHK(hipMemcpyAsync(hist, c->d_hist(), sizeof(double) * NHIST, hipMemcpyDeviceToDevice, s));
     }
     if (l == L - 1) break;
     cfd_ctx* cn = lv[l + 1];
-    ghost_fill(c, q[l], s);
     StageArgs A = stage_args(c);
+    stage_ghosts(c, q[l], A, s);
     A.qs = q[l];
     A.qn = q[l];
     A.out = R[l];
     launch_stage(c, A, 0, s);
     launch_mg_restrict(q[l], c->met(), R[l], l ? F[l] : nullptr, c->dblocks, q[l + 1], Q0[l + 1], F[l + 1],
                        cn->met(), cn->dblocks, nblk, cn->nchunks, dt_nwg(cn), s);
-    ghost_fill(cn, q[l + 1], s);
     StageArgs B = stage_args(cn);
+    stage_ghosts(cn, q[l + 1], B, s);
     B.qs = q[l + 1];
     B.qn = q[l + 1];
     B.out = R[l + 1];

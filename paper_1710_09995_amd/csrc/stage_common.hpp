@@ -315,7 +315,7 @@ __device__ __forceinline__ void finish_cell(const StageArgs& A, const BlockDesc&
   update_cell<MODE>(A, B, c, Di, Dj, Dk, in, nullptr, nullptr, A.force);
 }
 
-// Fixed-order workgroup reduction of NPART partials; thread 0 writes the row.
+// Fixed-order workgroup reduction of NPART partials; one thread a slot writes the row.
 // Slots: sums for [0,10) and 11, max for 10, min for 12.  red: LDS scratch of
 // NPART x 16 doubles that no thread uses any more (the first barrier below
 // orders the caller's last uses before it).
@@ -337,16 +337,15 @@ __device__ __forceinline__ void wg_reduce_partials(double acc[NPART], double* __
     if (lane == 0) red[q][wave] = v;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 0; q < NPART; ++q) {
-      double v = red[q][0];
-      for (int w = 1; w < nwave; ++w) {
-        if (q == 10) v = fmax(v, red[q][w]);
-        else if (q == 12) v = fmin(v, red[q][w]);
-        else v = v + red[q][w];
-      }
-      out_row[q] = v;
+  if (threadIdx.x < NPART) {
+    const int q = threadIdx.x;
+    double v = red[q][0];
+    for (int w = 1; w < nwave; ++w) {
+      if (q == 10) v = fmax(v, red[q][w]);
+      else if (q == 12) v = fmin(v, red[q][w]);
+      else v = v + red[q][w];
     }
+    out_row[q] = v;
   }
   __syncthreads();
 }
