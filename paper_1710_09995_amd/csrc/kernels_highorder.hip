@@ -53,20 +53,34 @@ struct Eq2OpT {
   }
 };
 
-// WCNS-E-5 left state at the face between u0 and up1: three 3-cell Taylor
-// candidates u0 + (h/2) g + (h^2/8) s, smoothness (h g)^2 + (h^2 s)^2, linear
-// weights 1/16, 10/16, 5/16 made nonlinear by d_k / (eps + beta_k)^2.  Four
-// refined hardware reciprocals (frcp, within 1 ulp) instead of six divisions.
+// WCNS-E-5 states at both faces of the cell u0 of five: l at the face toward
+// up1 (its left state), r at the face toward um1 (its right state).  Three
+// 3-cell Taylor candidates u0 +- (h/2) g + (h^2/8) s, smoothness
+// (h g)^2 + (h^2 s)^2, linear weights 1/16, 10/16, 5/16 (from the far side of
+// each face) made nonlinear by d_k / (eps + beta_k)^2.  Both faces share the
+// smoothness, its three refined hardware reciprocals (frcp, within 1 ulp) and
+// most of the candidates: 86 operations where two one-sided states take 144.
+// Every step is an explicit operation whose mirror image rounds alike, so
+// wcns5_left of the mirrored cells is r to the bit.
+__device__ __forceinline__ void wcns5_pair(double um2, double um1, double u0, double up1, double up2, double eps,
+                                           double& l, double& r) {
+  auto fma = [](double a, double b, double c) { return __builtin_fma(a, b, c); };
+  const double g0 = 0.5 * fma(3.0, u0, fma(-4.0, um1, um2)), g1 = 0.5 * (up1 - um1),
+               g2 = 0.5 * fma(3.0, u0, fma(-4.0, up1, up2));   // g2: toward um1, as g0 toward up1
+  const double s0 = fma(-2.0, um1, um2 + u0), s1 = fma(-2.0, u0, um1 + up1), s2 = fma(-2.0, up1, up2 + u0);
+  const double t0 = fma(0.125, s0, u0), t1 = fma(0.125, s1, u0), t2 = fma(0.125, s2, u0);
+  const double b0 = fma(s0, s0, fma(g0, g0, eps)), b1 = fma(s1, s1, fma(g1, g1, eps)),
+               b2 = fma(s2, s2, fma(g2, g2, eps));
+  const double r0 = frcp(b0 * b0), r1 = 10.0 * frcp(b1 * b1), r2 = frcp(b2 * b2);
+  const double f0 = 5.0 * r0, f2 = 5.0 * r2;
+  const double il = frcp((r0 + r1) + f2), ir = frcp((r2 + r1) + f0);
+  l = fma(fma(-0.5, g2, t2), f2 * il, fma(fma(0.5, g1, t1), r1 * il, fma(0.5, g0, t0) * (r0 * il)));
+  r = fma(fma(-0.5, g0, t0), f0 * ir, fma(fma(-0.5, g1, t1), r1 * ir, fma(0.5, g2, t2) * (r2 * ir)));
+}
 __device__ __forceinline__ double wcns5_left(double um2, double um1, double u0, double up1, double up2, double eps) {
-  const double g0 = (um2 - 4.0 * um1 + 3.0 * u0) / 2.0, g1 = (up1 - um1) / 2.0,
-               g2 = (-3.0 * u0 + 4.0 * up1 - up2) / 2.0;
-  const double s0 = um2 - 2.0 * um1 + u0, s1 = um1 - 2.0 * u0 + up1, s2 = u0 - 2.0 * up1 + up2;
-  const double c0 = u0 + 0.5 * g0 + 0.125 * s0, c1 = u0 + 0.5 * g1 + 0.125 * s1, c2 = u0 + 0.5 * g2 + 0.125 * s2;
-  const double b0 = eps + g0 * g0 + s0 * s0, b1 = eps + g1 * g1 + s1 * s1, b2 = eps + g2 * g2 + s2 * s2;
-  const double a0 = (1.0 / 16.0) * frcp(b0 * b0), a1 = (10.0 / 16.0) * frcp(b1 * b1),
-               a2 = (5.0 / 16.0) * frcp(b2 * b2);
-  const double it = frcp(a0 + a1 + a2);
-  return (a0 * it) * c0 + (a1 * it) * c1 + (a2 * it) * c2;
+  double l, r;
+  wcns5_pair(um2, um1, u0, up1, up2, eps, l, r);
+  return l;
 }
 
 // The window of face p spans cells p .. p + 5; the face lies between the
@@ -721,38 +735,146 @@ __device__ __forceinline__ LineRef wrap_ref(const Line& L, const int c0[3], int 
   return r;
 }
 
+// Blocks run in batches of up to WCNS_BATCH, one launch a pass with grid.y the
+// block: a block of 128 x 64 x 64 alone leaves the last waves of every launch
+// half empty (2 RK3 Navier-Stokes steps on 8 of them: 16.5 ms with a launch a
+// block and pass, three passes a direction; 12.2 ms in batches with the j and k
+// marches; 9.5 ms with the row runs and loads a face ahead as well).
+constexpr int WCNS_BATCH = 8;
+template <class Blk>
+struct Batch {
+  Blk b[WCNS_BATCH];
+};
+// launch(batch, blocks in it, largest work item count) for every batch of v
+template <class Blk, class Items, class Launch>
+void for_batches(const std::vector<Blk>& v, Items items, Launch launch) {
+  for (size_t g = 0; g < v.size(); g += WCNS_BATCH) {
+    Batch<Blk> B{};
+    const int count = (int)std::min<size_t>(WCNS_BATCH, v.size() - g);
+    int64_t most = 0;
+    for (int k = 0; k < count; ++k) {
+      B.b[k] = v[g + k];
+      most = std::max<int64_t>(most, items(v[g + k]));
+    }
+    launch(B, count, most);
+  }
+}
+
+// A block's inviscid pass along d: the state arrays (5 fields) and the face
+// metrics along d (own == NULL: per unit area through e_d), its residual and
+// J^{-1}.
+struct EulerBlk {
+  Line Q, S;
+  double* r;
+  const double* jinv;
+  int n[3];
+};
+
+// A march along D = 1 or 2: workgroups of 256 lines along D (lanes along i, then
+// along the third direction O), each over a chunk of the direction.  The place
+// along D is one value for the workgroup, so that seams are resolved and bases
+// advanced in scalar registers.
+template <int D>
+struct MarchAt {
+  static constexpr int O = D == 1 ? 2 : 1;
+  int i, x0, x1;     // the line's i, the chunk
+  int64_t row;       // o * n0
+  bool in;
+  __device__ __forceinline__ MarchAt(int64_t item, int chunk, const int n[3]) {
+    const int64_t lines = (int64_t)n[0] * n[O], tiles = (lines + 255) / 256;
+    const int64_t l = item % tiles * 256 + threadIdx.x;
+    in = l < lines;
+    const int64_t o = l / n[0];
+    i = (int)(l - o * n[0]);
+    row = o * n[0];
+    x0 = (int)(item / tiles) * chunk;
+    x1 = min(x0 + chunk, n[D]);
+  }
+  static __host__ __device__ int64_t items(const int n[3], int chunk) {
+    return ((int64_t)n[0] * n[O] + 255) / 256 * ((n[D] + chunk - 1) / chunk);
+  }
+  // the block's cell x of the line
+  __device__ __forceinline__ int64_t cell(int x, const int n[3]) const {
+    return D == 1 ? row * n[1] + i + (int64_t)x * n[0] : row + i + (int64_t)x * n[0] * n[1];
+  }
+  // wrap_ref for cell x of the line
+  __device__ __forceinline__ LineRef at(const Line& L, int x, const int n[3]) const {
+    LineRef r{L.own, L.cown, 0};
+    int nd = n[D];
+    if (x < 0) {
+      r.base = L.lo;
+      r.cells = L.clo;
+      nd = L.nlo;
+      x += nd;
+      if (x < 0) x = (x % nd + nd) % nd;
+    } else if (x >= nd) {
+      r.base = L.hi;
+      r.cells = L.chi;
+      x -= nd;
+      nd = L.nhi;
+      if (x >= nd) x %= nd;
+    }
+    r.base += D == 1 ? (int64_t)x * n[0] : (int64_t)x * n[0] * n[1];
+    r.idx = (D == 1 ? row * nd : row) + i;
+    return r;
+  }
+};
+
+// Lines of chunks that a march along d gives the blocks, in threads.
+template <class Blk>
+int64_t march_threads(const std::vector<Blk>& v, int d, int chunk) {
+  int64_t t = 0;
+  for (const Blk& b : v) t += (int64_t)b.n[0] * b.n[d == 1 ? 2 : 1] * ((b.n[d] + chunk - 1) / chunk);
+  return t;
+}
+
+// Orders a wave's LDS accesses before and after: its lanes run in step, so no
+// barrier is needed.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The inviscid residual along d = 1 or 2 in one pass (Eq. 2 of the WCNS-E-5
 // face fluxes): each thread marches a line of cells along d (lanes along i,
 // coalesced rows) over a chunk of cells, converting each cell's state to
-// primitives once, keeping the six cells around the current face and the last
-// six face fluxes in registers, so neither the padded primitives nor the face
-// fluxes go through memory.  Face v (between cells v and v + 1) takes its left
-// state from cells v - 2 .. v + 2 and its right state from v + 3 .. v - 1
-// (k_wcns5_roe_faces' arithmetic); cell x takes Eq. 2 of faces x - 3 .. x + 2.
-// Q: the state arrays (5 fields) along d; S: the face metrics along d (own ==
-// NULL: per unit area through e_d).  MODE 1: r += Eq. 2; MODE 2: r = (r +
-// Eq. 2) / J^{-1} (the last direction of a curvilinear residual).
+// primitives once and keeping the cells around the current face in registers
+// and the last five face fluxes in LDS, so neither the padded primitives nor
+// the face fluxes go through memory.  Face v (between cells v and v + 1) takes
+// its left state from cells v - 2 .. v + 2 and its right state from v + 3 ..
+// v - 1 (k_wcns5_roe_faces' arithmetic); a cell's two states are formed
+// together (wcns5_pair), its left state kept for the next face; cell x takes
+// Eq. 2 of faces x - 3 .. x + 2.  MODE 1: r += Eq. 2; MODE 2: r = (r + Eq. 2) /
+// J^{-1} (the last direction of a curvilinear residual).
+// At two waves a SIMD the loads bound it: the next cell and face metrics are
+// loaded a face ahead, the finished cell's residual before the flux that
+// finishes it (256 x 128 x 128, j / k: 248 / 259 us; states in pairs 209 / 225;
+// with the residual loaded early 163 / 173).  The fluxes are in LDS and
+// the left states pinned where they are formed because the registers would
+// otherwise spill; at 168 registers, three waves, they spill and take 287 us.
 template <int D, int MODE>
-__global__ void __launch_bounds__(256) k_wcns5_euler_march(Line Q, Line S, double* __restrict__ r,
-                                                           const double* __restrict__ jinv, Dims3 Dm, int chunk,
-                                                           double eps, double c1, double c2, double c3,
-                                                           Gas<double> gas) {
-  constexpr int O = D == 1 ? 2 : 1;
-  const int* n = Dm.n;
-  const int nD = n[D], nO = n[O], n0 = n[0];
-  const int nch = (nD + chunk - 1) / chunk;
-  const int64_t cells = (int64_t)n0 * n[1] * n[2];
-  const int64_t total = (int64_t)n0 * nO * nch;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    int c0[3];
-    c0[0] = (int)(t % n0);
-    const int64_t rest = t / n0;
-    c0[O] = (int)(rest % nO);
-    c0[D] = 0;
-    const int x0 = (int)(rest / nO) * chunk, x1 = min(x0 + chunk, nD);
-    double W[6][5], F[6][5];
-    auto load = [&](int x, double* w) {
-      const LineRef q = wrap_ref(Q, c0, x, D, n);
+__global__ void __launch_bounds__(256, 2) k_wcns5_euler_march(Batch<EulerBlk> Bt, int chunk, double eps, double c1,
+                                                              double c2, double c3, Gas<double> gas) {
+  __shared__ double F[5][5][256];   // the last five faces' fluxes, face v in slot (v - x0 + 3) % 5
+  const EulerBlk& Bk = Bt.b[blockIdx.y];
+  const Line Q = Bk.Q, S = Bk.S;
+  double* __restrict__ const r = Bk.r;
+  const double* __restrict__ const jinv = Bk.jinv;
+  const int tid = threadIdx.x;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
+  const int64_t cells = (int64_t)n[0] * n[1] * n[2];
+  const int64_t items = MarchAt<D>::items(n, chunk);
+  for (int64_t t = blockIdx.x; t < items; t += gridDim.x) {
+    const MarchAt<D> M(t, chunk, n);
+    if (!M.in) continue;
+    const int x0 = M.x0, x1 = M.x1;
+    double W[4][5], L[5];
+    auto load = [&](int x, double* q) {
+      const LineRef at = M.at(Q, x, n);
+#pragma unroll
+      for (int k = 0; k < 5; ++k) q[k] = at[k];
+    };
+    auto prim = [&](const double* q, double* w) {
       const Prim<double> p = to_prim<double>(q[0], q[1], q[2], q[3], q[4], gas.gm1);
       w[0] = p.r;
       w[1] = p.u;
@@ -760,179 +882,245 @@ __global__ void __launch_bounds__(256) k_wcns5_euler_march(Line Q, Line S, doubl
       w[3] = p.w;
       w[4] = p.p;
     };
+    auto load_face = [&](int x, double* a) {
+      const LineRef at = M.at(S, x, n);
 #pragma unroll
-    for (int k = 1; k < 6; ++k) load(x0 - 6 + k, W[k]);
-    for (int v = x0 - 3; v <= x1 + 1; ++v) {
+      for (int k = 0; k < 3; ++k) a[k] = at[3 * D + k];
+    };
+    double qn[5], sn[3] = {0, 0, 0}, w4[5];
+    load(x0 - 5, qn);
+    prim(qn, w4);
 #pragma unroll
-      for (int k = 0; k < 5; ++k)
+    for (int k = 0; k < 4; ++k) {
+      load(x0 - 4 + k, qn);
+      prim(qn, W[k]);
+    }
 #pragma unroll
-        for (int q = 0; q < 5; ++q) {
-          W[k][q] = W[k + 1][q];
-          F[k][q] = F[k + 1][q];
-        }
-      load(v + 3, W[5]);
-      double L[5], R[5];
+    for (int q = 0; q < 5; ++q) L[q] = wcns5_left(w4[q], W[0][q], W[1][q], W[2][q], W[3][q], eps);
+    load(x0, qn);
+    if (S.own) load_face(x0 - 3, sn);
+    int slot = 0;
+#pragma unroll 1
+    for (int v = x0 - 3; v <= x1 + 1; ++v) {   // face v; W: cells v - 1 .. v + 2
+      prim(qn, w4);
+      const double sx = sn[0], sy = sn[1], sz = sn[2];
+      load(v + 4, qn);
+      if (S.own) load_face(v + 1, sn);
+      const int64_t c = M.cell(max(v - 2, x0), n);   // the cell that face v finishes, from face x0 + 2 on
+      double rv[5], ji = 1.0;
+#pragma unroll
+      for (int q = 0; q < 5; ++q) rv[q] = r[q * cells + c];
+      if constexpr (MODE == 2) ji = jinv[c];
+      double LF[5], R[5], fn[5];
 #pragma unroll
       for (int q = 0; q < 5; ++q) {
-        L[q] = wcns5_left(W[0][q], W[1][q], W[2][q], W[3][q], W[4][q], eps);
-        R[q] = wcns5_left(W[5][q], W[4][q], W[3][q], W[2][q], W[1][q], eps);
+        LF[q] = L[q];
+        wcns5_pair(W[0][q], W[1][q], W[2][q], W[3][q], w4[q], eps, L[q], R[q]);
+        asm volatile("" : "+v"(L[q]));   // formed here: sunk to its use a face later, its inputs would stay live
+        W[0][q] = W[1][q];
+        W[1][q] = W[2][q];
+        W[2][q] = W[3][q];
+        W[3][q] = w4[q];
+      }
+      const Prim<double> PL{LF[0], LF[1], LF[2], LF[3], LF[4]};
+      const Prim<double> PR{R[0], R[1], R[2], R[3], R[4]};
+      if (!S.own) {
+        roe<double>(PL, PR, D == 0 ? 1.0 : 0.0, D == 1 ? 1.0 : 0.0, D == 2 ? 1.0 : 0.0, gas, fn);
+      } else {
+        const double area = fsqrt(sx * sx + sy * sy + sz * sz);
+        const double ia = frcp(area);
+        roe<double>(PL, PR, sx * ia, sy * ia, sz * ia, gas, fn);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) fn[q] *= area;
+      }
+      const int s1 = slot == 4 ? 0 : slot + 1;   // face v - 4; face v - 5 in slot, which face v takes
+      if (v >= x0 + 2) {   // cell v - 2: faces v - 5 .. v
+        const int s2 = s1 == 4 ? 0 : s1 + 1, s3 = s2 == 4 ? 0 : s2 + 1, s4 = s3 == 4 ? 0 : s3 + 1;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+          const double *f0 = &F[slot][q][tid], *f1 = &F[s1][q][tid], *f2 = &F[s2][q][tid], *f3 = &F[s3][q][tid],
+                       *f4 = &F[s4][q][tid];
+          const double o = rv[q] + (c1 * (*f3 - *f2) + c2 * (*f4 - *f1) + c3 * (fn[q] - *f0));
+          r[q * cells + c] = MODE == 2 ? o / ji : o;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 5; ++q) F[slot][q][tid] = fn[q];
+      slot = s1;
+    }
+  }
+}
+
+// The one-pass kernels take blocks of 32 k cells in all: below that the three
+// passes' thousands of short threads are quicker (16^3 41 us a residual against
+// 46, 24^3 43 against 46; 32^3 equal; 48^3 67 against 52, 128 x 64 x 64 131
+// against 86).  Rows under eight cells would be mostly end positions.
+bool one_pass_ok(const std::vector<EulerBlk>& v) {
+  int64_t cells = 0;
+  for (const EulerBlk& b : v) {
+    if (b.n[0] < 8) return false;
+    cells += (int64_t)b.n[0] * b.n[1] * b.n[2];
+  }
+  return cells >= (int64_t)1 << 15;
+}
+
+// Chunks of 32 cells, halved down to 4 while they give fewer than 64 k threads:
+// each chunk computes five extra faces.
+int euler_chunk(const std::vector<EulerBlk>& v, int d) {
+  int chunk = 32;
+  while (chunk > 4 && march_threads(v, d, chunk) < (int64_t)1 << 16) chunk /= 2;
+  return chunk;
+}
+
+// One direction d (1 or 2) of the inviscid residual added into the blocks' r;
+// div: the sums then divided by J^{-1} (curvilinear, last direction).
+void euler_march_launch(const std::vector<EulerBlk>& v, int d, bool div, double eps, double c1, double c2, double c3,
+                        const Gas<double>& gas, hipStream_t stream) {
+  const int ch = euler_chunk(v, d);
+  for_batches(
+      v, [&](const EulerBlk& b) { return d == 1 ? MarchAt<1>::items(b.n, ch) : MarchAt<2>::items(b.n, ch); },
+      [&](const Batch<EulerBlk>& B, int count, int64_t wgs) {
+        const dim3 g((unsigned)std::min<int64_t>(wgs, 1 << 16), count), t(256);
+        if (d == 1 && !div) hipLaunchKernelGGL((k_wcns5_euler_march<1, 1>), g, t, 0, stream, B, ch, eps, c1, c2, c3, gas);
+        else if (d == 1) hipLaunchKernelGGL((k_wcns5_euler_march<1, 2>), g, t, 0, stream, B, ch, eps, c1, c2, c3, gas);
+        else if (!div) hipLaunchKernelGGL((k_wcns5_euler_march<2, 1>), g, t, 0, stream, B, ch, eps, c1, c2, c3, gas);
+        else hipLaunchKernelGGL((k_wcns5_euler_march<2, 2>), g, t, 0, stream, B, ch, eps, c1, c2, c3, gas);
+      });
+}
+
+// The inviscid residual along i in one pass.  The rows, each with the five cells
+// beyond either end, count as one sequence of positions; a wave takes a run of
+// trips of 64 positions.  Each trip loads 64 cells as primitives into an LDS
+// ring, forms both face states of the cells two positions back (wcns5_pair),
+// takes the left states of the cell before from the lane below, computes the
+// faces between them into a second ring and stores Eq. 2 of the cells five
+// back.  Bound by FP64 issue: what counts is idle lanes, ten positions a row
+// and ten a run (256 x 128 x 128: 141 us; 211 us with a segment of 59 cells a wave
+// and each state formed alone, where rows of 128 cells left a third of the
+// lanes idle).
+struct RowPos {
+  int x, j, k;   // position within the row (cell x - 5), the row
+  __device__ __forceinline__ RowPos(int64_t p, int m, int n1) {
+    const int64_t row = (p + m) / m - 1;   // p >= -m
+    x = (int)(p - row * m);
+    k = (int)((row + n1) / n1) - 1;
+    j = (int)(row - (int64_t)k * n1);
+  }
+  __device__ __forceinline__ void advance(int m, int n1) {
+    x += 64;
+    while (x >= m) {
+      x -= m;
+      if (++j == n1) {
+        j = 0;
+        ++k;
+      }
+    }
+  }
+};
+
+// v of the lane below; lane 0 gets the last lane's *carry*, which then becomes this v's.
+__device__ __forceinline__ double lane_below(double v, double& carry) {
+  const double c = carry;
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  carry = __hiloint2double(__builtin_amdgcn_readlane(hi, 63), __builtin_amdgcn_readlane(lo, 63));
+  const double s = __shfl_up(v, 1);
+  return (threadIdx.x & 63) ? s : c;
+}
+
+__global__ void __launch_bounds__(256, 4) k_wcns5_euler_rows(Batch<EulerBlk> Bt, int trips, double eps, double c1,
+                                                             double c2, double c3, Gas<double> gas) {
+  __shared__ double sp[4][5][128];
+  __shared__ double sf[4][5][128];
+  const EulerBlk& Bk = Bt.b[blockIdx.y];
+  const Line Q = Bk.Q, S = Bk.S;
+  double* __restrict__ const r = Bk.r;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int m = n[0] + 10;
+  const int64_t cells = (int64_t)n[0] * n[1] * n[2];
+  const int64_t T = (int64_t)n[1] * n[2] * m;
+  const int run = 64 * trips - 10;
+  for (int64_t b0 = ((int64_t)blockIdx.x * 4 + w) * run; b0 < T; b0 += (int64_t)gridDim.x * 4 * run) {
+    RowPos A(b0 - 5 + lane, m, n[1]), B(b0 - 8 + lane, m, n[1]), C(b0 - 10 + lane, m, n[1]);   // cell, face, store
+    double qn[5], carry[5] = {0, 0, 0, 0, 0};
+    auto load = [&]() {
+      const bool in = (unsigned)A.k < (unsigned)n[2];
+      const int c0[3] = {0, in ? A.j : 0, in ? A.k : 0};
+      const LineRef q = wrap_ref(Q, c0, A.x - 5, 0, n);
+#pragma unroll
+      for (int f = 0; f < 5; ++f) qn[f] = q[f];
+    };
+    load();
+    for (int t = 0; t < trips; ++t) {
+      const int i = 64 * t + lane;
+      const Prim<double> P = to_prim<double>(qn[0], qn[1], qn[2], qn[3], qn[4], gas.gm1);
+      const double own[5] = {P.r, P.u, P.v, P.w, P.p};
+#pragma unroll
+      for (int q = 0; q < 5; ++q) sp[w][q][i & 127] = own[q];
+      double sx = 1.0, sy = 0.0, sz = 0.0;
+      if (S.own) {   // the face between the cells three and two back
+        const bool in = (unsigned)B.k < (unsigned)n[2];
+        const int c0[3] = {0, in ? B.j : 0, in ? B.k : 0};
+        const LineRef sr = wrap_ref(S, c0, B.x - 5, 0, n);
+        sx = sr[0];
+        sy = sr[1];
+        sz = sr[2];
+        B.advance(m, n[1]);
+      }
+      if (t + 1 < trips) {
+        A.advance(m, n[1]);
+        load();
+      }
+      wave_lds_sync();
+      double L[5], R[5], fl[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        const double* u = sp[w][q];
+        double l;
+        wcns5_pair(u[(i - 4) & 127], u[(i - 3) & 127], u[(i - 2) & 127], u[(i - 1) & 127], own[q], eps, l, R[q]);
+        L[q] = lane_below(l, carry[q]);
       }
       const Prim<double> PL{L[0], L[1], L[2], L[3], L[4]};
       const Prim<double> PR{R[0], R[1], R[2], R[3], R[4]};
-      double fl[5];
       if (!S.own) {
-        roe<double>(PL, PR, D == 0 ? 1.0 : 0.0, D == 1 ? 1.0 : 0.0, D == 2 ? 1.0 : 0.0, gas, fl);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) F[5][q] = fl[q];
+        roe<double>(PL, PR, 1.0, 0.0, 0.0, gas, fl);
       } else {
-        const LineRef sr = wrap_ref(S, c0, v, D, n);
-        const double sx = sr[3 * D], sy = sr[3 * D + 1], sz = sr[3 * D + 2];
         const double area = fsqrt(sx * sx + sy * sy + sz * sz);
         const double ia = frcp(area);
         roe<double>(PL, PR, sx * ia, sy * ia, sz * ia, gas, fl);
 #pragma unroll
-        for (int q = 0; q < 5; ++q) F[5][q] = fl[q] * area;
+        for (int q = 0; q < 5; ++q) fl[q] *= area;
       }
-      if (v >= x0 + 2) {   // cell v - 2: faces v - 5 .. v
-        int p[3] = {c0[0], c0[1], c0[2]};
-        p[D] = v - 2;
-        const int64_t c = ((int64_t)p[2] * n[1] + p[1]) * n0 + p[0];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) sf[w][q][i & 127] = fl[q];
+      wave_lds_sync();
+      if (i >= 10 && C.x >= 5 && C.x < n[0] + 5 && (unsigned)C.k < (unsigned)n[2]) {
+        const int64_t c = ((int64_t)C.k * n[1] + C.j) * n[0] + (C.x - 5);
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
-          const double o = c1 * (F[3][q] - F[2][q]) + c2 * (F[4][q] - F[1][q]) + c3 * (F[5][q] - F[0][q]);
-          double* at = r + q * cells + c;
-          if constexpr (MODE == 2) *at = (*at + o) / jinv[c];
-          else *at += o;
+          const double* F = sf[w][q];
+          r[q * cells + c] = c1 * (F[(i - 2) & 127] - F[(i - 3) & 127]) + c2 * (F[(i - 1) & 127] - F[(i - 4) & 127]) +
+                             c3 * (fl[q] - F[(i - 5) & 127]);
         }
       }
+      C.advance(m, n[1]);
     }
   }
 }
 
-// The inviscid marches take chunks of 32 cells: each chunk computes five
-// extra faces (and converts ten extra cells), an overhead that shorter chunks
-// make larger than the passes they replace.  A block whose lines give fewer
-// than 64 k such chunks (too few workgroups to fill the chip) keeps the
-// padded-primitive, face and Eq. 2 passes instead (measured: 128 x 64 x 64
-// blocks ran 1.4 % slower per step with 8-cell chunks).
-constexpr int EULER_CHUNK = 32;
-bool euler_march_ok(const int n[3], int d) {
-  return (int64_t)n[0] * n[d == 1 ? 2 : 1] * ((n[d] + EULER_CHUNK - 1) / EULER_CHUNK) >= (int64_t)1 << 16;
-}
-
-// One direction d (1 or 2) of the inviscid residual of a block added into r;
-// div: the sum then divided by J^{-1} (curvilinear, last direction).
-void euler_march_launch(const Line& Q, const Line& S, double* r, const double* jinv, const int n[3], int d, bool div,
-                        double eps, double c1, double c2, double c3, const Gas<double>& gas, hipStream_t stream) {
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int ch = EULER_CHUNK;
-  const int64_t th = (int64_t)n[0] * n[d == 1 ? 2 : 1] * ((n[d] + ch - 1) / ch);
-  const dim3 g(grid_for(th)), b(256);
-  if (d == 1 && !div) hipLaunchKernelGGL((k_wcns5_euler_march<1, 1>), g, b, 0, stream, Q, S, r, jinv, D, ch, eps, c1, c2, c3, gas);
-  else if (d == 1) hipLaunchKernelGGL((k_wcns5_euler_march<1, 2>), g, b, 0, stream, Q, S, r, jinv, D, ch, eps, c1, c2, c3, gas);
-  else if (!div) hipLaunchKernelGGL((k_wcns5_euler_march<2, 1>), g, b, 0, stream, Q, S, r, jinv, D, ch, eps, c1, c2, c3, gas);
-  else hipLaunchKernelGGL((k_wcns5_euler_march<2, 2>), g, b, 0, stream, Q, S, r, jinv, D, ch, eps, c1, c2, c3, gas);
-}
-
-// The inviscid residual along i in one pass: each wave takes a segment of 59
-// cells of a row, converts the 69 cells around it to primitives into LDS
-// (coalesced along i), computes the segment's 64 face fluxes, one per lane,
-// into LDS, then stores Eq. 2 of each cell into R (the first direction).  The
-// arithmetic is that of k_pad_prim_*, k_wcns5_roe_faces and the Eq. 2 pass.
-constexpr int EROW_SEG = 59, EROW_CELLS = EROW_SEG + 10, EROW_FACES = EROW_SEG + 5;
-
-__global__ void __launch_bounds__(256) k_wcns5_euler_rows(Line Q, Line S, double* __restrict__ r, Dims3 Dm,
-                                                          double eps, double c1, double c2, double c3,
-                                                          Gas<double> gas) {
-  __shared__ double sp[4][5][EROW_CELLS + 3];
-  __shared__ double sf[4][5][EROW_FACES];
-  const int* n = Dm.n;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nseg = (n[0] + EROW_SEG - 1) / EROW_SEG;
-  const int64_t cells = (int64_t)n[0] * n[1] * n[2];
-  const int64_t items = (int64_t)n[1] * n[2] * nseg;
-  for (int64_t base = (int64_t)blockIdx.x * 4; base < items; base += (int64_t)gridDim.x * 4) {
-    const int64_t it = base + w;
-    const bool act = it < items;
-    int c0[3] = {0, 0, 0}, x0 = 0, x1 = 0;
-    if (act) {
-      const int64_t row = it / nseg;
-      x0 = (int)(it % nseg) * EROW_SEG;
-      x1 = min(x0 + EROW_SEG, n[0]);
-      c0[1] = (int)(row % n[1]);
-      c0[2] = (int)(row / n[1]);
-      for (int e = lane; e < EROW_CELLS; e += 64) {
-        const int x = x0 - 5 + e;
-        if (x <= x1 + 4) {
-          const LineRef q = wrap_ref(Q, c0, x, 0, n);
-          const Prim<double> p = to_prim<double>(q[0], q[1], q[2], q[3], q[4], gas.gm1);
-          sp[w][0][e] = p.r;
-          sp[w][1][e] = p.u;
-          sp[w][2][e] = p.v;
-          sp[w][3][e] = p.w;
-          sp[w][4][e] = p.p;
-        }
-      }
-    }
-    __syncthreads();
-    if (act) {
-      const int v = x0 - 3 + lane;   // face between cells v and v + 1: cells v - 2 .. v + 3 at lane .. lane + 5
-      if (v <= x1 + 1) {
-        double L[5], R[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-          const double* u = &sp[w][q][lane];
-          L[q] = wcns5_left(u[0], u[1], u[2], u[3], u[4], eps);
-          R[q] = wcns5_left(u[5], u[4], u[3], u[2], u[1], eps);
-        }
-        const Prim<double> PL{L[0], L[1], L[2], L[3], L[4]};
-        const Prim<double> PR{R[0], R[1], R[2], R[3], R[4]};
-        double fl[5];
-        if (!S.own) {
-          roe<double>(PL, PR, 1.0, 0.0, 0.0, gas, fl);
-#pragma unroll
-          for (int q = 0; q < 5; ++q) sf[w][q][lane] = fl[q];
-        } else {
-          const LineRef sr = wrap_ref(S, c0, v, 0, n);
-          const double sx = sr[0], sy = sr[1], sz = sr[2];
-          const double area = fsqrt(sx * sx + sy * sy + sz * sz);
-          const double ia = frcp(area);
-          roe<double>(PL, PR, sx * ia, sy * ia, sz * ia, gas, fl);
-#pragma unroll
-          for (int q = 0; q < 5; ++q) sf[w][q][lane] = fl[q] * area;
-        }
-      }
-    }
-    __syncthreads();
-    if (act && lane < EROW_SEG) {
-      const int x = x0 + lane;   // faces x - 3 .. x + 2 at lane .. lane + 5
-      if (x < x1) {
-        const int64_t c = ((int64_t)c0[2] * n[1] + c0[1]) * n[0] + x;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-          const double* F = &sf[w][q][lane];
-          r[q * cells + c] = c1 * (F[3] - F[2]) + c2 * (F[4] - F[1]) + c3 * (F[5] - F[0]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Rows of n cells leave idle lanes in the last segment's faces; the row pass
-// is used where its face slots stay within 1.25 times the n + 5 faces needed
-// (256- and 512-cell rows: 1.23, 1.11; 128 cells: 1.44).
-bool euler_rows_ok(int n0) {
-  const int64_t nseg = (n0 + EROW_SEG - 1) / EROW_SEG;
-  return nseg * 64 * 4 <= (int64_t)(n0 + 5) * 5;
-}
-
-void euler_rows_launch(const Line& Q, const Line& S, double* r, const int n[3], double eps, double c1, double c2,
-                       double c3, const Gas<double>& gas, hipStream_t stream) {
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int64_t items = (int64_t)n[1] * n[2] * ((n[0] + EROW_SEG - 1) / EROW_SEG);
-  const int grid = (int)std::min<int64_t>((items + 3) / 4, 1 << 16);
-  hipLaunchKernelGGL(k_wcns5_euler_rows, dim3(grid), dim3(256), 0, stream, Q, S, r, D, eps, c1, c2, c3, gas);
+void euler_rows_launch(const std::vector<EulerBlk>& v, double eps, double c1, double c2, double c3,
+                       const Gas<double>& gas, hipStream_t stream) {
+  auto positions = [](const EulerBlk& b) { return (int64_t)b.n[1] * b.n[2] * (b.n[0] + 10); };
+  int64_t all = 0;
+  for (const EulerBlk& b : v) all += positions(b);
+  // four waves a SIMD where there is work for them; 2 to 32 trips a run
+  const int trips = (int)std::min<int64_t>(32, std::max<int64_t>(2, (all + 64 * 4096 - 1) / (64 * 4096)));
+  const int64_t run = 64 * trips - 10;
+  for_batches(v, positions, [&](const Batch<EulerBlk>& B, int count, int64_t most) {
+    const int64_t wgs = ((most + run - 1) / run + 3) / 4;
+    hipLaunchKernelGGL(k_wcns5_euler_rows, dim3((unsigned)std::min<int64_t>(wgs, 1 << 16), count), dim3(256), 0, stream,
+                       B, trips, eps, c1, c2, c3, gas);
+  });
 }
 
 // The periodic WCNS-E-5 residual along the three directions.  Cartesian when
@@ -967,16 +1155,12 @@ void wcns5_residual_core(const double* q_dev, const double* s_dev, const double*
   for (int d = 0; d < 3; ++d) {
     const double hd = s_dev ? 1.0 : h[d];
     const double c1 = 75.0 / (64.0 * hd), c2 = -25.0 / (384.0 * hd), c3 = 3.0 / (640.0 * hd);
-    if (d == 0 && euler_rows_ok(n[0])) {   // i: one row pass
-      const Line Q{q_dev, q_dev, q_dev, cells, cells, cells, n[0], n[0]};
-      const Line S{s_dev, s_dev, s_dev, cells, cells, cells, n[0], n[0]};
-      euler_rows_launch(Q, S, r_dev, n, eps, c1, c2, c3, gas, stream);
-      continue;
-    }
-    if (d > 0 && euler_march_ok(n, d)) {   // j and k: one marching pass (the last one divides the sum by J^{-1})
-      const Line Q{q_dev, q_dev, q_dev, cells, cells, cells, n[d], n[d]};
-      const Line S{s_dev, s_dev, s_dev, cells, cells, cells, n[d], n[d]};
-      euler_march_launch(Q, S, r_dev, jinv_dev, n, d, d == 2 && s_dev, eps, c1, c2, c3, gas, stream);
+    const std::vector<EulerBlk> one{EulerBlk{{q_dev, q_dev, q_dev, cells, cells, cells, n[d], n[d]},
+                                             {s_dev, s_dev, s_dev, cells, cells, cells, n[d], n[d]},
+                                             r_dev, jinv_dev, {n[0], n[1], n[2]}}};
+    if (one_pass_ok(one)) {   // the last march divides the sum by J^{-1}
+      if (d == 0) euler_rows_launch(one, eps, c1, c2, c3, gas, stream);
+      else euler_march_launch(one, d, d == 2 && s_dev, eps, c1, c2, c3, gas, stream);
       continue;
     }
     int64_t mp[3] = {n[0], n[1], n[2]}, mf[3] = {n[0], n[1], n[2]};
@@ -1151,11 +1335,11 @@ struct RkArgs {
   double dt, a, b;
   int keep;
 };
-// Whether a block's last viscous pass applies the RK3 stage itself: only where
-// its k march runs whole 32-cell chunks (on 128 x 64 x 64 blocks, with 8-cell
-// chunks, the fused update measured 3 % slower per step than a separate pass).
-int visc_chunk(const int n[3], int d);
-inline bool rk_fused(const int n[3]) { return visc_chunk(n, 2) >= 32; }
+// Whether the last viscous pass applies the RK3 stage itself: only where its k
+// march runs whole 32-cell chunks (with 8-cell chunks the fused update measured
+// 3 % slower per step than a separate pass).  dims: the blocks' extents; skip:
+// blocks without an update.
+bool rk_fused(int nblk, const int32_t* dims, const char* skip);
 void c4_viscous_curv_core(const double* q_dev, const double* s_dev, const double* jinv_dev, double* r_dev,
                           double* work, const double* fm, const int32_t n[3], const Gas<double>& gas,
                           hipStream_t stream, const RkArgs* rk = nullptr);
@@ -1192,7 +1376,7 @@ void wcns5_steps_core(double* q_dev, const double* s_dev, const double* jinv_dev
   for (int it = 0; it < nsteps; ++it)
     for (int st = 0; st < 3; ++st) {
       wcns5_residual_core(q_dev, s_dev, jinv_dev, r, work_dev, rw0, n, h, gamma, entropy_fix, eps, stream);
-      if (visc && rk_fused(n)) {   // the last viscous pass applies the stage
+      if (visc && rk_fused(1, n, nullptr)) {   // the last viscous pass applies the stage
         const RkArgs K{q_dev, qn, dt, a[st], b[st], st == 0 ? 1 : 0};
         c4_viscous_curv_core(q_dev, s_dev, jinv_dev, r, static_cast<double*>(work_dev), fm, n, *visc, stream, &K);
       } else {
@@ -1606,6 +1790,13 @@ size_t check_seams(int32_t nblk, const int32_t* dims, const int32_t* nbr) {
 
 namespace cfd {
 
+// The line along d around block b over per-block arrays.
+Line block_line(int b, int d, const int32_t* dims, const int32_t* nbr, const double* const* bases) {
+  const int lo = nbr[6 * b + 2 * d], hi = nbr[6 * b + 2 * d + 1];
+  return Line{bases[b], bases[lo], bases[hi], block_cells(dims, b), block_cells(dims, lo), block_cells(dims, hi),
+              dims[3 * lo + d], dims[3 * hi + d]};
+}
+
 // The residual of blocks joined face to face (arguments checked by the caller).
 void wcns5_blocks_residual_launch(int32_t nblk, const int32_t* dims, const int32_t* nbr, const double* const* q_dev,
                                   const double* const* s_dev, const double* const* jinv_dev, double* const* r_dev,
@@ -1616,44 +1807,39 @@ void wcns5_blocks_residual_launch(int32_t nblk, const int32_t* dims, const int32
   gas.gm1 = gamma - 1.0;
   gas.gg = gamma / (gamma - 1.0);
   gas.eps_h = entropy_fix;
-  for (int b = 0; b < nblk; ++b) {
-    if (skip && skip[b]) continue;   // a block whose residual nobody reads (a refilled ghost block)
-    const int32_t* n = dims + 3 * b;
-    int64_t pmax, fmax;
-    wcns5_work(n, pmax, fmax);
-    double* W = static_cast<double*>(work_dev);
-    double* F = W + pmax;
-    for (int d = 0; d < 3; ++d) {
-      const int lo = nbr[6 * b + 2 * d], hi = nbr[6 * b + 2 * d + 1];
-      const int nlo = dims[3 * lo + d], nhi = dims[3 * hi + d];
-      if (d == 0 && euler_rows_ok(n[0])) {   // i: one row pass across the seams
-        const Line Q{q_dev[b], q_dev[lo], q_dev[hi], block_cells(dims, b), block_cells(dims, lo),
-                     block_cells(dims, hi), nlo, nhi};
-        const Line S{s_dev[b], s_dev[lo], s_dev[hi], block_cells(dims, b), block_cells(dims, lo),
-                     block_cells(dims, hi), nlo, nhi};
-        euler_rows_launch(Q, S, r_dev[b], n, eps, 75.0 / 64.0, -25.0 / 384.0, 3.0 / 640.0, gas, stream);
-        continue;
-      }
-      if (d > 0 && euler_march_ok(n, d)) {   // j and k: one marching pass across the seams (the last divides by J^{-1})
-        const Line Q{q_dev[b], q_dev[lo], q_dev[hi], block_cells(dims, b), block_cells(dims, lo),
-                     block_cells(dims, hi), nlo, nhi};
-        const Line S{s_dev[b], s_dev[lo], s_dev[hi], block_cells(dims, b), block_cells(dims, lo),
-                     block_cells(dims, hi), nlo, nhi};
-        euler_march_launch(Q, S, r_dev[b], jinv_dev[b], n, d, d == 2, eps, 75.0 / 64.0, -25.0 / 384.0,
-                           3.0 / 640.0, gas, stream);
-        continue;
-      }
+  const double c1 = 75.0 / 64.0, c2 = -25.0 / 384.0, c3 = 3.0 / 640.0;
+  for (int d = 0; d < 3; ++d) {
+    std::vector<EulerBlk> v;
+    std::vector<int> id;
+    for (int b = 0; b < nblk; ++b) {
+      if (skip && skip[b]) continue;   // a block whose residual nobody reads (a refilled ghost block)
+      const int32_t* n = dims + 3 * b;
+      v.push_back({block_line(b, d, dims, nbr, q_dev), block_line(b, d, dims, nbr, s_dev), r_dev[b], jinv_dev[b],
+                   {n[0], n[1], n[2]}});
+      id.push_back(b);
+    }
+    if (one_pass_ok(v)) {   // across the seams; the last march divides by J^{-1}
+      if (d == 0) euler_rows_launch(v, eps, c1, c2, c3, gas, stream);
+      else euler_march_launch(v, d, d == 2, eps, c1, c2, c3, gas, stream);
+      continue;
+    }
+    for (size_t k = 0; k < v.size(); ++k) {
+      const int b = id[k];
+      const int32_t* n = dims + 3 * b;
+      const Line &Q = v[k].Q, &S = v[k].S;
+      int64_t pmax, fmax;
+      wcns5_work(n, pmax, fmax);
+      double* W = static_cast<double*>(work_dev);
+      double* F = W + pmax;
       int64_t mp[3] = {n[0], n[1], n[2]}, mf[3] = {n[0], n[1], n[2]};
       mp[d] += 10;
       mf[d] += 5;
       const int64_t nf = mf[0] * mf[1] * mf[2];
-      hipLaunchKernelGGL(k_pad_prim_blocks, dim3(grid_for(mp[0] * mp[1] * mp[2])), dim3(256), 0, stream,
-                         q_dev[b], q_dev[lo], q_dev[hi], W, n[0], n[1], n[2], d, nlo, nhi, gamma - 1.0);
-      hipLaunchKernelGGL(k_wcns5_roe_faces, dim3(grid_for(nf)), dim3(256), 0, stream, W, F, (int)mf[0],
-                         (int)mf[1], (int)mf[2], d, eps, s_dev[b], s_dev[lo], s_dev[hi], n[0], n[1], n[2], nlo, nhi,
-                         gas);
+      hipLaunchKernelGGL(k_pad_prim_blocks, dim3(grid_for(mp[0] * mp[1] * mp[2])), dim3(256), 0, stream, Q.own, Q.lo,
+                         Q.hi, W, n[0], n[1], n[2], d, Q.nlo, Q.nhi, gamma - 1.0);
+      hipLaunchKernelGGL(k_wcns5_roe_faces, dim3(grid_for(nf)), dim3(256), 0, stream, W, F, (int)mf[0], (int)mf[1],
+                         (int)mf[2], d, eps, S.own, S.lo, S.hi, n[0], n[1], n[2], S.nlo, S.nhi, gas);
       const int64_t m[3] = {n[0], n[1], n[2]};
-      const double c1 = 75.0 / 64.0, c2 = -25.0 / 384.0, c3 = 3.0 / 640.0;
       if (d == 0)
         launch_window6(F, r_dev[b], nullptr, m, d, 5, Eq2OpT<false>{c1, c2, c3}, stream);
       else if (d == 2)            // the last pass also divides the sum by J^{-1}
@@ -1715,10 +1901,22 @@ namespace cfd {
 // writes phi of its own 60 cells.
 constexpr int PGI_SEG = 60;
 
-__global__ void __launch_bounds__(256) k_c4_phi_grads_i(Line Q, double* __restrict__ phi, double* __restrict__ g,
-                                                        Dims3 Dm, double gm1) {
+// A block's u, v, w, T pass: its state (along i) or phi (along d) line, phi (4
+// fields) and the index derivatives g (12).
+struct PhiBlk {
+  Line L;
+  double* phi;
+  double* g;
+  int n[3];
+};
+
+__global__ void __launch_bounds__(256) k_c4_phi_grads_i(Batch<PhiBlk> Bt, double gm1) {
   __shared__ double sp[4][4][64];
-  const int* n = Dm.n;
+  const PhiBlk& Bk = Bt.b[blockIdx.y];
+  const Line Q = Bk.L;
+  double* __restrict__ const phi = Bk.phi;
+  double* __restrict__ const g = Bk.g;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nseg = (n[0] + PGI_SEG - 1) / PGI_SEG;
   const int64_t cells = (int64_t)n[0] * n[1] * n[2];
@@ -1768,23 +1966,20 @@ __global__ void __launch_bounds__(256) k_c4_phi_grads_i(Line Q, double* __restri
 // so every cell is read once per chunk instead of four times from other rows
 // or planes.
 template <int D>
-__global__ void __launch_bounds__(256) k_c4_grads_march(Line phi, double* __restrict__ g, Dims3 Dm, int chunk) {
-  constexpr int O = D == 1 ? 2 : 1;
-  const int* n = Dm.n;
-  const int nD = n[D], nO = n[O], n0 = n[0];
-  const int nch = (nD + chunk - 1) / chunk;
-  const int64_t cells = (int64_t)n0 * n[1] * n[2];
-  const int64_t total = (int64_t)n0 * nO * nch;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    int c0[3];
-    c0[0] = (int)(t % n0);
-    const int64_t rest = t / n0;
-    c0[O] = (int)(rest % nO);
-    c0[D] = 0;
-    const int x0 = (int)(rest / nO) * chunk, x1 = min(x0 + chunk, nD);
+__global__ void __launch_bounds__(256) k_c4_grads_march(Batch<PhiBlk> Bt, int chunk) {
+  const PhiBlk& Bk = Bt.b[blockIdx.y];
+  const Line phi = Bk.L;
+  double* __restrict__ const g = Bk.g;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
+  const int64_t cells = (int64_t)n[0] * n[1] * n[2];
+  const int64_t items = MarchAt<D>::items(n, chunk);
+  for (int64_t t = blockIdx.x; t < items; t += gridDim.x) {
+    const MarchAt<D> M(t, chunk, n);
+    if (!M.in) continue;
+    const int x0 = M.x0, x1 = M.x1;
     double w[5][4];
     auto load = [&](int x, double* v) {
-      const LineRef r = wrap_ref(phi, c0, x, D, n);
+      const LineRef r = M.at(phi, x, n);
 #pragma unroll
       for (int a = 0; a < 4; ++a) v[a] = r[a];
     };
@@ -1796,9 +1991,7 @@ __global__ void __launch_bounds__(256) k_c4_grads_march(Line phi, double* __rest
 #pragma unroll
         for (int a = 0; a < 4; ++a) w[k][a] = w[k + 1][a];
       load(x + 2, w[4]);
-      int p[3] = {c0[0], c0[1], c0[2]};
-      p[D] = x;
-      const int64_t c = ((int64_t)p[2] * n[1] + p[1]) * n0 + p[0];
+      const int64_t c = M.cell(x, n);
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const double m2 = w[0][a], m1 = w[1][a], p1 = w[3][a], p2 = w[4][a];
@@ -1808,36 +2001,51 @@ __global__ void __launch_bounds__(256) k_c4_grads_march(Line phi, double* __rest
   }
 }
 
-// Chunk of the gradient marches: 32 cells, halved (down to 8) while the grid
-// gives fewer than 128 k threads.
-int grads_chunk(const int n[3], int d) {
-  const int o = d == 1 ? 2 : 1;
+// Chunk of the gradient and viscous marches: 32 cells, halved (down to 8) while
+// the blocks give fewer than 128 k threads.
+template <class Blk>
+int march_chunk(const std::vector<Blk>& v, int d) {
   int chunk = 32;
-  while (chunk > 8 && (int64_t)n[0] * n[o] * ((n[d] + chunk - 1) / chunk) < (int64_t)1 << 17) chunk /= 2;
+  while (chunk > 8 && march_threads(v, d, chunk) < (int64_t)1 << 17) chunk /= 2;
   return chunk;
 }
 
-// phi and its index derivatives along i of a block (Qi: its state line along
-// i), into phi (4 fields) and g (12 fields).
-void phi_grads_i_launch(const Line& Qi, double* phi, double* g, const int n[3], double gm1, hipStream_t stream) {
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int64_t items = (int64_t)n[1] * n[2] * ((n[0] + PGI_SEG - 1) / PGI_SEG);
-  const int grid = (int)std::min<int64_t>((items + 3) / 4, 1 << 16);
-  hipLaunchKernelGGL(k_c4_phi_grads_i, dim3(grid), dim3(256), 0, stream, Qi, phi, g, D, gm1);
+// phi and its index derivatives along i of the blocks (lines: their states along i).
+void phi_grads_i_launch(const std::vector<PhiBlk>& v, double gm1, hipStream_t stream) {
+  for_batches(
+      v, [](const PhiBlk& b) { return ((int64_t)b.n[1] * b.n[2] * ((b.n[0] + PGI_SEG - 1) / PGI_SEG) + 3) / 4; },
+      [&](const Batch<PhiBlk>& B, int count, int64_t wgs) {
+        hipLaunchKernelGGL(k_c4_phi_grads_i, dim3((unsigned)std::min<int64_t>(wgs, 1 << 16), count), dim3(256), 0,
+                           stream, B, gm1);
+      });
 }
 
-// The index derivatives along j and k of a block's u, v, w, T (lines P[d]
-// over its phi fields and the neighbours', which must all be written) into g.
-void grads_jk_launch(const Line* P, double* g, const int n[3], hipStream_t stream) {
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int c1 = grads_chunk(n, 1), c2 = grads_chunk(n, 2);
-  const int64_t t1 = (int64_t)n[0] * n[2] * ((n[1] + c1 - 1) / c1), t2 = (int64_t)n[0] * n[1] * ((n[2] + c2 - 1) / c2);
-  hipLaunchKernelGGL(k_c4_grads_march<1>, dim3(grid_for(t1)), dim3(256), 0, stream, P[1], g, D, c1);
-  hipLaunchKernelGGL(k_c4_grads_march<2>, dim3(grid_for(t2)), dim3(256), 0, stream, P[2], g, D, c2);
+// The index derivatives along d = 1 or 2 of the blocks' u, v, w, T (lines over
+// their phi fields, which must all be written).
+void grads_launch(const std::vector<PhiBlk>& v, int d, hipStream_t stream) {
+  const int ch = march_chunk(v, d);
+  for_batches(
+      v, [&](const PhiBlk& b) { return d == 1 ? MarchAt<1>::items(b.n, ch) : MarchAt<2>::items(b.n, ch); },
+      [&](const Batch<PhiBlk>& B, int count, int64_t wgs) {
+        const dim3 g((unsigned)std::min<int64_t>(wgs, 1 << 16), count);
+        if (d == 1) hipLaunchKernelGGL(k_c4_grads_march<1>, g, dim3(256), 0, stream, B, ch);
+        else hipLaunchKernelGGL(k_c4_grads_march<2>, g, dim3(256), 0, stream, B, ch);
+      });
 }
 
 // sc[(t * 3 + x) * cells + c]: S_t at the cells from its faces along t.
-__global__ void __launch_bounds__(256) k_c4_cell_metrics_line(Line S, double* __restrict__ sc, Dims3 D, int t) {
+// A block's metric pass: its input line (and J^{-1}'s), the output.
+struct MetBlk {
+  Line L, J;
+  double* out;
+  int n[3];
+};
+
+__global__ void __launch_bounds__(256) k_c4_cell_metrics_line(Batch<MetBlk> Bt, int t) {
+  const MetBlk& Bk = Bt.b[blockIdx.y];
+  const Line S = Bk.L;
+  double* __restrict__ const sc = Bk.out;
+  const Dims3 D{{Bk.n[0], Bk.n[1], Bk.n[2]}};
   const int64_t cells = (int64_t)D.n[0] * D.n[1] * D.n[2];
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(c % D.n[0]), j = (int)((c / D.n[0]) % D.n[1]), k = (int)(c / ((int64_t)D.n[0] * D.n[1]));
@@ -1859,7 +2067,11 @@ constexpr int VW_PHI = 0, VW_G = 4;
 
 // Face metrics along d from the cell metrics sc (9 fields, S_t[x] at t * 3 + x)
 // and J^{-1}, four-point face values across the seams.
-__global__ void __launch_bounds__(256) k_c4_face_metrics(Line SC, Line J, double* __restrict__ fm, Dims3 D, int d) {
+__global__ void __launch_bounds__(256) k_c4_face_metrics(Batch<MetBlk> Bt, int d) {
+  const MetBlk& Bk = Bt.b[blockIdx.y];
+  const Line SC = Bk.L, J = Bk.J;
+  double* __restrict__ const fm = Bk.out;
+  const Dims3 D{{Bk.n[0], Bk.n[1], Bk.n[2]}};
   const int64_t cells = (int64_t)D.n[0] * D.n[1] * D.n[2];
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += (int64_t)gridDim.x * blockDim.x) {
     const int p[3] = {(int)(c % D.n[0]), (int)((c / D.n[0]) % D.n[1]), (int)(c / ((int64_t)D.n[0] * D.n[1]))};
@@ -1882,8 +2094,7 @@ __global__ void __launch_bounds__(256) k_c4_face_metrics(Line SC, Line J, double
 // A cell's inputs of the d-face fluxes: phi (4) and the index derivatives of
 // phi across d (8: a * 2 + u, u-th direction other than d).
 template <int D>
-__device__ __forceinline__ void load_visc_cell(const Line& PG, const int c0[3], int x, const int n[3], double w[12]) {
-  const LineRef r = wrap_ref(PG, c0, x, D, n);
+__device__ __forceinline__ void load_visc_cell(const LineRef& r, double w[12]) {
 #pragma unroll
   for (int a = 0; a < 4; ++a) w[a] = r[VW_PHI + a];
 #pragma unroll
@@ -1953,10 +2164,8 @@ __device__ __forceinline__ void visc_face_flux(const double A[12], const double 
 }
 
 template <int D>
-__device__ __forceinline__ void visc_face_at(const Line& FM, const Line& S, const int c0[3], int f, const int n[3],
-                                             const double* A, const double* B, const double* C, const double* E,
-                                             const Gas<double>& gas, double out[4]) {
-  const LineRef mr = wrap_ref(FM, c0, f, D, n), sr = wrap_ref(S, c0, f, D, n);
+__device__ __forceinline__ void visc_face_at(const LineRef& mr, const LineRef& sr, const double* A, const double* B,
+                                             const double* C, const double* E, const Gas<double>& gas, double out[4]) {
   double m[7], sd[3];
 #pragma unroll
   for (int k = 0; k < 7; ++k) m[k] = mr[D * 7 + k];
@@ -1965,103 +2174,121 @@ __device__ __forceinline__ void visc_face_at(const Line& FM, const Line& S, cons
   visc_face_flux<D>(A, B, C, E, m, sd, gas, out);
 }
 
-// r[1 + v] -= (F_{c-3/2} - 27 F_{c-1/2} + 27 F_{c+1/2} - F_{c+3/2}) / 24 / J^{-1}.
-__device__ __forceinline__ void visc_flux_sub(double* __restrict__ r, const double* __restrict__ jinv, int64_t cells,
-                                              int64_t c, const double* Fm2, const double* Fm1, const double* F0,
-                                              const double* Fp1) {
-  const double ji = jinv[c];
+// What a cell's r[1 + v] -= (F_{c-3/2} - 27 F_{c-1/2} + 27 F_{c+1/2} - F_{c+3/2})
+// / 24 / J^{-1} reads, loaded before the last of its fluxes is formed.  RK: the
+// stage of Eqs. 4-6 is applied at once, the residual being complete (nothing
+// reads the state after that pass; RkArgs: Q^(s) = a Q^n + b (Q^(s-1) - dt R),
+// Q^n kept from Q by the first stage), and not stored.
+template <bool RK>
+struct CellIn {
+  double ji, r[5], q[5], qn[5];
+  __device__ __forceinline__ CellIn(const double* __restrict__ R, const double* __restrict__ jinv, int64_t cells,
+                                    int64_t c, const RkArgs& K) {
+    ji = jinv[c];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const double dF = (Fm2[v] - 27.0 * Fm1[v] + 27.0 * F0[v] - Fp1[v]) * (1.0 / 24.0);
-    r[(1 + v) * cells + c] -= dF / ji;
-  }
-}
-
-// The RK3 stage of Eqs. 4-6 applied by the last viscous pass of a step's
-// stage, cell by cell, once its residual is complete (nothing reads the
-// state after that pass; RkArgs: Q^(s) = a Q^n + b (Q^(s-1) - dt R), Q^n
-// kept from Q by the first stage).  The residual itself is not stored.
-
-__device__ __forceinline__ void visc_flux_sub_rk(const double* __restrict__ r, const double* __restrict__ jinv,
-                                                 int64_t cells, int64_t c, const double* Fm2, const double* Fm1,
-                                                 const double* F0, const double* Fp1, const RkArgs& K) {
-  const double ji = jinv[c];
-  double R[5];
-  R[0] = r[c];
+    for (int v = RK ? 0 : 1; v < 5; ++v) r[v] = R[v * cells + c];
+    if constexpr (RK) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const double dF = (Fm2[v] - 27.0 * Fm1[v] + 27.0 * F0[v] - Fp1[v]) * (1.0 / 24.0);
-    R[1 + v] = r[(1 + v) * cells + c] - dF / ji;
-  }
+      for (int v = 0; v < 5; ++v) q[v] = K.q[v * cells + c];
+      if (!K.keep) {
 #pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    const int64_t t = v * cells + c;
-    const double x = K.q[t], y = R[v];
-    const double s = x - K.dt * y;
-    if (K.keep) {
-      K.qn[t] = x;
-      K.q[t] = s;
-    } else {
-      K.q[t] = K.a * K.qn[t] + K.b * s;
+        for (int v = 0; v < 5; ++v) qn[v] = K.qn[v * cells + c];
+      }
     }
   }
-}
+  __device__ __forceinline__ void finish(double* __restrict__ R, int64_t cells, int64_t c, const double dF[4],
+                                         const RkArgs& K) const {
+    if constexpr (!RK) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) R[(1 + v) * cells + c] = r[1 + v] - dF[v] / ji;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        const double y = v ? r[v] - dF[v - 1] / ji : r[0];
+        const double s = q[v] - K.dt * y;
+        if (K.keep) {
+          K.qn[v * cells + c] = q[v];
+          K.q[v * cells + c] = s;
+        } else {
+          K.q[v * cells + c] = K.a * qn[v] + K.b * s;
+        }
+      }
+    }
+  }
+};
+
+// A block's viscous pass along d: its phi and derivatives, face metrics and
+// face area vectors along d, its residual, J^{-1} and RK3 stage.
+struct ViscBlk {
+  Line PG, FM, S;
+  double* r;
+  const double* jinv;
+  int n[3];
+  RkArgs K;
+};
 
 // The viscous terms along d = 1 or 2 added into r: each thread marches one
 // line of cells along d (lanes along i, so every load is a coalesced row)
 // over a chunk of `chunk` cells, keeping the four cells around the current
-// face and the last four face fluxes in registers: each cell's inputs are
-// loaded once per chunk instead of once per face stencil, and the face
+// face in registers and the last three face fluxes in LDS: each cell's inputs
+// are loaded once per chunk instead of once per face stencil, and the face
 // fluxes never leave the chip.
 template <int D, bool RK>
-__global__ void __launch_bounds__(256) k_c4_visc_march(Line PG, Line FM, Line S, double* __restrict__ r,
-                                                       const double* __restrict__ jinv, Dims3 Dm, int chunk,
-                                                       Gas<double> gas, RkArgs K) {
-  constexpr int O = D == 1 ? 2 : 1;
-  const int* n = Dm.n;
-  const int nD = n[D], nO = n[O], n0 = n[0];
-  const int nch = (nD + chunk - 1) / chunk;
-  const int64_t cells = (int64_t)n0 * n[1] * n[2];
-  const int64_t total = (int64_t)n0 * nO * nch;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    int c0[3];
-    c0[0] = (int)(t % n0);
-    const int64_t rest = t / n0;
-    c0[O] = (int)(rest % nO);
-    c0[D] = 0;
-    const int x0 = (int)(rest / nO) * chunk, x1 = min(x0 + chunk, nD);
-    auto cell_index = [&](int x) {
-      int p[3] = {c0[0], c0[1], c0[2]};
-      p[D] = x;
-      return ((int64_t)p[2] * n[1] + p[1]) * n0 + p[0];
-    };
-    double W0[12], W1[12], W2[12], W3[12];
-    double F0[4], F1[4], F2[4], F3[4];
-    load_visc_cell<D>(PG, c0, x0 - 3, n, W0);
-    load_visc_cell<D>(PG, c0, x0 - 2, n, W1);
-    load_visc_cell<D>(PG, c0, x0 - 1, n, W2);
+__global__ void __launch_bounds__(256, 2) k_c4_visc_march(Batch<ViscBlk> Bt, int chunk, Gas<double> gas) {
+  __shared__ double F[3][4][256];   // the last three faces' fluxes, face g in slot (g - x0 + 2) % 3
+  const ViscBlk& Bk = Bt.b[blockIdx.y];
+  const Line PG = Bk.PG, FM = Bk.FM, S = Bk.S;
+  double* __restrict__ const r = Bk.r;
+  const double* __restrict__ const jinv = Bk.jinv;
+  const RkArgs K = Bk.K;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
+  const int tid = threadIdx.x;
+  const int64_t cells = (int64_t)n[0] * n[1] * n[2];
+  const int64_t items = MarchAt<D>::items(n, chunk);
+  for (int64_t t = blockIdx.x; t < items; t += gridDim.x) {
+    const MarchAt<D> M(t, chunk, n);
+    if (!M.in) continue;
+    const int x0 = M.x0, x1 = M.x1;
+    double W[3][12], en[12];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) load_visc_cell<D>(M.at(PG, x0 - 3 + k, n), W[k]);
+    load_visc_cell<D>(M.at(PG, x0, n), en);
+    int slot = 0;
     // face g (between cells g and g + 1) needs cells g - 1 .. g + 2; cell
-    // g - 1 is finished with face g.  Window and face slots rotate by one per
-    // face: four faces per trip, each with its own register names.
-#define CFD_VSTEP(U, A, B, C, E, FN, FA, FB, FC)                                    \
-  {                                                                               \
-    const int g = f + U;                                                          \
-    if (g <= x1) {                                                                \
-      load_visc_cell<D>(PG, c0, g + 2, n, E);                                     \
-      visc_face_at<D>(FM, S, c0, g, n, A, B, C, E, gas, FN);                      \
-      if (g > x0) {                                                               \
-        if constexpr (RK) visc_flux_sub_rk(r, jinv, cells, cell_index(g - 1), FA, FB, FC, FN, K); \
-        else visc_flux_sub(r, jinv, cells, cell_index(g - 1), FA, FB, FC, FN);   \
-      }                                                                           \
-    }                                                                             \
-  }
-    for (int f = x0 - 2; f <= x1; f += 4) {
-      CFD_VSTEP(0, W0, W1, W2, W3, F0, F1, F2, F3)
-      CFD_VSTEP(1, W1, W2, W3, W0, F1, F2, F3, F0)
-      CFD_VSTEP(2, W2, W3, W0, W1, F2, F3, F0, F1)
-      CFD_VSTEP(3, W3, W0, W1, W2, F3, F0, F1, F2)
+    // g - 1 is finished with face g.  What a face and its cell need is loaded
+    // a face ahead or before the flux is formed.
+#pragma unroll 1
+    for (int g = x0 - 2; g <= x1; ++g) {
+      double E[12], m[7], sd[3], FN[4];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) E[k] = en[k];
+      const LineRef mr = M.at(FM, g, n), sr = M.at(S, g, n);
+#pragma unroll
+      for (int k = 0; k < 7; ++k) m[k] = mr[D * 7 + k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sd[k] = sr[D * 3 + k];
+      load_visc_cell<D>(M.at(PG, g + 3, n), en);
+      const int64_t c = M.cell(max(g - 1, x0), n);
+      const CellIn<RK> in(r, jinv, cells, c, K);
+      visc_face_flux<D>(W[0], W[1], W[2], E, m, sd, gas, FN);
+      const int s1 = slot == 2 ? 0 : slot + 1, s2 = s1 == 2 ? 0 : s1 + 1;
+      if (g > x0) {
+        double dF[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          dF[v] = (F[slot][v][tid] - 27.0 * F[s1][v][tid] + 27.0 * F[s2][v][tid] - FN[v]) * (1.0 / 24.0);
+        in.finish(r, cells, c, dF, K);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) F[slot][v][tid] = FN[v];
+      slot = s1;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        W[0][k] = W[1][k];
+        W[1][k] = W[2][k];
+        W[2][k] = E[k];
+      }
     }
-#undef CFD_VSTEP
   }
 }
 
@@ -2070,11 +2297,14 @@ __global__ void __launch_bounds__(256) k_c4_visc_march(Line PG, Line FM, Line S,
 // i), computes the 67 face fluxes they need into LDS, then the differences.
 constexpr int VROW_CELLS = 70, VROW_FACES = 67;
 
-__global__ void __launch_bounds__(256) k_c4_visc_rows(Line PG, Line FM, Line S, double* __restrict__ r,
-                                                      const double* __restrict__ jinv, Dims3 Dm, Gas<double> gas) {
+__global__ void __launch_bounds__(256) k_c4_visc_rows(Batch<ViscBlk> Bt, Gas<double> gas) {
   __shared__ double sw[4][12][VROW_CELLS + 2];
   __shared__ double sf[4][4][VROW_FACES + 1];
-  const int* n = Dm.n;
+  const ViscBlk& Bk = Bt.b[blockIdx.y];
+  const Line PG = Bk.PG, FM = Bk.FM, S = Bk.S;
+  double* __restrict__ const r = Bk.r;
+  const double* __restrict__ const jinv = Bk.jinv;
+  const int n[3] = {Bk.n[0], Bk.n[1], Bk.n[2]};
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nseg = (n[0] + 63) / 64;
   const int64_t cells = (int64_t)n[0] * n[1] * n[2];
@@ -2093,7 +2323,7 @@ __global__ void __launch_bounds__(256) k_c4_visc_rows(Line PG, Line FM, Line S, 
         const int x = x0 - 3 + e;
         if (x <= x1 + 2) {
           double v[12];
-          load_visc_cell<0>(PG, c0, x, n, v);
+          load_visc_cell<0>(wrap_ref(PG, c0, x, 0, n), v);
 #pragma unroll
           for (int f = 0; f < 12; ++f) sw[w][f][e] = v[f];
         }
@@ -2112,7 +2342,7 @@ __global__ void __launch_bounds__(256) k_c4_visc_rows(Line PG, Line FM, Line S, 
             C[f] = sw[w][f][e + 2];
             E[f] = sw[w][f][e + 3];
           }
-          visc_face_at<0>(FM, S, c0, g, n, A, B, C, E, gas, out);
+          visc_face_at<0>(wrap_ref(FM, c0, g, 0, n), wrap_ref(S, c0, g, 0, n), A, B, C, E, gas, out);
 #pragma unroll
           for (int v = 0; v < 4; ++v) sf[w][v][e] = out[v];
         }
@@ -2122,51 +2352,61 @@ __global__ void __launch_bounds__(256) k_c4_visc_rows(Line PG, Line FM, Line S, 
     if (act) {
       const int x = x0 + lane;
       if (x < x1) {
-        double Fm2[4], Fm1[4], F0[4], Fp1[4];
+        const int64_t c = ((int64_t)c0[2] * n[1] + c0[1]) * n[0] + x;
+        const CellIn<false> in(r, jinv, cells, c, RkArgs{});
+        double dF[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          Fm2[v] = sf[w][v][lane];
-          Fm1[v] = sf[w][v][lane + 1];
-          F0[v] = sf[w][v][lane + 2];
-          Fp1[v] = sf[w][v][lane + 3];
+          const double* f = &sf[w][v][lane];
+          dF[v] = (f[0] - 27.0 * f[1] + 27.0 * f[2] - f[3]) * (1.0 / 24.0);
         }
-        visc_flux_sub(r, jinv, cells, ((int64_t)c0[2] * n[1] + c0[1]) * n[0] + x, Fm2, Fm1, F0, Fp1);
+        in.finish(r, cells, c, dF, RkArgs{});
       }
     }
     __syncthreads();
   }
 }
 
-// Chunk of the march kernels: 32 cells, halved (down to 8) while the grid
-// gives fewer than 128 k threads.
-int visc_chunk(const int n[3], int d) {
-  const int o = d == 1 ? 2 : 1;
-  int chunk = 32;
-  while (chunk > 8 && (int64_t)n[0] * n[o] * ((n[d] + chunk - 1) / chunk) < (int64_t)1 << 17) chunk /= 2;
-  return chunk;
+// One direction of the blocks' fused viscous passes: i rows, j and k marches,
+// each subtracting its differences from r; the k march applies the RK3 stage to
+// the blocks' states instead of storing the finished residual where they carry
+// one (all or none).
+void visc_launch(const std::vector<ViscBlk>& v, int d, const Gas<double>& gas, hipStream_t stream) {
+  if (v.empty()) return;
+  if (d == 0) {
+    for_batches(
+        v, [](const ViscBlk& b) { return ((int64_t)b.n[1] * b.n[2] * ((b.n[0] + 63) / 64) + 3) / 4; },
+        [&](const Batch<ViscBlk>& B, int count, int64_t wgs) {
+          hipLaunchKernelGGL(k_c4_visc_rows, dim3((unsigned)std::min<int64_t>(wgs, 1 << 16), count), dim3(256), 0,
+                             stream, B, gas);
+        });
+    return;
+  }
+  const int ch = march_chunk(v, d);
+  const bool rk = d == 2 && v[0].K.q;
+  for_batches(
+      v, [&](const ViscBlk& b) { return d == 1 ? MarchAt<1>::items(b.n, ch) : MarchAt<2>::items(b.n, ch); },
+      [&](const Batch<ViscBlk>& B, int count, int64_t wgs) {
+        const dim3 g((unsigned)std::min<int64_t>(wgs, 1 << 16), count);
+        if (d == 1) hipLaunchKernelGGL((k_c4_visc_march<1, false>), g, dim3(256), 0, stream, B, ch, gas);
+        else if (rk) hipLaunchKernelGGL((k_c4_visc_march<2, true>), g, dim3(256), 0, stream, B, ch, gas);
+        else hipLaunchKernelGGL((k_c4_visc_march<2, false>), g, dim3(256), 0, stream, B, ch, gas);
+      });
 }
 
-// The fused viscous passes of one block (lines built by the caller): i rows,
-// then the j and k marches, each subtracting its differences from r; with
-// rk (not NULL) the k march applies the RK3 stage to the block's state
-// instead of storing the finished residual.
-void visc_fused_launch(const Line* PG, const Line* FM, const Line* S, double* r, const double* jinv, const int n[3],
-                       const Gas<double>& gas, hipStream_t stream, const RkArgs* rk = nullptr) {
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int64_t rows = (int64_t)n[1] * n[2] * ((n[0] + 63) / 64);
-  const int grows = (int)std::min<int64_t>((rows + 3) / 4, 1 << 16);
-  hipLaunchKernelGGL(k_c4_visc_rows, dim3(grows), dim3(256), 0, stream, PG[0], FM[0], S[0], r, jinv, D, gas);
-  const int c1 = visc_chunk(n, 1), c2 = visc_chunk(n, 2);
-  const int64_t t1 = (int64_t)n[0] * n[2] * ((n[1] + c1 - 1) / c1), t2 = (int64_t)n[0] * n[1] * ((n[2] + c2 - 1) / c2);
-  const RkArgs none{};
-  hipLaunchKernelGGL((k_c4_visc_march<1, false>), dim3(grid_for(t1)), dim3(256), 0, stream, PG[1], FM[1], S[1], r, jinv,
-                     D, c1, gas, none);
-  if (rk)
-    hipLaunchKernelGGL((k_c4_visc_march<2, true>), dim3(grid_for(t2)), dim3(256), 0, stream, PG[2], FM[2], S[2], r,
-                       jinv, D, c2, gas, *rk);
-  else
-    hipLaunchKernelGGL((k_c4_visc_march<2, false>), dim3(grid_for(t2)), dim3(256), 0, stream, PG[2], FM[2], S[2], r,
-                       jinv, D, c2, gas, none);
+void face_metrics_launch(const std::vector<MetBlk>& v, int d, hipStream_t stream) {
+  for_batches(
+      v, [](const MetBlk& b) { return (int64_t)b.n[0] * b.n[1] * b.n[2]; },
+      [&](const Batch<MetBlk>& B, int count, int64_t cells) {
+        hipLaunchKernelGGL(k_c4_face_metrics, dim3(grid_for(cells), count), dim3(256), 0, stream, B, d);
+      });
+}
+
+bool rk_fused(int nblk, const int32_t* dims, const char* skip) {
+  std::vector<Dims3> v;
+  for (int b = 0; b < nblk; ++b)
+    if (!skip || !skip[b]) v.push_back(Dims3{{dims[3 * b], dims[3 * b + 1], dims[3 * b + 2]}});
+  return march_chunk(v, 2) >= 32;
 }
 
 // A periodic block's lines: every neighbour the block itself.
@@ -2176,12 +2416,11 @@ void c4_face_metrics_curv(const double* s_dev, const double* jinv_dev, double* s
                           hipStream_t stream) {
   const int64_t cells = (int64_t)n[0] * n[1] * n[2];
   const Cells3 C{{n[0], n[1], n[2]}};
-  const Dims3 D{{n[0], n[1], n[2]}};
-  const int gr = grid_for(cells);
-  hipLaunchKernelGGL(k_c4_cell_metrics, dim3(gr), dim3(256), 0, stream, s_dev, sc_tmp, C);
+  hipLaunchKernelGGL(k_c4_cell_metrics, dim3(grid_for(cells)), dim3(256), 0, stream, s_dev, sc_tmp, C);
   for (int d = 0; d < 3; ++d)
-    hipLaunchKernelGGL(k_c4_face_metrics, dim3(gr), dim3(256), 0, stream, self_line(sc_tmp, cells, n[d]),
-                       self_line(jinv_dev, cells, n[d]), fm, D, d);
+    face_metrics_launch({MetBlk{self_line(sc_tmp, cells, n[d]), self_line(jinv_dev, cells, n[d]), fm,
+                                {n[0], n[1], n[2]}}},
+                        d, stream);
 }
 
 // The curvilinear viscous terms of a periodic block added into r (work: phi
@@ -2192,15 +2431,13 @@ void c4_viscous_curv_core(const double* q_dev, const double* s_dev, const double
   const int64_t cells = (int64_t)n[0] * n[1] * n[2];
   double* phi = work;
   double* g = phi + 4 * cells;
-  Line PG[3], FM[3], S[3];
-  for (int d = 0; d < 3; ++d) {
-    PG[d] = self_line(work, cells, n[d]);
-    FM[d] = self_line(fm, cells, n[d]);
-    S[d] = self_line(s_dev, cells, n[d]);
-  }
-  phi_grads_i_launch(self_line(q_dev, cells, n[0]), phi, g, n, gas.gm1, stream);
-  grads_jk_launch(PG, g, n, stream);
-  visc_fused_launch(PG, FM, S, r_dev, jinv_dev, n, gas, stream, rk);
+  phi_grads_i_launch({PhiBlk{self_line(q_dev, cells, n[0]), phi, g, {n[0], n[1], n[2]}}}, gas.gm1, stream);
+  for (int d = 1; d < 3; ++d)
+    grads_launch({PhiBlk{self_line(phi, cells, n[d]), phi, g, {n[0], n[1], n[2]}}}, d, stream);
+  for (int d = 0; d < 3; ++d)
+    visc_launch({ViscBlk{self_line(work, cells, n[d]), self_line(fm, cells, n[d]), self_line(s_dev, cells, n[d]), r_dev,
+                         jinv_dev, {n[0], n[1], n[2]}, rk ? *rk : RkArgs{}}},
+                d, gas, stream);
 }
 
 }  // namespace cfd
@@ -2220,13 +2457,6 @@ std::vector<int64_t> field_offsets(int32_t nblk, const int32_t* dims, int per) {
   return off;
 }
 
-// The line along d around block b over per-block arrays.
-Line block_line(int b, int d, const int32_t* dims, const int32_t* nbr, const double* const* bases) {
-  const int lo = nbr[6 * b + 2 * d], hi = nbr[6 * b + 2 * d + 1];
-  return Line{bases[b], bases[lo], bases[hi], block_cells(dims, b), block_cells(dims, lo), block_cells(dims, hi),
-              dims[3 * lo + d], dims[3 * hi + d]};
-}
-
 // Face metrics of blocks joined face to face into FM (21 doubles per cell of
 // every block), once per grid; W (16 doubles per cell of every block) holds
 // the cell metrics meanwhile.
@@ -2235,20 +2465,23 @@ void c4_face_metrics_blocks(int32_t nblk, const int32_t* dims, const int32_t* nb
   const std::vector<int64_t> off = field_offsets(nblk, dims, VW_FIELDS), offm = field_offsets(nblk, dims, FM_FIELDS);
   std::vector<const double*> sc(nblk);
   for (int b = 0; b < nblk; ++b) sc[b] = W + off[b];
-  for (int b = 0; b < nblk; ++b) {
-    const int64_t cb = block_cells(dims, b);
-    const Dims3 D{{dims[3 * b], dims[3 * b + 1], dims[3 * b + 2]}};
-    for (int t = 0; t < 3; ++t)
-      hipLaunchKernelGGL(k_c4_cell_metrics_line, dim3(grid_for(cb)), dim3(256), 0, stream,
-                         block_line(b, t, dims, nbr, s_dev), W + off[b], D, t);
+  auto blk = [&](int b, int d, const double* const* in, double* out) {
+    const int32_t* n = dims + 3 * b;
+    return MetBlk{block_line(b, d, dims, nbr, in), block_line(b, d, dims, nbr, jinv_dev), out, {n[0], n[1], n[2]}};
+  };
+  for (int t = 0; t < 3; ++t) {
+    std::vector<MetBlk> v;
+    for (int b = 0; b < nblk; ++b) v.push_back(blk(b, t, s_dev, W + off[b]));
+    for_batches(
+        v, [](const MetBlk& b) { return (int64_t)b.n[0] * b.n[1] * b.n[2]; },
+        [&](const Batch<MetBlk>& B, int count, int64_t cells) {
+          hipLaunchKernelGGL(k_c4_cell_metrics_line, dim3(grid_for(cells), count), dim3(256), 0, stream, B, t);
+        });
   }
-  for (int b = 0; b < nblk; ++b) {
-    const int64_t cb = block_cells(dims, b);
-    const Dims3 D{{dims[3 * b], dims[3 * b + 1], dims[3 * b + 2]}};
-    for (int d = 0; d < 3; ++d)
-      hipLaunchKernelGGL(k_c4_face_metrics, dim3(grid_for(cb)), dim3(256), 0, stream,
-                         block_line(b, d, dims, nbr, sc.data()), block_line(b, d, dims, nbr, jinv_dev), FM + offm[b],
-                         D, d);
+  for (int d = 0; d < 3; ++d) {
+    std::vector<MetBlk> v;
+    for (int b = 0; b < nblk; ++b) v.push_back(blk(b, d, sc.data(), FM + offm[b]));
+    face_metrics_launch(v, d, stream);
   }
 }
 
@@ -2265,26 +2498,27 @@ void c4_viscous_blocks_launch(int32_t nblk, const int32_t* dims, const int32_t* 
     wb[b] = W + off[b];
     fb[b] = FM + offm[b];
   }
-  for (int b = 0; b < nblk; ++b) {
-    const int64_t cb = block_cells(dims, b);
-    phi_grads_i_launch(block_line(b, 0, dims, nbr, q_dev), W + off[b], W + off[b] + VW_G * cb, dims + 3 * b, gas.gm1,
-                       stream);
-  }
-  for (int b = 0; b < nblk; ++b) {
-    const int64_t cb = block_cells(dims, b);
-    const Line P[3] = {block_line(b, 0, dims, nbr, wb.data()), block_line(b, 1, dims, nbr, wb.data()),
-                       block_line(b, 2, dims, nbr, wb.data())};
-    grads_jk_launch(P, W + off[b] + VW_G * cb, dims + 3 * b, stream);
-  }
-  for (int b = 0; b < nblk; ++b) {
-    if (skip && skip[b]) continue;   // its u, v, w, T and gradients still serve the neighbours' stencils
-    Line PG[3], FL[3], S[3];
-    for (int d = 0; d < 3; ++d) {
-      PG[d] = block_line(b, d, dims, nbr, wb.data());
-      FL[d] = block_line(b, d, dims, nbr, fb.data());
-      S[d] = block_line(b, d, dims, nbr, s_dev);
+  auto phi = [&](int d, const double* const* in) {
+    std::vector<PhiBlk> v;
+    for (int b = 0; b < nblk; ++b) {
+      const int32_t* n = dims + 3 * b;
+      v.push_back({block_line(b, d, dims, nbr, in), W + off[b], W + off[b] + VW_G * block_cells(dims, b),
+                   {n[0], n[1], n[2]}});
     }
-    visc_fused_launch(PG, FL, S, r_dev[b], jinv_dev[b], dims + 3 * b, gas, stream, rk && rk[b].q ? rk + b : nullptr);
+    return v;
+  };
+  phi_grads_i_launch(phi(0, q_dev), gas.gm1, stream);
+  for (int d = 1; d < 3; ++d) grads_launch(phi(d, wb.data()), d, stream);
+  for (int d = 0; d < 3; ++d) {
+    std::vector<ViscBlk> v;
+    for (int b = 0; b < nblk; ++b) {
+      if (skip && skip[b]) continue;   // its u, v, w, T and gradients still serve the neighbours' stencils
+      const int32_t* n = dims + 3 * b;
+      v.push_back({block_line(b, d, dims, nbr, wb.data()), block_line(b, d, dims, nbr, fb.data()),
+                   block_line(b, d, dims, nbr, s_dev), r_dev[b], jinv_dev[b], {n[0], n[1], n[2]},
+                   rk ? rk[b] : RkArgs{}});
+    }
+    visc_launch(v, d, gas, stream);
   }
 }
 
@@ -3065,6 +3299,7 @@ cfd_status ns_steps_blocks_impl(int32_t nblk, const int32_t* dims, const int32_t
     double* FM = base + off[nblk];      // the viscous face metrics, once per call
     if (viscous && nsteps > 0)
       cfd::c4_face_metrics_blocks(nblk, dims, nbr, s_dev, jinv_dev, static_cast<double*>(work_dev), FM, stream);
+    const bool fused = viscous && cfd::rk_fused(nblk, dims, ghost.data());
     for (int it = 0; it < nsteps; ++it)
       for (int st = 0; st < 3; ++st) {
         for (int c = 0; c < nclosures; ++c) {
@@ -3075,10 +3310,10 @@ cfd_status ns_steps_blocks_impl(int32_t nblk, const int32_t* dims, const int32_t
         }
         cfd::wcns5_blocks_residual_launch(nblk, dims, nbr, q_dev, s_dev, jinv_dev, R.data(), work_dev, gamma,
                                           entropy_fix, eps, stream, ghost.data());
-        // the last viscous pass of a large block applies the stage (K[b].q set)
+        // the last viscous pass of blocks that fill the chip applies the stage (K[b].q set)
         std::vector<cfd::RkArgs> K(nblk);
         for (int b = 0; b < nblk; ++b)
-          if (viscous && cfd::rk_fused(dims + 3 * b))
+          if (fused)
             K[b] = cfd::RkArgs{q_dev[b], qn[b], dt, a[st], bb[st], st == 0 ? 1 : 0};
         if (viscous)
           cfd::c4_viscous_blocks_launch(nblk, dims, nbr, q_dev, s_dev, jinv_dev, R.data(),
