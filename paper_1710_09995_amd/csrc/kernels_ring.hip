@@ -26,7 +26,20 @@
 // (shuffle) instead of through LDS; only the tile's edge i-faces and the
 // j-faces go through LDS.  Every face flux gets the same bits as in the
 // other stage kernels (same primitives, same expressions).
+//
+// With two waves a SIMD and barriers between them, what bounds it beside FP64
+// issue is the latency of loads that sit right before their use.  So: a face's
+// metrics are loaded together before its flux; W(k+2) and W(k+3) are loaded
+// before the k-face, without branches (columns and planes clamped to the ghost
+// layers; a load under a branch is waited for where the branch ends), the FP32
+// Euler variants, four waves a SIMD, excepted for W(k+2); and addresses are one
+// 32-bit column offset beside scalar bases.  64-bit vector addresses per field,
+// hoisted out of the plane loop, filled the registers and spilled: FP64
+// Navier-Stokes 62 to 8 (stage 1) and 0 (stage 2) dwords.  256 x 128 x 128 NS
+// 1577 -> 1500 us a step, 2 x 2 x (250 x 203 x 72) FP32 NS 5.07 -> 4.66 ms,
+// 128 x (48 x 24 x 24) Euler V-cycles 5.50 -> 5.19 ms; FP32 Euler as before.
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include "cfd_internal.hpp"
 #include "physics.hpp"
 #include "stage_common.hpp"
@@ -67,6 +80,7 @@ template <typename T, bool VISC, int MODE, int TI, int TJ>
 __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_ring(
     StageArgs A, const BlockDesc* __restrict__ blocks, const TileDesc* __restrict__ tiles, Gas<T> gas) {
   using LD = RingLds<T, VISC, TI, TJ>;
+  constexpr bool F64 = sizeof(T) == 8, EARLY = F64 || VISC;
   constexpr int NT = TI * TJ;
   constexpr int WI = LD::WI, WJ = LD::WJ;
   __shared__ __attribute__((aligned(16))) char smem[MODE == 3 ? LD::TOTAL_DT : LD::TOTAL];
@@ -101,11 +115,13 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
 
   for (int tile = blockIdx.x; tile < A.ntiles; tile += gridDim.x) {
     const TileDesc td = tiles[tile];
-    const BlockDesc B = blocks[td.blk];
+    BlockDesc B = blocks[td.blk];
     const int ni = B.n[0], nj = B.n[1], nk = B.n[2];
     const int i0 = td.i0, j0 = td.j0;
     int k0, kend;
     tile_run(nk, A.tile_k, td.kp, k0, kend);
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    kend = __builtin_amdgcn_readfirstlane(kend);
     const int i = i0 + tx, j = j0 + ty;
     const bool act = i < ni && j < nj;
     const bool fi_ok = i <= ni && j < nj;
@@ -118,23 +134,48 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
     const double* qb = A.qs + B.qoff;
     const double* mb = A.met + B.moff;
     const double* vb = VISC ? A.vmet + B.voff : nullptr;
-    const int64_t sj = B.sj, sk = B.sk, sv = B.sv;
+    const int64_t sj = B.sj, sk = B.sk;
+    int64_t sv = B.sv;
     auto off = [&](int ii, int jj, int kk) -> int64_t {
       return (int64_t)(kk + NG) * sk + (int64_t)(jj + NG) * sj + (ii + NG);
     };
-    // W(kk) with halo 2 into ring slot `slot`; a fixed trip count, unrolled,
+    // a column's byte offset, new to the compiler at each use: known to be the
+    // same for every plane it would be added to each field's base outside the loop
+    auto fresh = [](uint32_t c) {
+      asm volatile("" : "+v"(c));
+      return c;
+    };
+    auto col = [&](int ii, int jj) { return fresh((uint32_t)((jj + NG) * (int)sj + (ii + NG)) * 8u); };
+    auto plane = [&](int kk) { return (int64_t)(__builtin_amdgcn_readfirstlane(kk) + NG) * sk; };
+    const uint32_t own0 = col(min(i, ni + 1), min(j, nj + 1));
+    // W(kk) with halo 2 into ring slot `slot`: a fixed trip count, unrolled,
     // so that all of a thread's loads are in flight together
-    auto fill = [&](int slot, int kk) {
-      constexpr int NS = (WJ * WI + NT - 1) / NT;
+    constexpr int NS = (WJ * WI + NT - 1) / NT;
+    struct Raw {
+      double q[5];
+    };
+    using Cell3 = std::conditional_t<F64, Raw, Prim<T>>;   // W(k + 2) of the column: converted late where that
+                                                           // takes no more registers
+    auto load_raw = [&](CellAt c, Raw& r) { load_fields<5>(qb, sv, c, r.q); };
+    auto prim_of = [&](const auto& r) {
+      if constexpr (std::is_same_v<std::decay_t<decltype(r)>, Raw>)
+        return to_prim<T>(r.q[0], r.q[1], r.q[2], r.q[3], r.q[4], gas.gm1);
+      else return r;
+    };
+    auto fill_load = [&](int kk, Raw raw[NS]) {
+#pragma unroll
+      for (int it = 0; it < NS; ++it) {
+        const int s = min(tid + it * NT, WJ * WI - 1);
+        const int pj = s / WI, pi = s - (s / WI) * WI;
+        load_raw(CellAt{plane(kk), col(min(i0 - 2 + pi, ni + 1), min(j0 - 2 + pj, nj + 1))}, raw[it]);
+      }
+    };
+    auto fill_store = [&](int slot, const Raw raw[NS]) {
 #pragma unroll
       for (int it = 0; it < NS; ++it) {
         const int s = tid + it * NT;
         if (s >= WJ * WI) break;
-        const int pj = s / WI, pi = s - (s / WI) * WI;
-        const int gi = i0 - 2 + pi, gj = j0 - 2 + pj;
-        Prim<T> w;
-        w.r = T(1); w.u = T(0); w.v = T(0); w.w = T(0); w.p = T(1);
-        if (gi <= ni + 1 && gj <= nj + 1) w = ld_prim<T>(qb, off(gi, gj, kk), sv, gas.gm1);
+        const Prim<T> w = prim_of(raw[it]);
         W(slot, 0, s) = w.r;
         W(slot, 1, s) = w.u;
         W(slot, 2, s) = w.v;
@@ -143,14 +184,22 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
         if (VISC) W(slot, 5, s) = temp_of(w);
       }
     };
+    auto fill = [&](int slot, int kk) {
+      Raw raw[NS];
+      fill_load(kk, raw);
+      fill_store(slot, raw);
+    };
 
     // lower k-face of the tile from global memory; queue cell W(k0+2)
     double Fklo[5] = {0, 0, 0, 0, 0};
-    Prim<T> q3{};
+    Cell3 q3{};
     if (act) {
       const int64_t c0 = off(i, j, k0);
       face_flux_global<T, VISC>(qb, mb, vb, B, c0, 2, gas, Fklo);
-      q3 = ld_prim<T>(qb, c0 + 2 * sk, sv, gas.gm1);
+      Raw r;
+      load_raw(CellAt{plane(k0 + 2), own0}, r);
+      if constexpr (F64) q3 = r;
+      else q3 = prim_of(r);
     }
     __syncthreads();   // the previous tile's LDS users are done
     int sm = 0, s0 = 1, sp = 2;   // ring slots of W(k-1), W(k), W(k+1)
@@ -160,22 +209,26 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
     __syncthreads();
 
     for (int k = k0; k < kend; ++k) {
+      const uint32_t own = fresh(own0);
+      // the field stride anew every plane: its multiples are cheap scalar
+      // work, kept across the planes they filled the scalar registers
+      asm volatile("" : "+s"(sv));
+      B.sv = sv;
       // inputs of this plane's cell update, loaded before the face work
       CellIn cin;
-      if (act) load_cell<MODE>(A, B, off(i, j, k), cin);
+      load_cell<MODE>(A, B, CellAt{plane(k), own}, cin);
       // ---- A. faces of plane k
       // lower face, along direction d = 0 (i) or 1 (j), of cell (i0+ci, j0+rj):
       // flux F, area vector S.  One expression for both directions, so that
       // the tile-edge faces of either run in the same lanes.
-      auto face = [&](int d, int ci, int rj, double F[5], double S[3]) {
+      auto metrics = [&](int d, auto c, double S[3], double St[2][3], double& vf) {
+        load_fields<3>(mb + (int64_t)(3 * d) * sv, sv, c, S);
+        if (VISC) face_vmetrics(vb, sv, c, d, St, vf);
+      };
+      auto face = [&](int d, int ci, int rj, const double S[3], const double St[2][3], double vf, double F[5]) {
         const int p = (rj + 2) * WI + ci + 2;             // the cell above the face
         const int st = d == 0 ? 1 : WI, tr = d == 0 ? WI : 1;   // along the face normal, across
-        const int64_t c = off(i0 + ci, j0 + rj, k);
-        const double* ms = mb + (int64_t)(3 * d) * sv + c;
-        const double sx = ms[0], sy = ms[sv], sz = ms[2 * sv];
-        S[0] = sx;
-        S[1] = sy;
-        S[2] = sz;
+        const double sx = S[0], sy = S[1], sz = S[2];
         T f[5], n[3];
         const double area = face_inviscid<T>(wprim(s0, p - 2 * st), wprim(s0, p - st), wprim(s0, p),
                                              wprim(s0, p + st), sx, sy, sz, gas, f, n);
@@ -187,8 +240,6 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
           tdiff(a, b, e, g, d1);
           wphi(sp, p - st, a); wphi(sp, p, b); wphi(sm, p - st, e); wphi(sm, p, g);
           tdiff(a, b, e, g, d2);
-          double St[2][3], vf;
-          face_vmetrics(vb, sv, c, d, St, vf);
           face_viscous<T>(pl, pr, sx, sy, sz, n, d1, d2, St, vf, gas, f);
         }
         scale_flux_f64(f, area, F);
@@ -199,36 +250,50 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
           for (int x = 0; x < 3; ++x) sSj[(x * (TJ + 1) + rj) * TI + ci] = S[x];
       };
       double Fi[5] = {0, 0, 0, 0, 0};
+      double S[3], St[2][3], vf;
       if (fi_ok) {
-        double Si[3];
-        face(0, tx, ty, Fi, Si);
+        metrics(0, CellAt{plane(k), own}, S, St, vf);
+        CFD_FACE_FENCE_RING();
+        face(0, tx, ty, S, St, vf, Fi);
       }
       CFD_FACE_FENCE_RING();
       if (fj_ok) {
-        double Fj[5], Sj[3];
-        face(1, tx, ty, Fj, Sj);
-        keep_j(tx, ty, Fj, Sj);
+        metrics(1, CellAt{plane(k), own}, S, St, vf);
+        CFD_FACE_FENCE_RING();
+        double Fj[5];
+        face(1, tx, ty, S, St, vf, Fj);
+        keep_j(tx, ty, Fj, S);
       }
       CFD_FACE_FENCE_RING();
       if (e_ok) {
-        double Fe[5], Se[3];
-        face(e_j ? 1 : 0, e_ci, e_rj, Fe, Se);
+        double Fe[5];
+        metrics(e_j ? 1 : 0, off(i0 + e_ci, j0 + e_rj, k), S, St, vf);
+        face(e_j ? 1 : 0, e_ci, e_rj, S, St, vf, Fe);
         if (e_j) {
-          keep_j(e_ci, TJ, Fe, Se);
+          keep_j(e_ci, TJ, Fe, S);
         } else {
           for (int q = 0; q < 5; ++q) sFe[q * TJ + e_rj] = Fe[q];
           if (MODE == 3)
-            for (int x = 0; x < 3; ++x) sSe[x * TJ + e_rj] = Se[x];
+            for (int x = 0; x < 3; ++x) sSe[x * TJ + e_rj] = S[x];
         }
       }
+      CFD_FACE_FENCE_RING();
+      const bool more = k + 1 < kend;
+      Raw raw[NS], r3;
+      metrics(2, CellAt{plane(k + 1), own}, S, St, vf);
+      if (EARLY) {
+        CFD_FACE_FENCE_RING();
+        fill_load(k + 2, raw);
+      }
+      load_raw(CellAt{plane(min(k + 3, nk + 1)), own}, r3);
       CFD_FACE_FENCE_RING();
       double Fku[5] = {0, 0, 0, 0, 0};
       if (act) {   // upper k-face between (i, j, k) and (i, j, k+1)
         const int p = (ty + 2) * WI + tx + 2;
-        const int64_t cu = off(i, j, k) + sk;
-        const double sx = mb[6 * sv + cu], sy = mb[7 * sv + cu], sz = mb[8 * sv + cu];
+        const double sx = S[0], sy = S[1], sz = S[2];
         T f[5], n[3];
-        const double area = face_inviscid<T>(wprim(sm, p), wprim(s0, p), wprim(sp, p), q3, sx, sy, sz, gas, f, n);
+        const double area =
+            face_inviscid<T>(wprim(sm, p), wprim(s0, p), wprim(sp, p), prim_of(q3), sx, sy, sz, gas, f, n);
         if (VISC) {
           T pl[4], pr[4], d1[4], d2[4], a[4], b[4], e[4], g[4];
           wphi(s0, p, pl);
@@ -237,8 +302,6 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
           tdiff(a, b, e, g, d1);
           wphi(s0, p + WI, a); wphi(sp, p + WI, b); wphi(s0, p - WI, e); wphi(sp, p - WI, g);
           tdiff(a, b, e, g, d2);
-          double St[2][3], vf;
-          face_vmetrics(vb, sv, cu, 2, St, vf);
           face_viscous<T>(pl, pr, sx, sy, sz, n, d1, d2, St, vf, gas, f);
         }
         scale_flux_f64(f, area, Fku);
@@ -249,9 +312,9 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
       __syncthreads();   // j-face and edge fluxes stored; every read of W(k-1) done
 
       // ---- B. cell update of plane k; fill W(k+2) over W(k-1); queue W(k+3)
-      const bool more = k + 1 < kend;
-      Prim<T> q3n = q3;
-      if (act && more) q3n = ld_prim<T>(qb, off(i, j, k) + 3 * sk, sv, gas.gm1);
+      Cell3 q3n = q3;
+      if constexpr (F64) q3n = r3;
+      else q3n = prim_of(r3);
       // mode 3: the cell's face-averaged area vectors b[d] = (S_d(c) + S_d(c + e_d)) / 2.
       // Upper faces from this plane's face work: S_i of the next lane
       // (shuffle; the tile-edge face from LDS for lane 63), S_j of the next
@@ -261,13 +324,11 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
       if (MODE == 3) {
         double Si[3] = {0, 0, 0}, Sk[3] = {0, 0, 0}, Sku[3] = {0, 0, 0};
         if (fi_ok) {
-          const int64_t c = off(i, j, k);
-          for (int x = 0; x < 3; ++x) Si[x] = mb[x * sv + c];
+          load_fields<3>(mb, sv, CellAt{plane(k), own}, Si);
         }
         if (act) {
-          const int64_t c = off(i, j, k);
-          for (int x = 0; x < 3; ++x) Sk[x] = mb[(6 + x) * sv + c];
-          for (int x = 0; x < 3; ++x) Sku[x] = mb[(6 + x) * sv + c + sk];
+          load_fields<3>(mb + 6 * sv, sv, CellAt{plane(k), own}, Sk);
+          load_fields<3>(mb + 6 * sv, sv, CellAt{plane(k + 1), own}, Sku);
         }
         double Siu[3];
         for (int x = 0; x < 3; ++x) Siu[x] = __shfl_down(Si[x], 1, 64);
@@ -279,7 +340,10 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
             bdt[2][x] = 0.5 * (Sk[x] + Sku[x]);
           }
       }
-      if (more) fill(sm, k + 2);
+      if (more) {
+        if constexpr (EARLY) fill_store(sm, raw);
+        else fill(sm, k + 2);
+      }
       if (act) {
         double Di[5], Dj[5], Dk[5];
         for (int q = 0; q < 5; ++q) {
@@ -289,7 +353,7 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
           Dk[q] = Fku[q] - Fklo[q];
         }
         double Rc[5], Qo[5];
-        update_cell<MODE>(A, B, off(i, j, k), Di, Dj, Dk, cin, Rc, Qo);
+        update_cell<MODE>(A, B, CellAt{plane(k), own}, Di, Dj, Dk, cin, Rc, Qo);
         if (MODE == 1) {
 #pragma unroll
           for (int q = 0; q < 5; ++q) {

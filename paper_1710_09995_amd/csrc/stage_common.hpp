@@ -67,14 +67,67 @@ __device__ __forceinline__ void visc_metrics(const double* __restrict__ mb, int6
   vf = 0.5 * (mb[9 * sv + cl] + mb[9 * sv + c]);
 }
 
+// A cell of a block's fields: plane, one value for the workgroup, counts whole
+// k-planes from the field's start; col is the byte offset of the cell's column
+// within a plane, 32 bits wide (a plane of 2^29 cells would put 20 fields of at
+// least five planes at 429 GB).  A load of any field then needs one vector
+// register for its address; the rest stays in scalar ones.
+struct CellAt {
+  int64_t plane;
+  uint32_t col;
+};
+
+// N consecutive fields (stride sv) of a cell, read or written.  The scalar
+// address steps from field to field; the empty asm keeps it one pair of
+// registers, where the compiler would else keep a product or a vector address
+// per field live across the planes.
+__device__ __forceinline__ uint64_t scalar64(uint64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return (uint64_t)hi << 32 | lo;
+}
+template <int N>
+__device__ __forceinline__ void load_fields(const double* base, int64_t sv, CellAt c, double* v) {
+  const double* p = reinterpret_cast<const double*>(scalar64(reinterpret_cast<uint64_t>(base + c.plane)));
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    v[q] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + c.col);
+    p += sv;
+    asm("" : "+s"(p));
+  }
+}
+template <int N>
+__device__ __forceinline__ void load_fields(const double* base, int64_t sv, int64_t c, double* v) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) v[q] = base[q * sv + c];
+}
+template <int N>
+__device__ __forceinline__ void store_fields(double* base, int64_t sv, CellAt c, const double* v) {
+  double* p = reinterpret_cast<double*>(scalar64(reinterpret_cast<uint64_t>(base + c.plane)));
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    *reinterpret_cast<double*>(reinterpret_cast<char*>(p) + c.col) = v[q];
+    p += sv;
+    asm("" : "+s"(p));
+  }
+}
+template <int N>
+__device__ __forceinline__ void store_fields(double* base, int64_t sv, int64_t c, const double* v) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) base[q * sv + c] = v[q];
+}
+
 // Viscous metric terms of the lower d-face of cell c, from the arena vb.
-__device__ __forceinline__ void face_vmetrics(const double* __restrict__ vb, int64_t sv, int64_t c, int d,
-                                              double St[2][3], double& vf) {
+template <class At>
+__device__ __forceinline__ void face_vmetrics(const double* __restrict__ vb, int64_t sv, At c, int d, double St[2][3],
+                                              double& vf) {
+  double m[7];
+  load_fields<7>(vb + (int64_t)(7 * d) * sv, sv, c, m);
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int x = 0; x < 3; ++x) St[u][x] = vb[(int64_t)(7 * d + 3 * u + x) * sv + c];
-  vf = vb[(int64_t)(7 * d + 6) * sv + c];
+    for (int x = 0; x < 3; ++x) St[u][x] = m[3 * u + x];
+  vf = m[6];
 }
 
 // Inviscid part of one face: MUSCL states from cells c-2, c-1 (L), c (R),
@@ -247,26 +300,22 @@ struct CellIn {
 // as far as the compiler knows, so a load placed after a store would wait for
 // that store (and, through the shared memory counter, for every store before
 // it).  A kernel may load them early, before its face work, to hide latency.
-template <int MODE>
-__device__ __forceinline__ void load_cell(const StageArgs& A, const BlockDesc& B, int64_t c, CellIn& in) {
-  in.vol = A.met[B.moff + 9 * B.sv + c];
+template <int MODE, class At>
+__device__ __forceinline__ void load_cell(const StageArgs& A, const BlockDesc& B, At c, CellIn& in) {
+  load_fields<1>(A.met + B.moff + 9 * B.sv, B.sv, c, &in.vol);
   if (MODE == 0) return;
-  in.dt = A.local_dt ? A.dt[B.soff + c] : A.dt[0];
-  const double* qb = A.qs + B.qoff;
-#pragma unroll
-  for (int q = 0; q < 5; ++q) in.qv[q] = qb[q * B.sv + c];
-  if (MODE >= 2) {
-#pragma unroll
-    for (int q = 0; q < 5; ++q) in.qn[q] = A.qn[B.qoff + q * B.sv + c];
-  }
+  if (A.local_dt) load_fields<1>(A.dt + B.soff, B.sv, c, &in.dt);
+  else in.dt = A.dt[0];
+  load_fields<5>(A.qs + B.qoff, B.sv, c, in.qv);
+  if (MODE >= 2) load_fields<5>(A.qn + B.qoff, B.sv, c, in.qn);
 }
 
 // R = ((Di + Dj) + Dk) / V, then write R (mode 0) or the stage update
 // (modes 1-3; mode 1 also writes R for the norms if A.rout is set), less
 // (A.fb dt) force when a multigrid level's forcing is given.  R is returned
 // in Rc, the written state in Qo (modes 1-3).
-template <int MODE>
-__device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc& B, int64_t c, const double Di[5],
+template <int MODE, class At>
+__device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc& B, At c, const double Di[5],
                                             const double Dj[5], const double Dk[5], const CellIn& in,
                                             double Rc[5] = nullptr, double Qo[5] = nullptr,
                                             const double* force = nullptr) {
@@ -275,31 +324,22 @@ __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc&
 #pragma unroll
   for (int q = 0; q < 5; ++q) R[q] = ((Di[q] + Dj[q]) + Dk[q]) * ivol;
   if (MODE == 0) {
-#pragma unroll
-    for (int q = 0; q < 5; ++q) A.out[B.qoff + q * B.sv + c] = R[q];
-  } else if (MODE == 1) {
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      double o = in.qv[q] - in.dt * R[q];
-      if (force) {
-        const double h = A.fb * in.dt;
-        o = o - h * force[B.qoff + q * B.sv + c];
-      }
-      A.out[B.qoff + q * B.sv + c] = o;
-      if (A.rout) A.rout[B.qoff + q * B.sv + c] = R[q];
-      if (Qo) Qo[q] = o;
-    }
+    store_fields<5>(A.out + B.qoff, B.sv, c, R);
   } else {
+    double o[5], F[5];
+    if (force) load_fields<5>(force + B.qoff, B.sv, c, F);
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
-      double o = A.a * in.qn[q] + A.b * (in.qv[q] - in.dt * R[q]);
+      if (MODE == 1) o[q] = in.qv[q] - in.dt * R[q];
+      else o[q] = A.a * in.qn[q] + A.b * (in.qv[q] - in.dt * R[q]);
       if (force) {
         const double h = A.fb * in.dt;
-        o = o - h * force[B.qoff + q * B.sv + c];
+        o[q] = o[q] - h * F[q];
       }
-      A.out[B.qoff + q * B.sv + c] = o;
-      if (Qo) Qo[q] = o;
+      if (Qo) Qo[q] = o[q];
     }
+    store_fields<5>(A.out + B.qoff, B.sv, c, o);
+    if (MODE == 1 && A.rout) store_fields<5>(A.rout + B.qoff, B.sv, c, R);
   }
   if (Rc) {
 #pragma unroll
