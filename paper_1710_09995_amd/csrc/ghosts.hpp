@@ -42,7 +42,8 @@ __device__ __forceinline__ void wall_state(int kind, const double w[NV], double 
 // apart, so a thread per (point, layer) puts a row's layers on adjacent lanes
 // and halves the memory segments each access touches.
 // With delta set, q is an update (the implicit step's dQ): connections copy it
-// as they copy the state, and the ghost cells of physical patches get zero.
+// as they copy the state, and the ghost cells of physical patches get zero (1) or
+// hold it already (2).
 __device__ __forceinline__ void ghost_fill_point(double* __restrict__ q, const double* __restrict__ met,
                                                  const BlockDesc* __restrict__ blocks, const PatchDesc& P, int t,
                                                  const StepParams& SP, int delta) {
@@ -88,6 +89,7 @@ __device__ __forceinline__ void ghost_fill_point(double* __restrict__ q, const d
     return;
   }
   if (delta) {
+    if (delta == 2) return;   // zero already
     if (per != 1) {     // this thread's layer only
       const int m = 1 + t % per;
       const int64_t od = pos3(d, side == 0 ? -m : n - 1 + m, p1, p2, B.sj, B.sk);

@@ -14,6 +14,7 @@ struct ImplicitArgs {
   const double* dq_in;   // current iterate (ghost cells filled)
   double* dq_out;        // next iterate
   const double* dt;      // global step (1 double) when !local
+  double* rows;          // partials: the face kernel's workgroups, then the diagonal kernel's
   int local;
   int viscous;
   double gamma, prandtl, mu_inf, s_star;
@@ -26,8 +27,8 @@ void launch_ifv_faces(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, 
                       const StepParams& P, int nwg, hipStream_t s);
 void launch_ifv_diag(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                      hipStream_t s);
-void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
-                      hipStream_t s);
+// kc: planes a march; items: workgroups of the block that has the most
+void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int items, hipStream_t s);
 void launch_ifv_apply(double* q, const double* dq, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                       hipStream_t s);
 

@@ -13,9 +13,10 @@
 //   MU   variables 0-2: mu of the lower d-face of every cell position (index
 //        0..n_d along d, so the last entry is the block's upper face), 3: the
 //        diagonal D, 4: the per-cell time step.
-// Every kernel walks the interior cells as the grid's 64-cell row chunks
-// (chunks.hpp), one launch over all blocks, coalesced along i.
+// Every kernel but the sweep walks the interior cells as the grid's 64-cell row
+// chunks (chunks.hpp), one launch over all blocks, coalesced along i.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include "cfd_internal.hpp"
 #include "physics.hpp"
 #include "stage_common.hpp"
@@ -66,9 +67,14 @@ __device__ __forceinline__ void load5(const double* __restrict__ a, int64_t o, i
 }
 
 // mu of the three lower faces of every interior cell (and of the block's upper
-// faces, by the last cell along each direction); the per-cell time step.
+// faces, by the last cell along each direction); the per-cell time step, with a
+// workgroup's row of partials as k_dt writes it: minimum step (slot 12), sum V Q
+// (5-9) and non-finite count of Q (11).  Here because Q and the metrics are read
+// anyway (a time-step pass of its own took 49 us at 192 x 96 x 96).
 __global__ void __launch_bounds__(256) k_ifv_faces(ImplicitArgs A, const BlockDesc* __restrict__ blocks, int nblk,
                                                    int64_t nchunks, StepParams P) {
+  double acc[NPART];
+  init_partials(acc);
   const int lane = threadIdx.x & 63;
   int64_t r0, r1;
   wave_rows(nchunks, r0, r1);
@@ -100,13 +106,24 @@ __global__ void __launch_bounds__(256) k_ifv_faces(ImplicitArgs A, const BlockDe
                                      mb[(3 * d + 2) * B.sv + cu], vc, mb[9 * B.sv + cu], A);
       }
     }
-    mub[4 * B.sv + c] = cell_dt(qc, mb, c, B.sv, B.sj, B.sk, P);
+    const double dtc = cell_dt(qc, mb, c, B.sv, B.sj, B.sk, P);
+    mub[4 * B.sv + c] = dtc;
+    acc[12] = fmin(acc[12], dtc);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      acc[5 + v] += vc * qc[v];
+      if (!finite(qc[v])) acc[11] += 1.0;
+    }
   }
+  wg_reduce_partials(acc, A.rows + (int64_t)blockIdx.x * NPART);
 }
 
-// D = V/dt + the six faces' mu; first iterate dQ = -V R / D.
+// D = V/dt + the six faces' mu; first iterate dQ = -V R / D; the partials of R as
+// k_norms writes them: sum R^2 (0-4), max |R_rho| (10), non-finite count (11).
 __global__ void __launch_bounds__(256) k_ifv_diag(ImplicitArgs A, const BlockDesc* __restrict__ blocks, int nblk,
                                                   int64_t nchunks) {
+  double acc[NPART];
+  init_partials(acc);
   const int lane = threadIdx.x & 63;
   int64_t r0, r1;
   wave_rows(nchunks, r0, r1);
@@ -131,75 +148,118 @@ __global__ void __launch_bounds__(256) k_ifv_diag(ImplicitArgs A, const BlockDes
     const double* rb = A.r + B.qoff;
     double* ob = A.dq_out + B.qoff;
 #pragma unroll
-    for (int v = 0; v < 5; ++v) ob[v * B.sv + c] = -vc * rb[v * B.sv + c] / D;
+    for (int v = 0; v < 5; ++v) {
+      const double rv = rb[v * B.sv + c];
+      ob[v * B.sv + c] = -vc * rv / D;
+      acc[v] += rv * rv;
+      if (!finite(rv)) acc[11] += 1.0;
+      if (v == 0) acc[10] = fmax(acc[10], fabs(rv));
+    }
   }
+  wg_reduce_partials(acc, A.rows + (int64_t)(gridDim.x + blockIdx.x) * NPART);
+}
+
+// A neighbour's share of the off-diagonal sum: sign dF / 2 - mu dQ, with
+// dF = F(Q + dQ) . S - F(Q) . S through the face between.
+__device__ __forceinline__ void neighbour(const double Q[5], const double dQ[5], const double S[3], double mu,
+                                          double half, double gm1, double o[5]) {
+  double Qp[5], F0[5], F1[5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) Qp[v] = Q[v] + dQ[v];
+  flux_dot(Qp, S[0], S[1], S[2], gm1, F1);
+  flux_dot(Q, S[0], S[1], S[2], gm1, F0);
+#pragma unroll
+  for (int v = 0; v < 5; ++v) o[v] = half * (F1[v] - F0[v]) - mu * dQ[v];
 }
 
 // One point-Jacobi sweep: dQ_out = (-V R - O(dQ_in)) / D, where over each
 // direction the upper face adds dF(c+e)/2 - mu dQ(c+e) and the lower face
-// -dF(c-e)/2 - mu dQ(c-e), dF(m) = F(Q_m + dQ_m) . S - F(Q_m) . S.
-__global__ void __launch_bounds__(256) k_ifv_sweep(ImplicitArgs A, const BlockDesc* __restrict__ blocks, int nblk,
-                                                   int64_t nchunks) {
-  const int lane = threadIdx.x & 63;
+// -dF(c-e)/2 - mu dQ(c-e).
+// Bound by memory: 34 doubles a cell.  A wave takes 64 cells of a row and
+// marches them over kc planes, its workgroup four rows side by side, so that Q,
+// dQ and the k-face of a plane are read once a march instead of by three
+// planes' waves that share no cache (row chunks in any order: 155 us a sweep at
+// 192 x 96 x 96; marching 142).  Three waves a SIMD: at four (128 registers) it
+// spills (the step 2.3 ms against 1.5).
+__global__ void __launch_bounds__(256, 3) k_ifv_sweep(ImplicitArgs A, const BlockDesc* __restrict__ blocks,
+                                                      int nblk, int kc) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const double gm1 = A.gamma - 1.0;
-  int64_t r0, r1;
-  wave_rows(nchunks, r0, r1);
-  ChunkWalk W;
-  if (r0 < r1) W.start(blocks, nblk, r0);
-  for (int64_t u = r0; u < r1; ++u) {
-    int i, j, k;
-    if (!W.cell(u, lane, i, j, k)) continue;
-    const BlockDesc& B = W.B;
-    const int64_t c = (int64_t)(k + NG) * B.sk + (int64_t)(j + NG) * B.sj + (i + NG);
+  for (int b = blockIdx.y; b < nblk; b += gridDim.y) {
+    const BlockDesc B = blocks[b];
+    const int nci = (B.n[0] + 63) >> 6, njg = (B.n[1] + 3) >> 2;
+    const int u = blockIdx.x;                     // i chunk fastest, then the row group, then the planes
+    const int i = u % nci * 64 + lane, j = u / nci % njg * 4 + w, k0 = __builtin_amdgcn_readfirstlane(u / nci / njg) * kc;
+    if (i >= B.n[0] || j >= B.n[1] || k0 >= B.n[2]) continue;
+    const int k1 = __builtin_amdgcn_readfirstlane(min(k0 + kc, B.n[2]));
     const double* qb = A.q + B.qoff;
     const double* mb = A.met + B.moff;
     const double* mub = A.mu + B.qoff;
     const double* db = A.dq_in + B.qoff;
-    double O[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const int64_t sv = B.sv;
+    const uint32_t col0 = (uint32_t)((j + NG) * (int)B.sj + (i + NG)) * 8u, sj8 = (uint32_t)B.sj * 8u;
+    auto cell = [&](int k, uint32_t col) { return CellAt{(int64_t)(k + NG) * B.sk, col}; };
+    double Qm[5], dm[5], Q0[5], d0[5], Sk[3], mk;
+    load_fields<5>(qb, sv, cell(k0 - 1, col0), Qm);
+    load_fields<5>(db, sv, cell(k0 - 1, col0), dm);
+    load_fields<5>(qb, sv, cell(k0, col0), Q0);
+    load_fields<5>(db, sv, cell(k0, col0), d0);
+    load_fields<3>(mb + 6 * sv, sv, cell(k0, col0), Sk);
+    load_fields<1>(mub + 2 * sv, sv, cell(k0, col0), &mk);
+#pragma unroll 1
+    for (int k = k0; k < k1; ++k) {
+      uint32_t col = col0;
+      asm volatile("" : "+v"(col));   // addresses formed here, not kept per field across the planes
+      const CellAt here = cell(k, col);
+      double Qp[5], dp[5], Su[3], mu, r[5], vc, D;
+      load_fields<5>(qb, sv, cell(k + 1, col), Qp);
+      load_fields<5>(db, sv, cell(k + 1, col), dp);
+      load_fields<3>(mb + 6 * sv, sv, cell(k + 1, col), Su);
+      load_fields<1>(mub + 2 * sv, sv, cell(k + 1, col), &mu);
+      load_fields<5>(A.r + B.qoff, sv, here, r);
+      load_fields<1>(mb + 9 * sv, sv, here, &vc);
+      load_fields<1>(mub + 3 * sv, sv, here, &D);
+      double O[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int64_t sd = d == 0 ? 1 : (d == 1 ? B.sj : B.sk);
+      for (int d = 0; d < 2; ++d) {
+        const uint32_t st = d == 0 ? 8u : sj8;
+        double up[5], lo[5], Q[5], dQ[5], S[3], m;
+        load_fields<5>(qb, sv, cell(k, col + st), Q);
+        load_fields<5>(db, sv, cell(k, col + st), dQ);
+        load_fields<3>(mb + 3 * d * sv, sv, cell(k, col + st), S);
+        load_fields<1>(mub + d * sv, sv, cell(k, col + st), &m);
+        neighbour(Q, dQ, S, m, 0.5, gm1, up);
+        load_fields<5>(qb, sv, cell(k, col - st), Q);
+        load_fields<5>(db, sv, cell(k, col - st), dQ);
+        load_fields<3>(mb + 3 * d * sv, sv, here, S);
+        load_fields<1>(mub + d * sv, sv, here, &m);
+        neighbour(Q, dQ, S, m, -0.5, gm1, lo);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) O[v] = O[v] + (up[v] + lo[v]);
+      }
       double up[5], lo[5];
-      {
-        const int64_t m = c + sd;            // upper neighbour, through the cell's upper face
-        double Qm[5], dQ[5], Qp[5], F0[5], F1[5];
-        load5(qb, m, B.sv, Qm);
-        load5(db, m, B.sv, dQ);
-        const double sx = mb[(3 * d) * B.sv + m], sy = mb[(3 * d + 1) * B.sv + m], sz = mb[(3 * d + 2) * B.sv + m];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) Qp[v] = Qm[v] + dQ[v];
-        flux_dot(Qp, sx, sy, sz, gm1, F1);
-        flux_dot(Qm, sx, sy, sz, gm1, F0);
-        const double mu = mub[d * B.sv + m];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) up[v] = 0.5 * (F1[v] - F0[v]) - mu * dQ[v];
-      }
-      {
-        const int64_t m = c - sd;            // lower neighbour, through the cell's lower face
-        double Qm[5], dQ[5], Qp[5], F0[5], F1[5];
-        load5(qb, m, B.sv, Qm);
-        load5(db, m, B.sv, dQ);
-        const double sx = mb[(3 * d) * B.sv + c], sy = mb[(3 * d + 1) * B.sv + c], sz = mb[(3 * d + 2) * B.sv + c];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) Qp[v] = Qm[v] + dQ[v];
-        flux_dot(Qp, sx, sy, sz, gm1, F1);
-        flux_dot(Qm, sx, sy, sz, gm1, F0);
-        const double mu = mub[d * B.sv + c];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) lo[v] = -0.5 * (F1[v] - F0[v]) - mu * dQ[v];
-      }
+      neighbour(Qp, dp, Su, mu, 0.5, gm1, up);
+      neighbour(Qm, dm, Sk, mk, -0.5, gm1, lo);
 #pragma unroll
       for (int v = 0; v < 5; ++v) O[v] = O[v] + (up[v] + lo[v]);
+      double o[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        const double rhs = -vc * r[v];
+        o[v] = (rhs - O[v]) / D;
+      }
+      store_fields<5>(A.dq_out + B.qoff, sv, here, o);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        Qm[v] = Q0[v];
+        dm[v] = d0[v];
+        Q0[v] = Qp[v];
+        d0[v] = dp[v];
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x) Sk[x] = Su[x];
+      mk = mu;
     }
-    const double vc = mb[9 * B.sv + c];
-    const double D = mub[3 * B.sv + c];
-    const double* rb = A.r + B.qoff;
-    double* ob = A.dq_out + B.qoff;
-    double rhs[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) rhs[v] = -vc * rb[v * B.sv + c];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) ob[v * B.sv + c] = (rhs[v] - O[v]) / D;
   }
 }
 
@@ -234,9 +294,8 @@ void launch_ifv_diag(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, i
                      hipStream_t s) {
   hipLaunchKernelGGL(k_ifv_diag, dim3(nwg), dim3(256), 0, s, A, blocks, nblk, nchunks);
 }
-void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_ifv_sweep, dim3(nwg), dim3(256), 0, s, A, blocks, nblk, nchunks);
+void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int items, hipStream_t s) {
+  hipLaunchKernelGGL(k_ifv_sweep, dim3(items, std::min(nblk, 65535)), dim3(256), 0, s, A, blocks, nblk, kc);
 }
 void launch_ifv_apply(double* q, const double* dq, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                       hipStream_t s) {

@@ -338,10 +338,11 @@ struct cfd_ctx {
   // per sweep: [node sweeps 0..2][cell sweeps 0..2]
   int poff[6] = {0}, pcount[6] = {0}, pmax[6] = {0};
   int qthreads[3] = {0};   // threads of each state ghost sweep (k_ghost_q)
-  // inviscid flow: every face's ghost layers over its own cells, all three
-  // directions in one launch (no stencil of the inviscid stage reads an edge
-  // or corner ghost cell, the only cells the sweep order exists for)
+  // every face's ghost layers over its own cells, all three directions in one
+  // launch: for the inviscid stage and the implicit sweeps, whose stencils read
+  // no edge or corner ghost cell, the only cells the sweep order exists for
   int pm_off = 0, pm_count = 0, pm_threads = 0;
+  int nconn = 0;
   // those patches grouped by block and face: ranges [6 nblk + 1] (device), for
   // the brick kernel (null: viscous flow, or no room in the workspace)
   const int32_t* dpatch_first = nullptr;
@@ -691,7 +692,7 @@ void timed(cfd_ctx* c, int cls, hipStream_t s, F&& launch) {
 // full: the i -> j -> k sweeps (edges and corners included) even where one
 // launch over the faces would do.
 void ghost_fill(cfd_ctx* c, double* q, hipStream_t s, bool full = false) {
-  if (!full && c->pm_count > 0) {
+  if (!full && !c->params.viscous) {
     timed(c, 1, s, [&] {
       launch_ghost_q(q, c->met(), c->dblocks, c->dpatches + c->pm_off, c->pm_count, c->pm_threads, c->SP, s);
     });
@@ -931,11 +932,10 @@ cfd_status guard(cfd_ctx* c, F&& f) {
 size_t implicit_arena_bytes(const cfd_ctx* c) { return align256((size_t)c->L.q_elems * sizeof(double)); }
 
 // One implicit step on the finite-volume residual (kernels_implicit.hip):
-// ghost fill of Q^n, the CFL step at `cfl` (global minimum; the per-cell steps
-// come with the face coefficients), R(Q^n), the history row (norms of R, totals
-// of Q^n, minimum step), face coefficients and the diagonal, `sweeps` Jacobi
-// sweeps each after a ghost fill of the iterate (connections copy it, physical
-// patches zero it), Q += dQ.
+// ghost fill of Q^n, R(Q^n), face coefficients with the CFL step at `cfl` (per
+// cell, and the global minimum) and the totals of Q^n, the diagonal with the
+// norms of R, the history row, `sweeps` Jacobi sweeps each after a ghost fill of
+// the iterate (connections copy it, physical patches zero it), Q += dQ.
 void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* work, hipStream_t s) {
   const size_t ab = implicit_arena_bytes(c);
   double* R = reinterpret_cast<double*>(work);
@@ -946,17 +946,11 @@ void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* 
   P.cfl = cfl;
   const int nwg = dt_nwg(c);
   ghost_fill(c, q, s);
-  timed(c, 2, s, [&] {
-    launch_dt(q, c->met(), c->scal(), c->part_dt(), c->dblocks, c->nblk, c->nchunks, P, nwg, false, s);
-  });
-  launch_finalize(c->part_dt(), nwg, 0, 0.0, c->d_dt(), nullptr, nullptr, s);
   StageArgs A = stage_args(c);
   A.qs = q;
   A.qn = q;
   A.out = R;
   launch_stage(c, A, 0, s);
-  timed(c, 3, s, [&] { launch_norms(q, R, c->met(), c->part_nrm(), c->dblocks, c->nblk, c->nchunks, nwg, s); });
-  launch_finalize(c->part_nrm(), nwg, 1, 1.0 / (double)c->ncells, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
   ImplicitArgs I{};
   I.q = q;
   I.met = c->met();
@@ -970,18 +964,31 @@ void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* 
   I.mu_inf = c->SP.mu_inf;
   I.s_star = c->SP.s_star;
   I.cfl = cfl;
-  launch_ifv_faces(I, c->dblocks, c->nblk, c->nchunks, P, nwg, s);
+  I.rows = c->part_dt();
+  timed(c, 2, s, [&] { launch_ifv_faces(I, c->dblocks, c->nblk, c->nchunks, P, nwg, s); });
+  if (!c->params.local_dt) launch_finalize(c->part_dt(), nwg, 0, 0.0, c->d_dt(), nullptr, nullptr, s);
   I.dq_out = dA;
-  launch_ifv_diag(I, c->dblocks, c->nblk, c->nchunks, nwg, s);
+  timed(c, 3, s, [&] { launch_ifv_diag(I, c->dblocks, c->nblk, c->nchunks, nwg, s); });
+  launch_finalize(c->part_dt(), 2 * nwg, 2, 1.0 / (double)c->ncells, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
   double* cur = dA;
   double* nxt = dB;
+  // planes a sweep's march: more waves than fit (three a SIMD, twice over): the last of them leave less idle
+  // (192 x 96 x 96: 4 planes 1.49 ms a step, 6 1.53, 9 1.60)
+  const int kc = (int)std::max<int64_t>(1, std::min<int64_t>(16, c->nchunks / (24 * c->num_cu)));
+  int64_t items = 1;
+  for (const BlockDesc& B : c->hblocks)
+    items = std::max(items, (int64_t)((B.n[0] + 63) / 64) * ((B.n[1] + 3) / 4) * ((B.n[2] + kc - 1) / kc));
   for (int k = 0; k < sweeps; ++k) {
-    for (int d = 0; d < 3; ++d)
-      launch_ghost_q(cur, c->met(), c->dblocks, c->dpatches + c->poff[3 + d], c->pcount[3 + d], c->qthreads[d],
-                     c->SP, s, 1);
+    // A sweep reads the neighbours across faces alone, so one launch over the
+    // faces' own layers does (24 launches of three sweeps: 146 us at 192 x 96 x
+    // 96); the zeros behind physical patches stay in both iterates from their
+    // first fill on.
+    if (k < 2 || c->nconn > 0)
+      launch_ghost_q(cur, c->met(), c->dblocks, c->dpatches + c->pm_off, c->pm_count, c->pm_threads, c->SP, s,
+                     k < 2 ? 1 : 2);
     I.dq_in = cur;
     I.dq_out = nxt;
-    timed(c, 0, s, [&] { launch_ifv_sweep(I, c->dblocks, c->nblk, c->nchunks, nwg, s); });
+    timed(c, 0, s, [&] { launch_ifv_sweep(I, c->dblocks, c->nblk, kc, (int)items, s); });
     std::swap(cur, nxt);
   }
   launch_ifv_apply(q, cur, c->dblocks, c->nblk, c->nchunks, nwg, s);
@@ -1070,6 +1077,7 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
     c->id = g_ctx_ids++;
     c->params = *params;
     c->nblk = nblk;
+    c->nconn = nconn;
     c->dims.assign(dims, dims + nblk);
     c->L = make_layout(nblk, dims);
     size_t need = 0;
@@ -1118,7 +1126,7 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
         for (int p = c->poff[sweep]; p < (int)all.size(); ++p)
           c->qthreads[d] = std::max(c->qthreads[d], all[p].count * ghost_threads_per_point(all[p].kind, d));
     }
-    if (!params->viscous) {
+    {
       c->pm_off = (int)all.size();
       for (int d = 0; d < 3; ++d) {
         int mx = 0;
@@ -1135,7 +1143,7 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
       for (int p = c->pm_off; p < (int)all.size(); ++p) ++first[6 * all[p].blk + all[p].face + 1];
       for (int f = 0; f < 6 * nblk; ++f) first[f + 1] += first[f];
       const size_t slots = (first.size() * sizeof(int32_t) + sizeof(PatchDesc) - 1) / sizeof(PatchDesc);
-      if (all.size() + slots <= (size_t)PATCHES_PER_BLOCK * nblk) {
+      if (!params->viscous && all.size() + slots <= (size_t)PATCHES_PER_BLOCK * nblk) {
         c->dpatch_first = reinterpret_cast<const int32_t*>(c->dpatches + all.size());
         all.resize(all.size() + slots);
         std::memcpy(all.data() + (all.size() - slots), first.data(), first.size() * sizeof(int32_t));
