@@ -38,6 +38,10 @@
 // Navier-Stokes 62 to 8 (stage 1) and 0 (stage 2) dwords.  256 x 128 x 128 NS
 // 1577 -> 1500 us a step, 2 x 2 x (250 x 203 x 72) FP32 NS 5.07 -> 4.66 ms,
 // 128 x (48 x 24 x 24) Euler V-cycles 5.50 -> 5.19 ms; FP32 Euler as before.
+// FP64 Navier-Stokes on a grid past the caches runs at the rate of a copy (500 B
+// a cell and stage); face metrics, Q^n and the output, used once, then carry the
+// non-temporal hint so that the caches keep the halos: 2 x 2 x (512 x 512 x 144)
+// 56.0 -> 54.7 ms, 256 x 128 x 128 alike; FP32 NS would lose 2 % by it.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "cfd_internal.hpp"
@@ -80,7 +84,7 @@ template <typename T, bool VISC, int MODE, int TI, int TJ>
 __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_ring(
     StageArgs A, const BlockDesc* __restrict__ blocks, const TileDesc* __restrict__ tiles, Gas<T> gas) {
   using LD = RingLds<T, VISC, TI, TJ>;
-  constexpr bool F64 = sizeof(T) == 8, EARLY = F64 || VISC;
+  constexpr bool F64 = sizeof(T) == 8, EARLY = F64 || VISC, STREAM = F64 && VISC;
   constexpr int NT = TI * TJ;
   constexpr int WI = LD::WI, WJ = LD::WJ;
   __shared__ __attribute__((aligned(16))) char smem[MODE == 3 ? LD::TOTAL_DT : LD::TOTAL];
@@ -216,14 +220,14 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
       B.sv = sv;
       // inputs of this plane's cell update, loaded before the face work
       CellIn cin;
-      load_cell<MODE>(A, B, CellAt{plane(k), own}, cin);
+      load_cell<MODE, STREAM>(A, B, CellAt{plane(k), own}, cin);
       // ---- A. faces of plane k
       // lower face, along direction d = 0 (i) or 1 (j), of cell (i0+ci, j0+rj):
       // flux F, area vector S.  One expression for both directions, so that
       // the tile-edge faces of either run in the same lanes.
       auto metrics = [&](int d, auto c, double S[3], double St[2][3], double& vf) {
-        load_fields<3>(mb + (int64_t)(3 * d) * sv, sv, c, S);
-        if (VISC) face_vmetrics(vb, sv, c, d, St, vf);
+        load_fields<3, STREAM>(mb + (int64_t)(3 * d) * sv, sv, c, S);
+        if (VISC) face_vmetrics<STREAM>(vb, sv, c, d, St, vf);
       };
       auto face = [&](int d, int ci, int rj, const double S[3], const double St[2][3], double vf, double F[5]) {
         const int p = (rj + 2) * WI + ci + 2;             // the cell above the face
@@ -353,7 +357,7 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
           Dk[q] = Fku[q] - Fklo[q];
         }
         double Rc[5], Qo[5];
-        update_cell<MODE>(A, B, CellAt{plane(k), own}, Di, Dj, Dk, cin, Rc, Qo);
+        update_cell<MODE, STREAM>(A, B, CellAt{plane(k), own}, Di, Dj, Dk, cin, Rc, Qo);
         if (MODE == 1) {
 #pragma unroll
           for (int q = 0; q < 5; ++q) {

@@ -77,7 +77,8 @@ struct CellAt {
   uint32_t col;
 };
 
-// N consecutive fields (stride sv) of a cell, read or written.  The scalar
+// N consecutive fields (stride sv) of a cell, read or written; STREAM: with the
+// non-temporal hint.  The scalar
 // address steps from field to field; the empty asm keeps it one pair of
 // registers, where the compiler would else keep a product or a vector address
 // per field live across the planes.
@@ -86,43 +87,46 @@ __device__ __forceinline__ uint64_t scalar64(uint64_t x) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
   return (uint64_t)hi << 32 | lo;
 }
-template <int N>
+template <int N, bool STREAM = false>
 __device__ __forceinline__ void load_fields(const double* base, int64_t sv, CellAt c, double* v) {
   const double* p = reinterpret_cast<const double*>(scalar64(reinterpret_cast<uint64_t>(base + c.plane)));
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    v[q] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + c.col);
+    const double* a = reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + c.col);
+    v[q] = STREAM ? __builtin_nontemporal_load(a) : *a;
     p += sv;
     asm("" : "+s"(p));
   }
 }
-template <int N>
+template <int N, bool STREAM = false>
 __device__ __forceinline__ void load_fields(const double* base, int64_t sv, int64_t c, double* v) {
 #pragma unroll
   for (int q = 0; q < N; ++q) v[q] = base[q * sv + c];
 }
-template <int N>
+template <int N, bool STREAM = false>
 __device__ __forceinline__ void store_fields(double* base, int64_t sv, CellAt c, const double* v) {
   double* p = reinterpret_cast<double*>(scalar64(reinterpret_cast<uint64_t>(base + c.plane)));
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    *reinterpret_cast<double*>(reinterpret_cast<char*>(p) + c.col) = v[q];
+    double* a = reinterpret_cast<double*>(reinterpret_cast<char*>(p) + c.col);
+    if (STREAM) __builtin_nontemporal_store(v[q], a);
+    else *a = v[q];
     p += sv;
     asm("" : "+s"(p));
   }
 }
-template <int N>
+template <int N, bool STREAM = false>
 __device__ __forceinline__ void store_fields(double* base, int64_t sv, int64_t c, const double* v) {
 #pragma unroll
   for (int q = 0; q < N; ++q) base[q * sv + c] = v[q];
 }
 
 // Viscous metric terms of the lower d-face of cell c, from the arena vb.
-template <class At>
+template <bool STREAM = false, class At>
 __device__ __forceinline__ void face_vmetrics(const double* __restrict__ vb, int64_t sv, At c, int d, double St[2][3],
                                               double& vf) {
   double m[7];
-  load_fields<7>(vb + (int64_t)(7 * d) * sv, sv, c, m);
+  load_fields<7, STREAM>(vb + (int64_t)(7 * d) * sv, sv, c, m);
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -300,21 +304,21 @@ struct CellIn {
 // as far as the compiler knows, so a load placed after a store would wait for
 // that store (and, through the shared memory counter, for every store before
 // it).  A kernel may load them early, before its face work, to hide latency.
-template <int MODE, class At>
+template <int MODE, bool STREAM = false, class At>
 __device__ __forceinline__ void load_cell(const StageArgs& A, const BlockDesc& B, At c, CellIn& in) {
   load_fields<1>(A.met + B.moff + 9 * B.sv, B.sv, c, &in.vol);
   if (MODE == 0) return;
   if (A.local_dt) load_fields<1>(A.dt + B.soff, B.sv, c, &in.dt);
   else in.dt = A.dt[0];
   load_fields<5>(A.qs + B.qoff, B.sv, c, in.qv);
-  if (MODE >= 2) load_fields<5>(A.qn + B.qoff, B.sv, c, in.qn);
+  if (MODE >= 2) load_fields<5, STREAM>(A.qn + B.qoff, B.sv, c, in.qn);
 }
 
 // R = ((Di + Dj) + Dk) / V, then write R (mode 0) or the stage update
 // (modes 1-3; mode 1 also writes R for the norms if A.rout is set), less
 // (A.fb dt) force when a multigrid level's forcing is given.  R is returned
 // in Rc, the written state in Qo (modes 1-3).
-template <int MODE, class At>
+template <int MODE, bool STREAM = false, class At>
 __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc& B, At c, const double Di[5],
                                             const double Dj[5], const double Dk[5], const CellIn& in,
                                             double Rc[5] = nullptr, double Qo[5] = nullptr,
@@ -324,7 +328,7 @@ __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc&
 #pragma unroll
   for (int q = 0; q < 5; ++q) R[q] = ((Di[q] + Dj[q]) + Dk[q]) * ivol;
   if (MODE == 0) {
-    store_fields<5>(A.out + B.qoff, B.sv, c, R);
+    store_fields<5, STREAM>(A.out + B.qoff, B.sv, c, R);
   } else {
     double o[5], F[5];
     if (force) load_fields<5>(force + B.qoff, B.sv, c, F);
@@ -338,7 +342,7 @@ __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc&
       }
       if (Qo) Qo[q] = o[q];
     }
-    store_fields<5>(A.out + B.qoff, B.sv, c, o);
+    store_fields<5, STREAM>(A.out + B.qoff, B.sv, c, o);
     if (MODE == 1 && A.rout) store_fields<5>(A.rout + B.qoff, B.sv, c, R);
   }
   if (Rc) {
