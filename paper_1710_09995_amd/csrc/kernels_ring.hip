@@ -31,16 +31,18 @@
 // issue is the latency of loads that sit right before their use.  So: a face's
 // metrics are loaded together before its flux; W(k+2) and W(k+3) are loaded
 // before the k-face, without branches (columns and planes clamped to the ghost
-// layers; a load under a branch is waited for where the branch ends), the FP32
-// Euler variants, four waves a SIMD, excepted for W(k+2); and addresses are one
-// 32-bit column offset beside scalar bases.  64-bit vector addresses per field,
+// layers; a load under a branch is waited for where the branch ends), but for
+// W(k+2) in the FP32 Euler variants, four waves a SIMD, and in the FP64 stage 3,
+// which would spill (256 x 128 x 128 NS, stage 3: 585 us before, 619 with it, 533
+// without); and addresses are one 32-bit column offset beside scalar bases.  64-bit vector addresses per field,
 // hoisted out of the plane loop, filled the registers and spilled: FP64
 // Navier-Stokes 62 to 8 (stage 1) and 0 (stage 2) dwords.  256 x 128 x 128 NS
 // 1577 -> 1500 us a step, 2 x 2 x (250 x 203 x 72) FP32 NS 5.07 -> 4.66 ms,
 // 128 x (48 x 24 x 24) Euler V-cycles 5.50 -> 5.19 ms; FP32 Euler as before.
 // FP64 Navier-Stokes on a grid past the caches runs at the rate of a copy (500 B
 // a cell and stage); face metrics, Q^n and the output, used once, then carry the
-// non-temporal hint so that the caches keep the halos: 2 x 2 x (512 x 512 x 144)
+// non-temporal hint (the face vectors not in stage 3, which reads them again)
+// so that the caches keep the halos: 2 x 2 x (512 x 512 x 144)
 // 56.0 -> 54.7 ms, 256 x 128 x 128 alike; FP32 NS would lose 2 % by it.
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -84,7 +86,7 @@ template <typename T, bool VISC, int MODE, int TI, int TJ>
 __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_ring(
     StageArgs A, const BlockDesc* __restrict__ blocks, const TileDesc* __restrict__ tiles, Gas<T> gas) {
   using LD = RingLds<T, VISC, TI, TJ>;
-  constexpr bool F64 = sizeof(T) == 8, EARLY = F64 || VISC, STREAM = F64 && VISC;
+  constexpr bool F64 = sizeof(T) == 8, EARLY = (F64 || VISC) && !(F64 && MODE == 3), STREAM = F64 && VISC;
   constexpr int NT = TI * TJ;
   constexpr int WI = LD::WI, WJ = LD::WJ;
   __shared__ __attribute__((aligned(16))) char smem[MODE == 3 ? LD::TOTAL_DT : LD::TOTAL];
@@ -226,7 +228,7 @@ __global__ void __launch_bounds__(TI * TJ, (ring_min_waves<T, VISC>())) k_stage_
       // flux F, area vector S.  One expression for both directions, so that
       // the tile-edge faces of either run in the same lanes.
       auto metrics = [&](int d, auto c, double S[3], double St[2][3], double& vf) {
-        load_fields<3, STREAM>(mb + (int64_t)(3 * d) * sv, sv, c, S);
+        load_fields<3, STREAM && MODE != 3>(mb + (int64_t)(3 * d) * sv, sv, c, S);   // stage 3 reads them again
         if (VISC) face_vmetrics<STREAM>(vb, sv, c, d, St, vf);
       };
       auto face = [&](int d, int ci, int rj, const double S[3], const double St[2][3], double vf, double F[5]) {

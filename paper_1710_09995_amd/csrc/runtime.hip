@@ -583,9 +583,11 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 // 64 x 32 x 32 54 / 79, 96 x 48 x 48 (1728 bricks) 129 / 136, 128 x 64 x 64
 // (4096) 332 / 188; 128 blocks of 12 x 8 x 8 (1024) 119 / 143, of 24 x 12 x 12
 // (3456) 271 / 245; NS 64 x 32 x 32 83 / 134, 96 x 48 x 48 173 / 202.
-// FP32-flux kernels take 256-column tiles (tile_j 4): chain of 40 uneven Euler
-// blocks 4.42 ms a step against 4.64 with 512 columns, 2 x 2 blocks of 250 x
-// 203 x 72 NS 5.37 against 5.47.  FP64 kernels take 512 columns on grids that
+// FP32 Euler takes 256-column tiles (tile_j 4): chain of 40 uneven Euler blocks
+// 4.42 ms a step against 4.64 with 512 columns.  FP32 NS takes either by cost:
+// 512 columns load fewer halo cells, which counts on a grid past the caches
+// (2 x 2 blocks of 512 x 512 x 144 44.6 ms against 49.5; of 250 x 203 x 72 4.47
+// against 4.44).  FP64 kernels take 512 columns on grids that
 // fill the chip (256 x 128 x 128 NS 1.774 against 1.787 ms) unless 256-column
 // tiles pad the blocks that much less (2 x 2 blocks of 130 x 260 x 100 NS 6.46
 // against 7.16 ms); both keep two waves per SIMD.
@@ -593,7 +595,7 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
   if (brick_count(dims) <= 7 * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
   cfd_tuning best{2, 8, 32, 1, 1};
   double least = 0.0;
-  for (int tj = p.flux_fp32 ? 4 : 8; tj >= 4; tj /= 2)
+  for (int tj = p.flux_fp32 && !p.viscous ? 4 : 8; tj >= 4; tj /= 2)
     for (int tk = 32; tk >= 4; --tk) {
       const cfd_tuning t{2, tj, tk, 1, 1};
       const double cost = ring_cost(dims, t, max_tiles, num_cu, p.flux_fp32 != 0, p.viscous != 0);
