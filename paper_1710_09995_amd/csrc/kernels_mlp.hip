@@ -39,23 +39,30 @@ __device__ __forceinline__ float4_t unpack_bf16(short4_t h) {
   return float4_t{bf2f((uint16_t)h[0]), bf2f((uint16_t)h[1]), bf2f((uint16_t)h[2]), bf2f((uint16_t)h[3])};
 }
 
-// a / (1 + exp(-z)), correctly rounded for every quotient in the normal range:
-// reciprocal estimate, one Newton step, quotient and two residual corrections
-// in FMA arithmetic, without the scaling of the general division (the
-// denominator lies in [1, 2^100]: exp is capped there, where the quotient is 0
-// to any precision).
-__device__ __forceinline__ float logistic_of(float a, float z) {
-  const float d = 1.0f + fminf(__expf(-z), 1.2676506e30f);
+// SiLU and its derivative, by the general division (infinities, NaN and quotients
+// below the normal range included).
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
+__device__ __forceinline__ float silu_grad_f(float z) {
+  const float s = 1.0f / (1.0f + __expf(-z));
+  return s * (1.0f + z * (1.0f - s));
+}
+
+// silu_f's value to the bit (but for the sign of zero) where |z| < SILU_MID, the
+// denominator in [1, 2^100): reciprocal estimate, one Newton-Raphson step,
+// quotient, two residual corrections q' = q + r (z - d q) (Markstein, IBM J. Res.
+// Dev. 34(1), 1990), without the scaling and the special cases of the general
+// division.  For large batches, where SiLU is what bounds the pass: 1,769,472
+// points of the 5-128x4-5 net 0.494 ms, 0.537 with the division alone.  A wave of
+// small batches has its SIMD to itself, and the branch costs it more than the
+// division (131,071 points: 76 us against 63).
+constexpr float SILU_MID = 69.0f;
+__device__ __forceinline__ float silu_mid(float z) {
+  const float d = 1.0f + __expf(-z);
   float r = __builtin_amdgcn_rcpf(d);
   r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-  float q = a * r;
-  q = __builtin_fmaf(__builtin_fmaf(-d, q, a), r, q);
-  return __builtin_fmaf(__builtin_fmaf(-d, q, a), r, q);
-}
-__device__ __forceinline__ float silu_f(float z) { return logistic_of(z, z); }
-__device__ __forceinline__ float silu_grad_f(float z) {
-  const float s = logistic_of(1.0f, z);
-  return s * (1.0f + z * (1.0f - s));
+  float q = z * r;
+  q = __builtin_fmaf(__builtin_fmaf(-d, q, z), r, q);
+  return __builtin_fmaf(__builtin_fmaf(-d, q, z), r, q);
 }
 
 // ------------------------------------------------------------------ forward
@@ -73,7 +80,7 @@ __device__ __forceinline__ float silu_grad_f(float z) {
 //
 // Bound: SiLU (exp and reciprocal at a quarter of the VALU rate, about 80 issue
 // cycles a wave and activation) before the MFMAs (106 kflop a point).
-// 1,769,472 points of the 5-128x4-5 net: 0.487 ms (0.385 PFLOP/s); 2.45 ms with
+// 1,769,472 points of the 5-128x4-5 net: 0.494 ms (0.380 PFLOP/s); 2.45 ms with
 // the activations in LDS and the weights read from L2 by every wave.
 constexpr int MLP_LDS_MAX = 144 * 1024;   // weights held by a workgroup
 
@@ -120,20 +127,32 @@ __device__ __forceinline__ void layer_fwd(const uint16_t* w, const float* b, con
       for (int m = 0; m < M; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, in[m][ks], acc[m], 0, 0, 0);
     }
     const float4_t bias = *reinterpret_cast<const float4_t*>(b + nt * 16 + g4);
+    float most = 0.f;
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const float4_t z = acc[m] + bias;
-      if (CACHE && p[m] < n) *reinterpret_cast<float4_mem*>(cache + p[m] * cpp + zoff + nt * 16 + g4) = z;
-      if (LAST) {
-        y[m] = z;
-      } else {
-        float4_t h;
+      acc[m] = acc[m] + bias;
+      if (CACHE && p[m] < n) *reinterpret_cast<float4_mem*>(cache + p[m] * cpp + zoff + nt * 16 + g4) = acc[m];
+      if (LAST) y[m] = acc[m];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) h[r] = silu_f(z[r]);
-        out[m][nt] = pack_bf16(h);
-        if (CACHE && p[m] < n)
-          *reinterpret_cast<float4_mem*>(cache + p[m] * cpp + hoff + nt * 16 + g4) = unpack_bf16(out[m][nt]);
-      }
+      for (int r = 0; r < 4; ++r) most = fmaxf(most, fabsf(acc[m][r]));
+    }
+    if (LAST) continue;
+    if (M == 1 || __any(most >= SILU_MID)) {
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[m][r] = silu_f(acc[m][r]);
+    } else {
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[m][r] = silu_mid(acc[m][r]);
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      out[m][nt] = pack_bf16(acc[m]);
+      if (CACHE && p[m] < n)
+        *reinterpret_cast<float4_mem*>(cache + p[m] * cpp + hoff + nt * 16 + g4) = unpack_bf16(out[m][nt]);
     }
   }
 }
