@@ -286,13 +286,23 @@ __global__ void __launch_bounds__(256) k_mlp_mse_final(const double* __restrict_
 struct Split3 {
   short4_t hi, mid, lo;
 };
+// An infinity goes into mid (hi the largest BF16 value, lo zero), so that products
+// and sums stay infinite, and a value past the largest BF16 one is not rounded to
+// infinity.  Terms below BF16's least subnormal, 9e-41, are lost: values under
+// 1e-33 have fewer than 24 bits.
 __device__ __forceinline__ Split3 split3(float4_t v) {
+  constexpr float BF16_MAX = 3.38953139e38f;
   Split3 s;
-  s.hi = pack_bf16(v);
+  float4_t c;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c[r] = __builtin_amdgcn_fmed3f(v[r], -BF16_MAX, BF16_MAX);
+  s.hi = pack_bf16(c);
   v = v - unpack_bf16(s.hi);
   s.mid = pack_bf16(v);
-  v = v - unpack_bf16(s.mid);
-  s.lo = pack_bf16(v);
+  c = v - unpack_bf16(s.mid);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c[r] = __builtin_isinf(v[r]) ? 0.f : c[r];
+  s.lo = pack_bf16(c);
   return s;
 }
 __device__ __forceinline__ float4_t mfma3(short4_t w, const Split3& d, float4_t acc) {

@@ -1,12 +1,14 @@
 """GPU: the network at pre-activations whose exponential overflows, underflows or
 is infinite: SiLU and its derivative are those of the general division z / (1 +
 exp(-z)), through every variant of the forward pass (cached, small batches, large
-batches) and the backward pass."""
+batches) and the backward pass; gradients of infinite loss gradients and of ones
+past the largest BF16 value."""
 import numpy as np
 import pytest
 
+from oracle import mlp as omlp
 from paper_1710_09995_amd import cases
-from test_gpu_mlp import round_bf16
+from test_gpu_mlp import _rel, round_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +61,47 @@ def test_silu_derivative_is_the_general_quotients():
         s = 0.0 if v < -89.0 else 1.0 / (1.0 + np.exp(-v))
         want = s * (1.0 + v * (1.0 - s)) / 16.0
         assert np.all(np.abs(db - want) <= 1e-5 * abs(want)), v
+
+
+def _positive(scale):
+    """A net of positive weights over positive inputs (every activation and
+    derivative is positive), its cached activations and the size of its outputs."""
+    import torch
+    from paper_1710_09995_amd.binding import Mlp
+    params = [(scale * np.abs(W), b) for W, b in cases.mlp_init(5, 32, 2, 5, seed=1, out_scale=1.0)]
+    m = Mlp(params, d_hidden=32, n_hidden=2)
+    x = np.random.default_rng(2).uniform(0.1, 1.0, (40, 5)).astype(np.float32)
+    y, cache = m.forward(torch.from_numpy(x).cuda(), cache=True)
+    return m, y, cache
+
+
+@pytest.mark.parametrize("v", [np.inf, -np.inf])
+def test_infinite_loss_gradients_give_infinite_gradients(v):
+    import torch
+    from paper_1710_09995_amd.binding import unpack_params
+    m, y, cache = _positive(1.0)
+    dy = torch.zeros_like(y)
+    dy[3, 1] = float(v)
+    g = unpack_params(m.backward(cache, dy).cpu().numpy(), 5, 32, 2, 5)
+    for gw, gb in g[:2]:
+        assert np.all(gw == v) and np.all(gb == v)
+    rest = [0, 2, 3, 4]
+    assert np.all(g[2][0][1] == v) and g[2][1][1] == v
+    assert np.all(g[2][0][rest] == 0.0) and np.all(g[2][1][rest] == 0.0)
+
+
+@pytest.mark.parametrize("v", [3.3895314e38, 3.39e38, -3.4e38])
+def test_loss_gradients_past_the_largest_bf16_value(v):
+    """The gates of the gradients at ordinary sizes (FP32 rounding: 2e-6)."""
+    import torch
+    from paper_1710_09995_amd.binding import unpack_params
+    m, y, cache = _positive(0.1)
+    dy = np.zeros((40, 5), np.float32)
+    dy[3, 1] = v
+    got = unpack_params(m.backward(cache, torch.from_numpy(dy).cuda()).cpu().numpy(), 5, 32, 2, 5)
+    c = cache.cpu().numpy().astype(np.float64)
+    kept = [(c[:, :5], c[:, 16:48]), (c[:, 48:80], c[:, 80:112]), (c[:, 112:144], c[:, 144:149])]
+    want = omlp.backward(m.bf16_params(), kept, dy.astype(np.float64))
+    for (gw, gb), (ww, wb) in zip(got, want):
+        gw, gb = gw.astype(np.float64), gb.astype(np.float64)
+        assert _rel(gw, ww) <= 2e-6 and _rel(gb, wb) <= 2e-6
