@@ -954,13 +954,13 @@ __global__ void __launch_bounds__(256, 2) k_wcns5_euler_march(Batch<EulerBlk> Bt
 // The one-pass kernels take blocks of 32 k cells in all: below that the three
 // passes' thousands of short threads are quicker (16^3 41 us a residual against
 // 46, 24^3 43 against 46; 32^3 equal; 48^3 67 against 52, 128 x 64 x 64 131
-// against 86).  Rows under eight cells would be mostly end positions.
+// against 86).  Short rows do not matter: the three passes handle their five
+// cells beyond either end as well, and through memory (4 x 256 x 256 cells 79 us
+// against 240, 7 x 512 x 64 65 against 156; a 256 x 128 x 64 block joined to one
+// of five cells along i 372 against 563).
 bool one_pass_ok(const std::vector<EulerBlk>& v) {
   int64_t cells = 0;
-  for (const EulerBlk& b : v) {
-    if (b.n[0] < 8) return false;
-    cells += (int64_t)b.n[0] * b.n[1] * b.n[2];
-  }
+  for (const EulerBlk& b : v) cells += (int64_t)b.n[0] * b.n[1] * b.n[2];
   return cells >= (int64_t)1 << 15;
 }
 
