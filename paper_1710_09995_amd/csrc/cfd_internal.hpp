@@ -23,7 +23,7 @@ constexpr int CFD_BC_KIND_EXTRAP = 4;
 // One block of the multi-block grid, as the kernels see it.
 struct BlockDesc {
   int32_t n[3];        // interior cells ni, nj, nk
-  int32_t pad0;
+  int32_t swg;         // workgroups of the implicit sweep for the blocks before this one
   int64_t qoff;        // state arena: element index of padded cell (-g,-g,-g), var 0
   int64_t moff;        // metrics arena offset (NM vars, same strides)
   int64_t soff;        // scalar arena offset (1 var, same strides)

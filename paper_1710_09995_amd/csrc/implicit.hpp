@@ -27,8 +27,8 @@ void launch_ifv_faces(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, 
                       const StepParams& P, int nwg, hipStream_t s);
 void launch_ifv_diag(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                      hipStream_t s);
-// kc: planes a march; items: workgroups of the block that has the most
-void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int items, hipStream_t s);
+// kc: planes a march; nwg: the blocks' workgroups (BlockDesc::swg counts them)
+void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int nwg, hipStream_t s);
 void launch_ifv_apply(double* q, const double* dq, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                       hipStream_t s);
 

@@ -16,7 +16,6 @@
 // Every kernel but the sweep walks the interior cells as the grid's 64-cell row
 // chunks (chunks.hpp), one launch over all blocks, coalesced along i.
 #include <hip/hip_runtime.h>
-#include <algorithm>
 #include "cfd_internal.hpp"
 #include "physics.hpp"
 #include "stage_common.hpp"
@@ -179,87 +178,93 @@ __device__ __forceinline__ void neighbour(const double Q[5], const double dQ[5],
 // marches them over kc planes, its workgroup four rows side by side, so that Q,
 // dQ and the k-face of a plane are read once a march instead of by three
 // planes' waves that share no cache (row chunks in any order: 155 us a sweep at
-// 192 x 96 x 96; marching 142).  Three waves a SIMD: at four (128 registers) it
+// 192 x 96 x 96; marching 142).  The workgroups are numbered over the blocks: with
+// the largest block's for each, 128 x 96 x 96 cells among 600 blocks of 8 x 4 x 4
+// took 11.6 ms a step of eight sweeps.  Three waves a SIMD: at four (128 registers) it
 // spills (the step 2.3 ms against 1.5).
 __global__ void __launch_bounds__(256, 3) k_ifv_sweep(ImplicitArgs A, const BlockDesc* __restrict__ blocks,
                                                       int nblk, int kc) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const double gm1 = A.gamma - 1.0;
-  for (int b = blockIdx.y; b < nblk; b += gridDim.y) {
-    const BlockDesc B = blocks[b];
-    const int nci = (B.n[0] + 63) >> 6, njg = (B.n[1] + 3) >> 2;
-    const int u = blockIdx.x;                     // i chunk fastest, then the row group, then the planes
-    const int i = u % nci * 64 + lane, j = u / nci % njg * 4 + w, k0 = __builtin_amdgcn_readfirstlane(u / nci / njg) * kc;
-    if (i >= B.n[0] || j >= B.n[1] || k0 >= B.n[2]) continue;
-    const int k1 = __builtin_amdgcn_readfirstlane(min(k0 + kc, B.n[2]));
-    const double* qb = A.q + B.qoff;
-    const double* mb = A.met + B.moff;
-    const double* mub = A.mu + B.qoff;
-    const double* db = A.dq_in + B.qoff;
-    const int64_t sv = B.sv;
-    const uint32_t col0 = (uint32_t)((j + NG) * (int)B.sj + (i + NG)) * 8u, sj8 = (uint32_t)B.sj * 8u;
-    auto cell = [&](int k, uint32_t col) { return CellAt{(int64_t)(k + NG) * B.sk, col}; };
-    double Qm[5], dm[5], Q0[5], d0[5], Sk[3], mk;
-    load_fields<5>(qb, sv, cell(k0 - 1, col0), Qm);
-    load_fields<5>(db, sv, cell(k0 - 1, col0), dm);
-    load_fields<5>(qb, sv, cell(k0, col0), Q0);
-    load_fields<5>(db, sv, cell(k0, col0), d0);
-    load_fields<3>(mb + 6 * sv, sv, cell(k0, col0), Sk);
-    load_fields<1>(mub + 2 * sv, sv, cell(k0, col0), &mk);
+  int b = 0;                                    // the block that holds workgroup blockIdx.x
+  for (int hi = nblk - 1; b < hi;) {
+    const int mid = (b + hi + 1) >> 1;
+    if (blocks[mid].swg <= (int)blockIdx.x) b = mid;
+    else hi = mid - 1;
+  }
+  const BlockDesc B = blocks[b];
+  const int nci = (B.n[0] + 63) >> 6, njg = (B.n[1] + 3) >> 2;
+  const int u = blockIdx.x - B.swg;             // i chunk fastest, then the row group, then the planes
+  const int i = u % nci * 64 + lane, j = u / nci % njg * 4 + w, k0 = __builtin_amdgcn_readfirstlane(u / nci / njg) * kc;
+  if (i >= B.n[0] || j >= B.n[1]) return;
+  const int k1 = __builtin_amdgcn_readfirstlane(min(k0 + kc, B.n[2]));
+  const double* qb = A.q + B.qoff;
+  const double* mb = A.met + B.moff;
+  const double* mub = A.mu + B.qoff;
+  const double* db = A.dq_in + B.qoff;
+  const int64_t sv = B.sv;
+  const uint32_t col0 = (uint32_t)((j + NG) * (int)B.sj + (i + NG)) * 8u, sj8 = (uint32_t)B.sj * 8u;
+  auto cell = [&](int k, uint32_t col) { return CellAt{(int64_t)(k + NG) * B.sk, col}; };
+  double Qm[5], dm[5], Q0[5], d0[5], Sk[3], mk;
+  load_fields<5>(qb, sv, cell(k0 - 1, col0), Qm);
+  load_fields<5>(db, sv, cell(k0 - 1, col0), dm);
+  load_fields<5>(qb, sv, cell(k0, col0), Q0);
+  load_fields<5>(db, sv, cell(k0, col0), d0);
+  load_fields<3>(mb + 6 * sv, sv, cell(k0, col0), Sk);
+  load_fields<1>(mub + 2 * sv, sv, cell(k0, col0), &mk);
 #pragma unroll 1
-    for (int k = k0; k < k1; ++k) {
-      uint32_t col = col0;
-      asm volatile("" : "+v"(col));   // addresses formed here, not kept per field across the planes
-      const CellAt here = cell(k, col);
-      double Qp[5], dp[5], Su[3], mu, r[5], vc, D;
-      load_fields<5>(qb, sv, cell(k + 1, col), Qp);
-      load_fields<5>(db, sv, cell(k + 1, col), dp);
-      load_fields<3>(mb + 6 * sv, sv, cell(k + 1, col), Su);
-      load_fields<1>(mub + 2 * sv, sv, cell(k + 1, col), &mu);
-      load_fields<5>(A.r + B.qoff, sv, here, r);
-      load_fields<1>(mb + 9 * sv, sv, here, &vc);
-      load_fields<1>(mub + 3 * sv, sv, here, &D);
-      double O[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int k = k0; k < k1; ++k) {
+    uint32_t col = col0;
+    asm volatile("" : "+v"(col));   // addresses formed here, not kept per field across the planes
+    const CellAt here = cell(k, col);
+    double Qp[5], dp[5], Su[3], mu, r[5], vc, D;
+    load_fields<5>(qb, sv, cell(k + 1, col), Qp);
+    load_fields<5>(db, sv, cell(k + 1, col), dp);
+    load_fields<3>(mb + 6 * sv, sv, cell(k + 1, col), Su);
+    load_fields<1>(mub + 2 * sv, sv, cell(k + 1, col), &mu);
+    load_fields<5>(A.r + B.qoff, sv, here, r);
+    load_fields<1>(mb + 9 * sv, sv, here, &vc);
+    load_fields<1>(mub + 3 * sv, sv, here, &D);
+    double O[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        const uint32_t st = d == 0 ? 8u : sj8;
-        double up[5], lo[5], Q[5], dQ[5], S[3], m;
-        load_fields<5>(qb, sv, cell(k, col + st), Q);
-        load_fields<5>(db, sv, cell(k, col + st), dQ);
-        load_fields<3>(mb + 3 * d * sv, sv, cell(k, col + st), S);
-        load_fields<1>(mub + d * sv, sv, cell(k, col + st), &m);
-        neighbour(Q, dQ, S, m, 0.5, gm1, up);
-        load_fields<5>(qb, sv, cell(k, col - st), Q);
-        load_fields<5>(db, sv, cell(k, col - st), dQ);
-        load_fields<3>(mb + 3 * d * sv, sv, here, S);
-        load_fields<1>(mub + d * sv, sv, here, &m);
-        neighbour(Q, dQ, S, m, -0.5, gm1, lo);
-#pragma unroll
-        for (int v = 0; v < 5; ++v) O[v] = O[v] + (up[v] + lo[v]);
-      }
-      double up[5], lo[5];
-      neighbour(Qp, dp, Su, mu, 0.5, gm1, up);
-      neighbour(Qm, dm, Sk, mk, -0.5, gm1, lo);
+    for (int d = 0; d < 2; ++d) {
+      const uint32_t st = d == 0 ? 8u : sj8;
+      double up[5], lo[5], Q[5], dQ[5], S[3], m;
+      load_fields<5>(qb, sv, cell(k, col + st), Q);
+      load_fields<5>(db, sv, cell(k, col + st), dQ);
+      load_fields<3>(mb + 3 * d * sv, sv, cell(k, col + st), S);
+      load_fields<1>(mub + d * sv, sv, cell(k, col + st), &m);
+      neighbour(Q, dQ, S, m, 0.5, gm1, up);
+      load_fields<5>(qb, sv, cell(k, col - st), Q);
+      load_fields<5>(db, sv, cell(k, col - st), dQ);
+      load_fields<3>(mb + 3 * d * sv, sv, here, S);
+      load_fields<1>(mub + d * sv, sv, here, &m);
+      neighbour(Q, dQ, S, m, -0.5, gm1, lo);
 #pragma unroll
       for (int v = 0; v < 5; ++v) O[v] = O[v] + (up[v] + lo[v]);
-      double o[5];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        const double rhs = -vc * r[v];
-        o[v] = (rhs - O[v]) / D;
-      }
-      store_fields<5>(A.dq_out + B.qoff, sv, here, o);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        Qm[v] = Q0[v];
-        dm[v] = d0[v];
-        Q0[v] = Qp[v];
-        d0[v] = dp[v];
-      }
-#pragma unroll
-      for (int x = 0; x < 3; ++x) Sk[x] = Su[x];
-      mk = mu;
     }
+    double up[5], lo[5];
+    neighbour(Qp, dp, Su, mu, 0.5, gm1, up);
+    neighbour(Qm, dm, Sk, mk, -0.5, gm1, lo);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) O[v] = O[v] + (up[v] + lo[v]);
+    double o[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const double rhs = -vc * r[v];
+      o[v] = (rhs - O[v]) / D;
+    }
+    store_fields<5>(A.dq_out + B.qoff, sv, here, o);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      Qm[v] = Q0[v];
+      dm[v] = d0[v];
+      Q0[v] = Qp[v];
+      d0[v] = dp[v];
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x) Sk[x] = Su[x];
+    mk = mu;
   }
 }
 
@@ -294,8 +299,8 @@ void launch_ifv_diag(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, i
                      hipStream_t s) {
   hipLaunchKernelGGL(k_ifv_diag, dim3(nwg), dim3(256), 0, s, A, blocks, nblk, nchunks);
 }
-void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int items, hipStream_t s) {
-  hipLaunchKernelGGL(k_ifv_sweep, dim3(items, std::min(nblk, 65535)), dim3(256), 0, s, A, blocks, nblk, kc);
+void launch_ifv_sweep(const ImplicitArgs& A, const BlockDesc* blocks, int nblk, int kc, int nwg, hipStream_t s) {
+  hipLaunchKernelGGL(k_ifv_sweep, dim3(nwg), dim3(256), 0, s, A, blocks, nblk, kc);
 }
 void launch_ifv_apply(double* q, const double* dq, const BlockDesc* blocks, int nblk, int64_t nchunks, int nwg,
                       hipStream_t s) {

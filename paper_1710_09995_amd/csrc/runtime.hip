@@ -352,6 +352,7 @@ struct cfd_ctx {
   bool brick = false;    // the tile list holds bricks (kernels_brick.hip)
   int64_t ncells = 0;
   int64_t nchunks = 0;   // 64-cell row chunks of the grid (time-step and norms kernels)
+  int sweep_kc = 1, sweep_nwg = 1;   // the implicit sweep: planes a march, workgroups
   cfd_tuning tun{2, 8, 32, 1, 1};   // replaced by default_tuning() when the blocks are created
   StepParams SP{};
   Gas<double> g64{};
@@ -974,12 +975,6 @@ void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* 
   launch_finalize(c->part_dt(), 2 * nwg, 2, 1.0 / (double)c->ncells, c->d_dt(), c->d_hist(), c->d_nonfinite(), s);
   double* cur = dA;
   double* nxt = dB;
-  // planes a sweep's march: more waves than fit (three a SIMD, twice over): the last of them leave less idle
-  // (192 x 96 x 96: 4 planes 1.49 ms a step, 6 1.53, 9 1.60)
-  const int kc = (int)std::max<int64_t>(1, std::min<int64_t>(16, c->nchunks / (24 * c->num_cu)));
-  int64_t items = 1;
-  for (const BlockDesc& B : c->hblocks)
-    items = std::max(items, (int64_t)((B.n[0] + 63) / 64) * ((B.n[1] + 3) / 4) * ((B.n[2] + kc - 1) / kc));
   for (int k = 0; k < sweeps; ++k) {
     // A sweep reads the neighbours across faces alone, so one launch over the
     // faces' own layers does (24 launches of three sweeps: 146 us at 192 x 96 x
@@ -990,7 +985,7 @@ void enqueue_implicit_step(cfd_ctx* c, double* q, int sweeps, double cfl, char* 
                      k < 2 ? 1 : 2);
     I.dq_in = cur;
     I.dq_out = nxt;
-    timed(c, 0, s, [&] { launch_ifv_sweep(I, c->dblocks, c->nblk, kc, (int)items, s); });
+    timed(c, 0, s, [&] { launch_ifv_sweep(I, c->dblocks, c->nblk, c->sweep_kc, c->sweep_nwg, s); });
     std::swap(cur, nxt);
   }
   launch_ifv_apply(q, cur, c->dblocks, c->nblk, c->nchunks, nwg, s);
@@ -1156,6 +1151,14 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
       int dev = 0;
       HIPCHK(hipGetDevice(&dev));
       HIPCHK(hipDeviceGetAttribute(&c->num_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    }
+    // planes a march of the implicit sweep: more waves than fit (three a SIMD, twice over): the last of them
+    // leave less idle (192 x 96 x 96: 4 planes 1.49 ms a step, 6 1.53, 9 1.60)
+    c->sweep_kc = (int)std::max<int64_t>(1, std::min<int64_t>(16, c->nchunks / (24 * c->num_cu)));
+    c->sweep_nwg = 0;
+    for (BlockDesc& B : c->hblocks) {
+      B.swg = c->sweep_nwg;
+      c->sweep_nwg += ((B.n[0] + 63) / 64) * ((B.n[1] + 3) / 4) * ((B.n[2] + c->sweep_kc - 1) / c->sweep_kc);
     }
     HIPCHK(hipMemcpyAsync(c->dblocks, c->hblocks.data(), sizeof(BlockDesc) * nblk, hipMemcpyHostToDevice, stream));
     if (!all.empty())
