@@ -72,6 +72,7 @@ using namespace cfd;
 namespace {
 
 constexpr int TILE_I = 64;
+constexpr int BRICKS_PER_CU = 7;   // up to which a grid takes bricks by default
 constexpr int PATCHES_PER_BLOCK = 3 * 6 * 64;   // reserved: 64 patches per face on average
 constexpr int NWG_MAX = 4096;   // persistent grid cap (rows of the partials buffers)
 
@@ -593,7 +594,7 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 // tiles pad the blocks that much less (2 x 2 blocks of 130 x 260 x 100 NS 6.46
 // against 7.16 ms); both keep two waves per SIMD.
 cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p, int64_t max_tiles) {
-  if (brick_count(dims) <= 7 * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
+  if (brick_count(dims) <= BRICKS_PER_CU * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
   cfd_tuning best{2, 8, 32, 1, 1};
   double least = 0.0;
   for (int tj = p.flux_fp32 && !p.viscous ? 4 : 8; tj >= 4; tj /= 2)
@@ -610,10 +611,16 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
 
 // The tiled kernel's one-plane tiles (tile_k 1) run as bricks: nothing marches
 // there, and a brick's faces run side by side where a one-plane tile computes
-// five or six one after the other.
+// five or six one after the other.  FP64 inviscid flow on a grid that fills the
+// chip keeps the tiles, whose halo is smaller (a step in us, bricks / 64 x 8
+// tiles: 128 x 64 x 64 240 / 193, 192 x 96 x 96 798 / 644, 256 x 128 x 128
+// 1936 / 1479; FP32 161 / 168, 508 / 546, 1306 / 1286, NS 308 / 323, 1099 / 1065,
+// 2566 / 2471 with 64 x 4 tiles).
 bool use_bricks(const cfd_ctx* c) {
   if (c->tun.kernel != 0 || c->tun.tile_k != 1) return false;
   if (!c->params.viscous && !c->dpatch_first) return false;
+  if (!c->params.viscous && !c->params.flux_fp32 && brick_count(c->dims) > BRICKS_PER_CU * (int64_t)c->num_cu)
+    return false;
   return brick_count(c->dims) <= c->W.max_tiles;
 }
 
