@@ -317,8 +317,12 @@ __device__ __forceinline__ void load_cell(const StageArgs& A, const BlockDesc& B
 // R = ((Di + Dj) + Dk) / V, then write R (mode 0) or the stage update
 // (modes 1-3; mode 1 also writes R for the norms if A.rout is set), less
 // (A.fb dt) force when a multigrid level's forcing is given.  R is returned
-// in Rc, the written state in Qo (modes 1-3).
-template <int MODE, bool STREAM = false, class At>
+// in Rc, the written state in Qo (modes 1-3).  EACH: every value is stored as it
+// is formed; five results and five forces held at once are quicker (the simple
+// kernel's FP64 inviscid step of 256 x 128 x 128 1.86 ms against 3.22) but cost the
+// tiled kernel's FP32 inviscid variants their third wave a SIMD (64 x 4 x 4 tiles,
+// 1.07 ms a step against 0.94).
+template <int MODE, bool STREAM = false, bool EACH = false, class At>
 __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc& B, At c, const double Di[5],
                                             const double Dj[5], const double Dk[5], const CellIn& in,
                                             double Rc[5] = nullptr, double Qo[5] = nullptr,
@@ -331,19 +335,26 @@ __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc&
     store_fields<5, STREAM>(A.out + B.qoff, B.sv, c, R);
   } else {
     double o[5], F[5];
-    if (force) load_fields<5>(force + B.qoff, B.sv, c, F);
+    if (force && !EACH) load_fields<5>(force + B.qoff, B.sv, c, F);
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       if (MODE == 1) o[q] = in.qv[q] - in.dt * R[q];
       else o[q] = A.a * in.qn[q] + A.b * (in.qv[q] - in.dt * R[q]);
       if (force) {
         const double h = A.fb * in.dt;
+        if constexpr (EACH) load_fields<1>(force + B.qoff + q * B.sv, B.sv, c, &F[q]);
         o[q] = o[q] - h * F[q];
+      }
+      if constexpr (EACH) {
+        store_fields<1>(A.out + B.qoff + q * B.sv, B.sv, c, &o[q]);
+        if (MODE == 1 && A.rout) store_fields<1>(A.rout + B.qoff + q * B.sv, B.sv, c, &R[q]);
       }
       if (Qo) Qo[q] = o[q];
     }
-    store_fields<5, STREAM>(A.out + B.qoff, B.sv, c, o);
-    if (MODE == 1 && A.rout) store_fields<5>(A.rout + B.qoff, B.sv, c, R);
+    if constexpr (!EACH) {
+      store_fields<5, STREAM>(A.out + B.qoff, B.sv, c, o);
+      if (MODE == 1 && A.rout) store_fields<5>(A.rout + B.qoff, B.sv, c, R);
+    }
   }
   if (Rc) {
 #pragma unroll
@@ -351,12 +362,12 @@ __device__ __forceinline__ void update_cell(const StageArgs& A, const BlockDesc&
   }
 }
 
-template <int MODE>
+template <int MODE, bool EACH = false>
 __device__ __forceinline__ void finish_cell(const StageArgs& A, const BlockDesc& B, int64_t c, const double Di[5],
                                             const double Dj[5], const double Dk[5]) {
   CellIn in;
   load_cell<MODE>(A, B, c, in);
-  update_cell<MODE>(A, B, c, Di, Dj, Dk, in, nullptr, nullptr, A.force);
+  update_cell<MODE, false, EACH>(A, B, c, Di, Dj, Dk, in, nullptr, nullptr, A.force);
 }
 
 // Fixed-order workgroup reduction of NPART partials; one thread a slot writes the row.
