@@ -611,16 +611,16 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
 
 // The tiled kernel's one-plane tiles (tile_k 1) run as bricks: nothing marches
 // there, and a brick's faces run side by side where a one-plane tile computes
-// five or six one after the other.  FP64 inviscid flow on a grid that fills the
-// chip keeps the tiles, whose halo is smaller (a step in us, bricks / 64 x 8
-// tiles: 128 x 64 x 64 240 / 193, 192 x 96 x 96 798 / 644, 256 x 128 x 128
-// 1936 / 1479; FP32 161 / 168, 508 / 546, 1306 / 1286, NS 308 / 323, 1099 / 1065,
-// 2566 / 2471 with 64 x 4 tiles).
+// five or six one after the other.  Inviscid flow on a grid that fills the chip
+// keeps the tiles, whose halo is smaller, in FP32 from 96 bricks a CU on (a step
+// in us, bricks / 64 x 8 tiles: 128 x 64 x 64 243 / 196, 192 x 96 x 96 797 / 648,
+// 256 x 128 x 128 1936 / 1493; with 64 x 4 tiles FP32 162 / 151, 508 / 504,
+// 1301 / 1168, at 224 x 112 x 112 807 / 870; NS 309 / 326, 1104 / 1073, 2577 / 2492).
 bool use_bricks(const cfd_ctx* c) {
   if (c->tun.kernel != 0 || c->tun.tile_k != 1) return false;
   if (!c->params.viscous && !c->dpatch_first) return false;
-  if (!c->params.viscous && !c->params.flux_fp32 && brick_count(c->dims) > BRICKS_PER_CU * (int64_t)c->num_cu)
-    return false;
+  const int64_t most = c->params.flux_fp32 ? 96 : BRICKS_PER_CU;
+  if (!c->params.viscous && brick_count(c->dims) > most * c->num_cu) return false;
   return brick_count(c->dims) <= c->W.max_tiles;
 }
 
