@@ -61,7 +61,7 @@ def _store(db: Dict[str, dict]) -> None:
 def _time_steps(solver, arena, steps: int) -> float:
     torch = solver.torch
     stream = solver.stream if solver.stream is not None else torch.cuda.current_stream(solver.device)
-    solver.step(1, hist=False, arena=arena)           # capture + warm
+    solver.step(steps, hist=False, arena=arena)       # the same call: it captures the graphs of a run of this length
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     e0.record(stream)

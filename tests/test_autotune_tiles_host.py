@@ -1,0 +1,62 @@
+"""Host logic of the tile autotuner (autotune) on a stand-in solver: what it
+times and what it keeps."""
+import types
+
+import pytest
+
+from paper_1710_09995_amd import autotune as at
+
+
+class _Solver:
+    """Steps cost a table of milliseconds by (kernel, tile_j, tile_k), 1 by default;
+    `capture`: tunings whose first call with a new step count costs 100 more."""
+    stream = None
+    device = "cpu"
+    dims = [(8, 8, 8)]
+    q = object()
+    case = types.SimpleNamespace(params=types.SimpleNamespace(viscous=1, flux_fp32=0, local_dt=0))
+
+    def __init__(self, current, costs, capture=()):
+        self.now, self.costs, self.capture, self.seen = 0.0, costs, capture, set()
+        self.t = dict(zip(("kernel", "tile_j", "tile_k"), current), use_graph=1, order=1)
+        solver = self
+
+        class Event:
+            def __init__(self, **kw):
+                self.t = None
+
+            def record(self, stream):
+                self.t = solver.now
+
+            def elapsed_time(self, other):
+                return other.t - self.t
+        cuda = types.SimpleNamespace(Event=Event, synchronize=lambda device=None: None,
+                                     current_stream=lambda device=None: None, is_available=lambda: False)
+        self.torch = types.SimpleNamespace(cuda=cuda)
+
+    def key(self):
+        return self.t["kernel"], self.t["tile_j"], self.t["tile_k"]
+
+    def get_tuning(self):
+        return dict(self.t)
+
+    def set_tuning(self, **t):
+        self.t.update(t)
+        self.seen = set()
+
+    def new_arena(self):
+        return types.SimpleNamespace(copy_=lambda src: None)
+
+    def step(self, n, hist=True, arena=None):
+        assert arena is not None and not hist
+        self.now += n * self.costs.get(self.key(), 1.0)
+        if self.key() in self.capture and n not in self.seen:
+            self.now += 100.0
+        self.seen.add(n)
+
+
+def test_timed_steps_follow_a_call_of_their_own_length():
+    """A run's graphs are captured on its first call; a run of another length has others."""
+    s = _Solver((2, 8, 32), {(2, 8, 16): 0.5, (0, 4, 8): 0.9}, capture=[(2, 8, 32), (2, 8, 16)])
+    res = at.autotune(s, candidates=[(2, 8, 16), (0, 4, 8)], use_cache=False)
+    assert s.key() == (2, 8, 16) and abs(res["ms_per_step"] - 0.5) < 1e-12
