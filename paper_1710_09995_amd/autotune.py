@@ -16,9 +16,11 @@ import json
 import os
 from typing import Dict, Iterable, Optional, Tuple
 
-DEFAULT_CANDIDATES: Tuple[Tuple[int, int, int, int], ...] = tuple(
+# Besides the tuning the solver has (by default the library's rule for its grid,
+# any depth): bricks, the tiled kernel's tiles, the plane-ring kernel's two sizes.
+DEFAULT_CANDIDATES: Tuple[Tuple[int, int, int, int], ...] = ((0, 4, 1, 1),) + tuple(
     (0, tj, tk, order) for order in (0, 1) for tj in (2, 4, 8) for tk in (4, 8, 16, 32, 64)) + tuple(
-    (2, 8, tk, order) for order in (0, 1) for tk in (4, 8, 16, 32, 64))
+    (2, tj, tk, order) for order in (0, 1) for tj in (4, 8) for tk in (4, 8, 16, 32, 64))
 
 
 def cache_path() -> str:
@@ -73,7 +75,8 @@ def _time_steps(solver, arena, steps: int) -> float:
 
 def autotune(solver, candidates: Optional[Iterable[Tuple[int, int, int]]] = None, steps: int = 3,
              use_cache: bool = True, verify: bool = False, log=None) -> dict:
-    """Pick and apply the fastest tuning; returns {"tuning", "ms_per_step", "table", "cached"}."""
+    """Pick and apply the fastest of the tuning the solver has and the candidates;
+    returns {"tuning", "ms_per_step", "table", "cached"}."""
     key = signature(solver)
     db = _load() if use_cache else {}
     if use_cache and key in db:
@@ -85,10 +88,12 @@ def autotune(solver, candidates: Optional[Iterable[Tuple[int, int, int]]] = None
     scratch = solver.new_arena()
     table = []
     best = None
-    for cand in (candidates or DEFAULT_CANDIDATES):
-        kernel, tj, tk = cand[:3]
-        order = cand[3] if len(cand) > 3 else 0
-        t = {"kernel": kernel, "tile_j": tj, "tile_k": tk, "use_graph": 1, "order": order}
+    current = solver.get_tuning()
+    tunings = [current] + [{"kernel": c[0], "tile_j": c[1], "tile_k": c[2], "use_graph": 1,
+                            "order": c[3] if len(c) > 3 else 0} for c in (candidates or DEFAULT_CANDIDATES)]
+    for n, t in enumerate(tunings):
+        if n and t == current:
+            continue
         try:
             solver.set_tuning(**t)
         except Exception:
@@ -100,10 +105,7 @@ def autotune(solver, candidates: Optional[Iterable[Tuple[int, int, int]]] = None
             log(f"# tune {t}: {ms:.3f} ms/step")
         if best is None or ms < best[1]:
             best = (t, ms)
-    if best is None:
-        raise RuntimeError("no tuning candidate could be applied")
     if verify:
-        ref = solver.get_tuning()
         outs = []
         for t in (best[0], {"kernel": 1, "tile_j": 4, "tile_k": 8, "use_graph": 0, "order": 0}):
             solver.set_tuning(**t)
@@ -114,7 +116,6 @@ def autotune(solver, candidates: Optional[Iterable[Tuple[int, int, int]]] = None
         for a, b in zip(*outs):
             if not torch.equal(a, b):
                 raise RuntimeError("tuning changed results: bitwise check failed")
-        del ref
     solver.set_tuning(**best[0])
     del scratch
     if use_cache:

@@ -60,3 +60,19 @@ def test_timed_steps_follow_a_call_of_their_own_length():
     s = _Solver((2, 8, 32), {(2, 8, 16): 0.5, (0, 4, 8): 0.9}, capture=[(2, 8, 32), (2, 8, 16)])
     res = at.autotune(s, candidates=[(2, 8, 16), (0, 4, 8)], use_cache=False)
     assert s.key() == (2, 8, 16) and abs(res["ms_per_step"] - 0.5) < 1e-12
+
+
+def test_keeps_the_current_tuning_when_nothing_is_faster():
+    s = _Solver((2, 8, 23), {(2, 8, 23): 0.4, (0, 4, 8): 0.5})
+    before = s.get_tuning()
+    res = at.autotune(s, candidates=[(0, 4, 8)], use_cache=False)
+    assert res["tuning"] == before == s.get_tuning() and abs(res["ms_per_step"] - 0.4) < 1e-12
+    assert [r["ms_per_step"] for r in res["table"]] == pytest.approx([0.4, 0.5])
+
+
+@pytest.mark.parametrize("fastest", [(0, 4, 1), (2, 4, 16), (2, 8, 16), (0, 8, 8)])
+def test_default_candidates_hold_every_kind_of_default_tuning(fastest):
+    """Bricks, both sizes of plane-ring tiles, tiled tiles."""
+    s = _Solver((2, 8, 32), {fastest: 0.5})
+    at.autotune(s, use_cache=False)
+    assert s.key() == fastest
