@@ -6,8 +6,9 @@ untouched, and keeps the fastest.  Every tuning gives bitwise identical
 results (the face fluxes are the same bits whichever tile computes them), so
 tuning changes speed only; ``verify=True`` re-checks that on one step.
 
-The winner is cached in a JSON file keyed by the GPU architecture, the flow
-variant and the block dimensions (``CFD_TUNE_CACHE`` overrides the path).
+The winner is cached in a JSON file keyed by the library's build, the GPU
+architecture, the flow variant and the block dimensions (``CFD_TUNE_CACHE``
+overrides the path).
 """
 from __future__ import annotations
 
@@ -15,6 +16,8 @@ import hashlib
 import json
 import os
 from typing import Dict, Iterable, Optional, Tuple
+
+from . import binding
 
 # Besides the tuning the solver has (by default the library's rule for its grid,
 # any depth): bricks, the tiled kernel's tiles, the plane-ring kernel's two sizes.
@@ -31,12 +34,18 @@ def cache_path() -> str:
     return os.path.join(base, "cfd_mi355x_tune.json")
 
 
+def _library() -> str:
+    """Digest of the library that is timed: another build's winners say nothing about it."""
+    with open(binding.LIBPATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()
+
+
 def signature(solver) -> str:
     torch = solver.torch
     arch = torch.cuda.get_device_properties(solver.device).gcnArchName if torch.cuda.is_available() else "cpu"
     p = solver.case.params
     dims = ",".join(f"{a}x{b}x{c}" for a, b, c in solver.dims)
-    raw = f"{arch}|visc{p.viscous}|fp32{p.flux_fp32}|ldt{p.local_dt}|{dims}"
+    raw = f"{_library()}|{arch}|visc{p.viscous}|fp32{p.flux_fp32}|ldt{p.local_dt}|{dims}"
     return hashlib.sha256(raw.encode()).hexdigest()[:24]
 
 
@@ -77,7 +86,7 @@ def autotune(solver, candidates: Optional[Iterable[Tuple[int, int, int]]] = None
              use_cache: bool = True, verify: bool = False, log=None) -> dict:
     """Pick and apply the fastest of the tuning the solver has and the candidates;
     returns {"tuning", "ms_per_step", "table", "cached"}."""
-    key = signature(solver)
+    key = signature(solver) if use_cache else None
     db = _load() if use_cache else {}
     if use_cache and key in db:
         t = db[key]["tuning"]

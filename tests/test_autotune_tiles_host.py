@@ -76,3 +76,18 @@ def test_default_candidates_hold_every_kind_of_default_tuning(fastest):
     s = _Solver((2, 8, 32), {fastest: 0.5})
     at.autotune(s, use_cache=False)
     assert s.key() == fastest
+
+
+def test_cached_winners_belong_to_the_library_that_timed_them(tmp_path, monkeypatch):
+    from paper_1710_09995_amd import binding
+    lib = tmp_path / "lib.so"
+    lib.write_bytes(b"one")
+    monkeypatch.setenv("CFD_TUNE_CACHE", str(tmp_path / "tune.json"))
+    monkeypatch.setattr(binding, "LIBPATH", str(lib))
+    kept = at.autotune(_Solver((2, 8, 32), {(0, 4, 8): 0.5}), candidates=[(0, 4, 8)])
+    again = at.autotune(_Solver((2, 8, 32), {}), candidates=[(0, 4, 8)])
+    assert not kept["cached"] and again["cached"] and again["tuning"] == kept["tuning"]
+    lib.write_bytes(b"two")
+    s = _Solver((2, 8, 32), {(0, 4, 8): 2.0})
+    other = at.autotune(s, candidates=[(0, 4, 8)])
+    assert not other["cached"] and s.key() == (2, 8, 32)
