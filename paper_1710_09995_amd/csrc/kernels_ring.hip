@@ -411,12 +411,13 @@ static void ring_mode(const StageArgs& A, int mode, const BlockDesc* blocks, con
   if (mode == 0) ring_launch<T, VISC, 0, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
   else if (mode == 1) ring_launch<T, VISC, 1, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
   else if (mode == 2) ring_launch<T, VISC, 2, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
-  else ring_launch<T, VISC, 3, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
+  else if constexpr (VISC) ring_launch<T, VISC, 3, TI, TJ>(A, blocks, tiles, gas, nwg, s, occ);
 }
 
 template <typename T, bool VISC>
 static bool ring_shape(const StageArgs& A, int mode, const BlockDesc* blocks, const TileDesc* tiles, const Gas<T>& gas,
                        int nwg, hipStream_t s, int* occ) {
+  if (mode == 3 && !VISC) return false;   // inviscid flow takes its time steps in a pass of their own
   if (A.tile_j == 8 && A.tile_i == 64) ring_mode<T, VISC, 64, 8>(A, mode, blocks, tiles, gas, nwg, s, occ);
   else if (A.tile_j == 8 && A.tile_i == 32) ring_mode<T, VISC, 32, 16>(A, mode, blocks, tiles, gas, nwg, s, occ);
   else if (A.tile_j == 4 && A.tile_i == 32) ring_mode<T, VISC, 32, 8>(A, mode, blocks, tiles, gas, nwg, s, occ);
@@ -426,7 +427,7 @@ static bool ring_shape(const StageArgs& A, int mode, const BlockDesc* blocks, co
 }
 
 // Launch (occ == nullptr) or query the resident workgroups per CU.  Takes
-// A.tile_j = 4 or 8.
+// A.tile_j = 4 or 8, mode 3 for viscous flow; false otherwise.
 bool stage_ring(const StageArgs& A, int mode, bool visc, bool fp32, const BlockDesc* blocks, const TileDesc* tiles,
                 const Gas<double>& g64, const Gas<float>& g32, int nwg, hipStream_t s, int* occ) {
   if (fp32) {

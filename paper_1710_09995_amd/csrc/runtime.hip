@@ -483,37 +483,6 @@ void set_params(cfd_ctx* c) {
   fill(c->g32);
 }
 
-int64_t count_tiles(const std::vector<cfd_dims>& dims, int tj, int tk) {
-  int64_t t = 0;
-  for (const auto& d : dims)
-    t += (int64_t)((d.ni + TILE_I - 1) / TILE_I) * ((d.nj + tj - 1) / tj) * ((d.nk + tk - 1) / tk);
-  return t;
-}
-
-// Default tuning for the grid: the plane-ring kernel with 64 x 8 x 32 tiles
-// (deep tiles amortise each tile's three plane fills; measured better than
-// 64 x 8 x 16 even where nk = 144 leaves a half-empty last tile), tile_k
-// halved (down to 4) while there are fewer tiles than CUs.  A grid that still
-// leaves CUs idle gets the tiled kernel with 4-row tiles, tile_k halved (down
-// to 1) until there are 4 tiles per CU: on such small grids the launch's
-// latency, not the halo planes each shallow tile reloads, bounds the stage
-// (measured on the 96x48x48 and 48x24x24 levels of a multigrid cycle: 64x4x1
-// tiles took the cycle from 1.45 to 1.26 ms against 64x4x4 and 64x2x4).
-// Grids of many small uneven blocks run faster with smaller tiles: the
-// autotuner finds them.
-// The FP32-flux Euler plane-ring kernels hold two workgroups per CU; tiles of
-// half the depth fill both and shorten the tail of the persistent grid.
-cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p) {
-  cfd_tuning t{2, 8, (p.flux_fp32 && !p.viscous) ? 16 : 32, 1, 1};
-  while (t.tile_k > 4 && count_tiles(dims, t.tile_j, t.tile_k) < (int64_t)num_cu) t.tile_k /= 2;
-  if (count_tiles(dims, t.tile_j, t.tile_k) < num_cu) {
-    t.kernel = 0;
-    t.tile_j = 4;
-    while (t.tile_k > 1 && count_tiles(dims, t.tile_j, t.tile_k) < 4 * (int64_t)num_cu) t.tile_k /= 2;
-  }
-  return t;
-}
-
 // Cell columns that a launch computes with tiles of ti x tj columns, padding
 // included, times their planes; and the tiles' count.
 int64_t padded_cells(const std::vector<cfd_dims>& dims, int ti, int tj, int tk, int64_t* tiles) {
@@ -784,7 +753,7 @@ void launch_stage(cfd_ctx* c, const StageArgs& A, int mode, hipStream_t s) {
   } else if (c->tun.kernel == 2) {
     timed(c, 0, s, [&] {
       if (!stage_ring(A, mode, visc, fp32, c->dblocks, c->dtiles, c->g64, c->g32, nwg, s, nullptr))
-        fail(CFD_EINVAL, "plane-ring kernel takes tile_j = 4 or 8, got %d", c->tun.tile_j);
+        fail(CFD_EINVAL, "plane-ring kernel has no variant for tile_j %d, mode %d", c->tun.tile_j, mode);
     });
   } else {
     timed(c, 0, s, [&] { launch_stage_simple(A, mode, visc, fp32, c->dblocks, c->dtiles, c->g64, c->g32, nwg, s); });
