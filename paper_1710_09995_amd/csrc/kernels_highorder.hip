@@ -2033,15 +2033,18 @@ void grads_launch(const std::vector<PhiBlk>& v, int d, hipStream_t stream) {
       });
 }
 
-// sc[(t * 3 + x) * cells + c]: S_t at the cells from its faces along t.
-// A block's metric pass: its input line (and J^{-1}'s), the output.
+// A block's metric pass: its input line (and J^{-1}'s), the output.  The direction
+// is a template argument: indexed by a variable, the extents went through LDS
+// (48^3 cells: 22 us a pass of the face metrics).
 struct MetBlk {
   Line L, J;
   double* out;
   int n[3];
 };
 
-__global__ void __launch_bounds__(256) k_c4_cell_metrics_line(Batch<MetBlk> Bt, int t) {
+// sc[(t * 3 + x) * cells + c]: S_t at the cells from its faces along t.
+template <int t>
+__global__ void __launch_bounds__(256) k_c4_cell_metrics_line(Batch<MetBlk> Bt) {
   const MetBlk& Bk = Bt.b[blockIdx.y];
   const Line S = Bk.L;
   double* __restrict__ const sc = Bk.out;
@@ -2067,7 +2070,8 @@ constexpr int VW_PHI = 0, VW_G = 4;
 
 // Face metrics along d from the cell metrics sc (9 fields, S_t[x] at t * 3 + x)
 // and J^{-1}, four-point face values across the seams.
-__global__ void __launch_bounds__(256) k_c4_face_metrics(Batch<MetBlk> Bt, int d) {
+template <int d>
+__global__ void __launch_bounds__(256) k_c4_face_metrics(Batch<MetBlk> Bt) {
   const MetBlk& Bk = Bt.b[blockIdx.y];
   const Line SC = Bk.L, J = Bk.J;
   double* __restrict__ const fm = Bk.out;
@@ -2398,7 +2402,10 @@ void face_metrics_launch(const std::vector<MetBlk>& v, int d, hipStream_t stream
   for_batches(
       v, [](const MetBlk& b) { return (int64_t)b.n[0] * b.n[1] * b.n[2]; },
       [&](const Batch<MetBlk>& B, int count, int64_t cells) {
-        hipLaunchKernelGGL(k_c4_face_metrics, dim3(grid_for(cells), count), dim3(256), 0, stream, B, d);
+        const dim3 g(grid_for(cells), count), t(256);
+        if (d == 0) hipLaunchKernelGGL(k_c4_face_metrics<0>, g, t, 0, stream, B);
+        else if (d == 1) hipLaunchKernelGGL(k_c4_face_metrics<1>, g, t, 0, stream, B);
+        else hipLaunchKernelGGL(k_c4_face_metrics<2>, g, t, 0, stream, B);
       });
 }
 
@@ -2475,7 +2482,10 @@ void c4_face_metrics_blocks(int32_t nblk, const int32_t* dims, const int32_t* nb
     for_batches(
         v, [](const MetBlk& b) { return (int64_t)b.n[0] * b.n[1] * b.n[2]; },
         [&](const Batch<MetBlk>& B, int count, int64_t cells) {
-          hipLaunchKernelGGL(k_c4_cell_metrics_line, dim3(grid_for(cells), count), dim3(256), 0, stream, B, t);
+          const dim3 g(grid_for(cells), count), n(256);
+          if (t == 0) hipLaunchKernelGGL(k_c4_cell_metrics_line<0>, g, n, 0, stream, B);
+          else if (t == 1) hipLaunchKernelGGL(k_c4_cell_metrics_line<1>, g, n, 0, stream, B);
+          else hipLaunchKernelGGL(k_c4_cell_metrics_line<2>, g, n, 0, stream, B);
         });
   }
   for (int d = 0; d < 3; ++d) {
