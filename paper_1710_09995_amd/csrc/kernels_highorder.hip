@@ -18,8 +18,9 @@
 // as one pass per direction that keeps every intermediate on chip: an LDS row
 // pass along i and register marches along j and k for the inviscid residual
 // (primitives, edge states, Roe's flux, Eq. 2), the index derivatives of the
-// viscous terms and their face fluxes with the staggered difference; smaller
-// blocks take the padded-primitive, face and Eq. 2 passes, with the same bits.
+// viscous terms and their face fluxes with the staggered difference; the smallest
+// blocks take the padded-primitive, face and Eq. 2 passes along j and k, with the
+// same bits.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -951,24 +952,33 @@ __global__ void __launch_bounds__(256, 2) k_wcns5_euler_march(Batch<EulerBlk> Bt
   }
 }
 
-// The one-pass kernels take blocks of 32 k cells in all: below that the three
-// passes' thousands of short threads are quicker (16^3 41 us a residual against
-// 46, 24^3 43 against 46; 32^3 equal; 48^3 67 against 52, 128 x 64 x 64 131
-// against 86).  Short rows do not matter: the three passes handle their five
-// cells beyond either end as well, and through memory (4 x 256 x 256 cells 79 us
-// against 240, 7 x 512 x 64 65 against 156; a 256 x 128 x 64 block joined to one
-// of five cells along i 372 against 563).
-bool one_pass_ok(const std::vector<EulerBlk>& v) {
+// The row pass takes every block, the marches blocks of 2 k cells in all; below
+// that the three passes' short threads are quicker along j and k (a curvilinear
+// residual of 8^3 cells 31 us against 34, 12^3 34 / 35; 16^3 37 / 35, 24^3 39 / 36,
+// 200 x 12 x 12 40 / 36, 128 x 64 x 64 128 / 84).  Short rows do not matter: the three
+// passes handle their five cells beyond either end as well, and through memory
+// (4 x 256 x 256 cells 240 / 79, 7 x 512 x 64 156 / 65; a 256 x 128 x 64 block joined
+// to one of five cells along i 563 / 372).
+bool one_pass_ok(const std::vector<EulerBlk>& v, int d) {
   int64_t cells = 0;
   for (const EulerBlk& b : v) cells += (int64_t)b.n[0] * b.n[1] * b.n[2];
-  return cells >= (int64_t)1 << 15;
+  return !v.empty() && (d == 0 || cells >= 2048);
 }
 
-// Chunks of 32 cells, halved down to 4 while they give fewer than 64 k threads:
-// each chunk computes five extra faces.
+// Chunks of 32 cells, halved down to 4 while they give fewer than 64 k threads,
+// and on to 1 while no more than one workgroup a CU comes of it: each chunk
+// computes five extra faces (a residual of 32^3 with chunks of 4 / 2 / 1 cells
+// 44 / 37 / 34 us, 40^3, whose chunks of 1 are 280 workgroups, 47 / 39 / 53,
+// 56^3, 364 of 2, 53 / 66).
+int64_t march_items(const std::vector<EulerBlk>& v, int d, int chunk) {
+  int64_t n = 0;
+  for (const EulerBlk& b : v) n += d == 1 ? MarchAt<1>::items(b.n, chunk) : MarchAt<2>::items(b.n, chunk);
+  return n;
+}
 int euler_chunk(const std::vector<EulerBlk>& v, int d) {
   int chunk = 32;
   while (chunk > 4 && march_threads(v, d, chunk) < (int64_t)1 << 16) chunk /= 2;
+  while (chunk > 1 && chunk <= 4 && march_items(v, d, chunk / 2) <= 256) chunk /= 2;
   return chunk;
 }
 
@@ -1113,8 +1123,9 @@ void euler_rows_launch(const std::vector<EulerBlk>& v, double eps, double c1, do
   auto positions = [](const EulerBlk& b) { return (int64_t)b.n[1] * b.n[2] * (b.n[0] + 10); };
   int64_t all = 0;
   for (const EulerBlk& b : v) all += positions(b);
-  // four waves a SIMD where there is work for them; 2 to 32 trips a run
-  const int trips = (int)std::min<int64_t>(32, std::max<int64_t>(2, (all + 64 * 4096 - 1) / (64 * 4096)));
+  // four waves a SIMD where there is work for them; 1 to 32 trips a run (400 x 10 x 10 cells, one trip instead of
+  // two: 2 us less)
+  const int trips = (int)std::min<int64_t>(32, std::max<int64_t>(1, (all + 64 * 4096 - 1) / (64 * 4096)));
   const int64_t run = 64 * trips - 10;
   for_batches(v, positions, [&](const Batch<EulerBlk>& B, int count, int64_t most) {
     const int64_t wgs = ((most + run - 1) / run + 3) / 4;
@@ -1158,7 +1169,7 @@ void wcns5_residual_core(const double* q_dev, const double* s_dev, const double*
     const std::vector<EulerBlk> one{EulerBlk{{q_dev, q_dev, q_dev, cells, cells, cells, n[d], n[d]},
                                              {s_dev, s_dev, s_dev, cells, cells, cells, n[d], n[d]},
                                              r_dev, jinv_dev, {n[0], n[1], n[2]}}};
-    if (one_pass_ok(one)) {   // the last march divides the sum by J^{-1}
+    if (one_pass_ok(one, d)) {   // the last march divides the sum by J^{-1}
       if (d == 0) euler_rows_launch(one, eps, c1, c2, c3, gas, stream);
       else euler_march_launch(one, d, d == 2 && s_dev, eps, c1, c2, c3, gas, stream);
       continue;
@@ -1818,7 +1829,7 @@ void wcns5_blocks_residual_launch(int32_t nblk, const int32_t* dims, const int32
                    {n[0], n[1], n[2]}});
       id.push_back(b);
     }
-    if (one_pass_ok(v)) {   // across the seams; the last march divides by J^{-1}
+    if (one_pass_ok(v, d)) {   // across the seams; the last march divides by J^{-1}
       if (d == 0) euler_rows_launch(v, eps, c1, c2, c3, gas, stream);
       else euler_march_launch(v, d, d == 2, eps, c1, c2, c3, gas, stream);
       continue;

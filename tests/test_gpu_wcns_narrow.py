@@ -1,23 +1,28 @@
 """GPU: blocks of one to seven cells along i, alone and joined to larger ones, take
 the same one-pass inviscid WCNS-E-5 kernels as any other: bitwise the three-pass
-path, and bitwise the unsplit block."""
+path, and bitwise the unsplit block.  Blocks whose marches take chunks of one and
+two cells, with remainders: within 1e-12 of the oracle's largest entry."""
+import numpy as np
 import pytest
 
 from gpu_util import say
+from oracle import highorder as ho
 from test_gpu_highorder import _smooth_state
 from test_gpu_zcurvilinear import _curv_grid
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,curved", [((1, 128, 100), False), ((2, 90, 70), True), ((3, 99, 101), False),
-                                      ((5, 64, 64), True), ((7, 61, 60), False), ((7, 31, 65), True)])
+@pytest.mark.parametrize("n,curved", [((1, 40, 50), False), ((2, 30, 31), True), ((3, 26, 25), False),
+                                      ((5, 20, 20), True), ((7, 17, 16), False), ((7, 31, 9), True),
+                                      ((12, 13, 13), True), ((100, 3, 6), True), ((11, 11, 11), False)])
 def test_narrow_rows_are_the_three_pass_path_bitwise(n, curved):
-    """A periodic block (three passes) and the same flow three periods deep (one pass)."""
+    """A periodic block (three passes along j and k) and the same flow three periods
+    deep (one pass)."""
     import torch
     from paper_1710_09995_amd.binding import (wcns5_euler_residual_curv_periodic, wcns5_euler_residual_periodic,
                                               wcns5_metrics_periodic)
-    assert n[0] * n[1] * n[2] < 32768 <= 3 * n[0] * n[1] * n[2]
+    assert n[0] * n[1] * n[2] < 2048 <= 3 * n[0] * n[1] * n[2]
     say("narrow rows", n, curved)
     q = torch.from_numpy(_smooth_state(n, seed=3)).cuda()
     deep = lambda t: torch.cat([t] * 3, dim=t.dim() - 3).contiguous()
@@ -50,3 +55,15 @@ def test_narrow_blocks_among_others_match_the_unsplit_block(n, cuts):
     whole = wcns5_euler_residual_curv_periodic(q, S, J)
     for part, sl in zip(parts, sls):
         assert torch.equal(part, whole[(slice(None),) + sl])
+
+
+@pytest.mark.parametrize("n", [(40, 41, 43), (64, 43, 16), (33, 31, 33), (100, 19, 18)])
+def test_short_chunks_match_the_oracle(n):
+    import torch
+    from paper_1710_09995_amd.binding import wcns5_euler_residual_periodic
+    q = _smooth_state(n, seed=sum(n))
+    h = (1.0 / n[0], 1.0 / n[1], 1.0 / n[2])
+    say("short chunks", n)
+    got = wcns5_euler_residual_periodic(torch.from_numpy(q).cuda(), h).cpu().numpy()
+    want = ho.wcns5_euler_residual_periodic(q, h, 1.4, 0.1)
+    assert np.max(np.abs(got - want)) <= 1e-12 * np.max(np.abs(want))
