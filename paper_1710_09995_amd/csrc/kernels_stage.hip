@@ -158,8 +158,8 @@ __global__ void __launch_bounds__(256) k_norms(const double* __restrict__ q, con
 // coalesced), then a fixed tree over the 64.  A row's place in the order does
 // not depend on the number of rows.  mode 2: the same with the minimum of slot
 // 12 for dt.  mode 0: the minimum of slot 12 -> dt.
-// Twelve loads of a thread are in flight (2304 rows: 9 to 12 us; 20 with them
-// one after the other).
+// Twelve loads of a thread are in flight (2048 rows 6 us, 13 rows 4; 10.5 and 6 with
+// the slot's operation chosen for every value, 20 with one load after the other).
 constexpr int FIN_T = 64 * NPART;
 
 __device__ __forceinline__ double fin_op(int q, double a, double b) {
@@ -185,20 +185,28 @@ __global__ void __launch_bounds__(FIN_T) k_finalize(const double* __restrict__ p
     return;
   }
   const int q = t % NPART;
-  double acc = q == 12 ? __builtin_inf() : 0.0;
+  const double none = q == 12 ? __builtin_inf() : 0.0;
   const int total = nrows * NPART;
-  const double none = acc;
-  for (int e0 = t; e0 < total; e0 += 12 * FIN_T) {      // twelve loads in flight
-    double v[12];
+  // the slot's sum, and its largest value, of slot 12 the largest of the negated ones
+  const uint64_t flip = q == 12 ? (uint64_t)1 << 63 : 0;
+  auto negated = [&](double x) { return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) ^ flip); };
+  double sum = 0.0, most = negated(none);
+  constexpr int U = 12;      // loads in flight
+  for (int e0 = t; e0 < total; e0 += U * FIN_T) {
+    double v[U];
 #pragma unroll
-    for (int u = 0; u < 12; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int e = e0 + u * FIN_T;
       v[u] = partials[e < total ? e : t];
       if (e >= total) v[u] = none;
     }
 #pragma unroll
-    for (int u = 0; u < 12; ++u) acc = fin_op(q, acc, v[u]);
+    for (int u = 0; u < U; ++u) {
+      sum += v[u];
+      most = fmax(most, negated(v[u]));
+    }
   }
+  const double acc = q == 10 || q == 12 ? negated(most) : sum;
   sh[t] = acc;
   __syncthreads();
   for (int s = 32; s > 0; s >>= 1) {
