@@ -215,11 +215,15 @@ __device__ __forceinline__ bool ghost_state(const double* __restrict__ q, const 
                                          P.uinf[1], P.uinf[2]);
 #pragma unroll
       for (int v = 0; v < NV; ++v) g[v] = far.q[v];
-    } else if (P.kind == CFD_BC_KIND_EXTRAP) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) g[v] = w[v];
     } else {
-      wall_state(P.kind, w, nx, ny, nz, g);
+      // by selection: as branches on the kind, the compiler formed the no-slip
+      // wall's negated momentum only in lanes that another branch excludes, and
+      // such ghosts held what the registers held
+      double wall[NV];
+      wall_state(CFD_BC_KIND_SLIPWALL, w, nx, ny, nz, wall);
+      const bool slip = P.kind == CFD_BC_KIND_SLIPWALL, same = P.kind == CFD_BC_KIND_EXTRAP;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) g[v] = slip ? wall[v] : same || v == 0 || v == NV - 1 ? w[v] : -w[v];
     }
     return true;
   }
