@@ -72,7 +72,8 @@ using namespace cfd;
 namespace {
 
 constexpr int TILE_I = 64;
-constexpr int BRICKS_PER_CU = 7;   // up to which a grid takes bricks by default
+// up to which a grid takes bricks by default
+int bricks_per_cu(bool fp32) { return fp32 ? 13 : 7; }
 constexpr int PATCHES_PER_BLOCK = 3 * 6 * 64;   // reserved: 64 patches per face on average
 constexpr int NWG_MAX = 4096;   // persistent grid cap (rows of the partials buffers)
 
@@ -548,12 +549,15 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 }
 
 // Default tuning for the grid: bricks (the tiled kernel's one-plane tiles) up
-// to seven bricks a CU, else the plane-ring kernel, its tiles' depth (4 to 32
-// planes) and, in FP64, size the ones of least estimated cost.
-// Bricks against the best ring or tiled tiles, us a step: Euler 32^3 32 / 73,
+// to seven bricks a CU, 13 with FP32 flux, else the plane-ring kernel, its tiles'
+// depth (4 to 32 planes) and, but for FP32 Euler, size the ones of least estimated
+// cost.  Bricks against the best ring or tiled tiles, us a step: Euler 32^3 32 / 73,
 // 64 x 32 x 32 54 / 79, 96 x 48 x 48 (1728 bricks) 129 / 136, 128 x 64 x 64
 // (4096) 332 / 188; 128 blocks of 12 x 8 x 8 (1024) 119 / 143, of 24 x 12 x 12
-// (3456) 271 / 245; NS 64 x 32 x 32 83 / 134, 96 x 48 x 48 173 / 202.
+// (3456) 271 / 245; NS 64 x 32 x 32 83 / 134, 96 x 48 x 48 173 / 202, 256 x 256 x 2
+// (2048, half filled) 173 / 139.  FP32, bricks / ring: Euler 128 x 64 x 32 (2048) 88 /
+// 115, 112 x 56 x 56 (2744) 111 / 140, 160 x 64 x 40 (3200) 128 / 144, 128 x 64 x 64 161 /
+// 148; NS 135 / 182, 165 / 187, 184 / 191, 222 / 206.
 // FP32 Euler takes 256-column tiles (tile_j 4): chain of 40 uneven Euler blocks
 // 4.42 ms a step against 4.64 with 512 columns.  FP32 NS takes either by cost:
 // 512 columns load fewer halo cells, which counts on a grid past the caches
@@ -563,7 +567,7 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 // tiles pad the blocks that much less (2 x 2 blocks of 130 x 260 x 100 NS 6.46
 // against 7.16 ms); both keep two waves per SIMD.
 cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p, int64_t max_tiles) {
-  if (brick_count(dims) <= BRICKS_PER_CU * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
+  if (brick_count(dims) <= bricks_per_cu(p.flux_fp32 != 0) * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
   cfd_tuning best{2, 8, 32, 1, 1};
   double least = 0.0;
   for (int tj = p.flux_fp32 && !p.viscous ? 4 : 8; tj >= 4; tj /= 2)
@@ -588,7 +592,7 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
 bool use_bricks(const cfd_ctx* c) {
   if (c->tun.kernel != 0 || c->tun.tile_k != 1) return false;
   if (!c->params.viscous && !c->dpatch_first) return false;
-  const int64_t most = c->params.flux_fp32 ? 96 : BRICKS_PER_CU;
+  const int64_t most = c->params.flux_fp32 ? 96 : bricks_per_cu(false);
   if (!c->params.viscous && brick_count(c->dims) > most * c->num_cu) return false;
   return brick_count(c->dims) <= c->W.max_tiles;
 }
