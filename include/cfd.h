@@ -114,7 +114,8 @@ typedef struct {
  *   (tile_k 1) run as bricks of 8 x 4 x 4 cells, one face a thread, which for
  *   inviscid flow form their ghost states as they read them (inviscid flow
  *   only up to seven bricks a CU, with FP32 flux up to 96).  Defaults (set by
- *   cfd_create_blocks): up to seven bricks a CU (13 with FP32 flux), kernel 0, tile_j 4, tile_k 1;
+ *   cfd_create_blocks): up to seven bricks a CU (13 with FP32 flux and blocks of 128
+ *   bricks or more on average), kernel 0, tile_j 4, tile_k 1;
  *   above, kernel 2 with tile_j 8 (4 for FP32 Euler, and where it pads or
  *   splits an FP64 grid that much better) and tile_k the depth in [4, 32] of
  *   least estimated cost for the grid; use_graph 1, order 1.

@@ -72,8 +72,7 @@ using namespace cfd;
 namespace {
 
 constexpr int TILE_I = 64;
-// up to which a grid takes bricks by default
-int bricks_per_cu(bool fp32) { return fp32 ? 13 : 7; }
+constexpr int BRICKS_PER_CU = 7, BRICKS_PER_CU_FP32 = 13;   // up to which a grid takes bricks by default
 constexpr int PATCHES_PER_BLOCK = 3 * 6 * 64;   // reserved: 64 patches per face on average
 constexpr int NWG_MAX = 4096;   // persistent grid cap (rows of the partials buffers)
 
@@ -549,9 +548,11 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 }
 
 // Default tuning for the grid: bricks (the tiled kernel's one-plane tiles) up
-// to seven bricks a CU, 13 with FP32 flux, else the plane-ring kernel, its tiles'
-// depth (4 to 32 planes) and, but for FP32 Euler, size the ones of least estimated
-// cost.  Bricks against the best ring or tiled tiles, us a step: Euler 32^3 32 / 73,
+// to seven bricks a CU, 13 with FP32 flux and blocks of 128 bricks on average (smaller
+// blocks are nearly all boundary, whose ghost states bricks form for themselves: 40
+// blocks of 8 to 29 cells a side, 3000 bricks, 177 us a step against 163), else the
+// plane-ring kernel, its tiles' depth (4 to 32 planes) and, but for FP32 Euler, size
+// the ones of least estimated cost.  Bricks against the best ring or tiled tiles, us a step: Euler 32^3 32 / 73,
 // 64 x 32 x 32 54 / 79, 96 x 48 x 48 (1728 bricks) 129 / 136, 128 x 64 x 64
 // (4096) 332 / 188; 128 blocks of 12 x 8 x 8 (1024) 119 / 143, of 24 x 12 x 12
 // (3456) 271 / 245; NS 64 x 32 x 32 83 / 134, 96 x 48 x 48 173 / 202, 256 x 256 x 2
@@ -567,7 +568,9 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 // tiles pad the blocks that much less (2 x 2 blocks of 130 x 260 x 100 NS 6.46
 // against 7.16 ms); both keep two waves per SIMD.
 cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const cfd_params& p, int64_t max_tiles) {
-  if (brick_count(dims) <= bricks_per_cu(p.flux_fp32 != 0) * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
+  const int64_t bricks = brick_count(dims);
+  const bool far = p.flux_fp32 && bricks >= 128 * (int64_t)dims.size();
+  if (bricks <= (far ? BRICKS_PER_CU_FP32 : BRICKS_PER_CU) * (int64_t)num_cu) return cfd_tuning{0, 4, 1, 1, 1};
   cfd_tuning best{2, 8, 32, 1, 1};
   double least = 0.0;
   for (int tj = p.flux_fp32 && !p.viscous ? 4 : 8; tj >= 4; tj /= 2)
@@ -592,7 +595,7 @@ cfd_tuning default_tuning(const std::vector<cfd_dims>& dims, int num_cu, const c
 bool use_bricks(const cfd_ctx* c) {
   if (c->tun.kernel != 0 || c->tun.tile_k != 1) return false;
   if (!c->params.viscous && !c->dpatch_first) return false;
-  const int64_t most = c->params.flux_fp32 ? 96 : bricks_per_cu(false);
+  const int64_t most = c->params.flux_fp32 ? 96 : BRICKS_PER_CU;
   if (!c->params.viscous && brick_count(c->dims) > most * c->num_cu) return false;
   return brick_count(c->dims) <= c->W.max_tiles;
 }

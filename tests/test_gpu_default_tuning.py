@@ -1,6 +1,6 @@
 """GPU: the default tuning's line between bricks and the plane-ring kernel: seven
-8 x 4 x 4 bricks a CU, 13 with FP32 flux; on either side the state is bitwise the
-simple kernel's."""
+8 x 4 x 4 bricks a CU, 13 with FP32 flux (blocks of 128 bricks and more); on either
+side the state is bitwise the simple kernel's."""
 import numpy as np
 import pytest
 
