@@ -155,7 +155,7 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
 
 cfd_status cfd_destroy(cfd_ctx* ctx);
 
-/* Replace the tuning knobs (default {0, 4, 32, 1, 1}).  Drops cached graphs. */
+/* Replace the tuning knobs (defaults: see cfd_tuning).  Drops cached graphs. */
 cfd_status cfd_set_tuning(cfd_ctx* ctx, const cfd_tuning* tuning);
 cfd_status cfd_get_tuning(const cfd_ctx* ctx, cfd_tuning* tuning);
 
@@ -172,9 +172,12 @@ cfd_status cfd_residual(cfd_ctx* ctx, const double* q_arena_dev, double* r_arena
                         hipStream_t stream);
 
 /* Advance q_arena_dev by nsteps third-order Runge-Kutta steps (Eqs. 4-6,
- * lambda = -dt) with a ghost fill before every stage and the CFL time step
- * recomputed from Q^n at every step.  Ghost cells of q_arena_dev are
- * overwritten.  For inviscid flow the fill covers every face's ghost layers
+ * lambda = -dt) with the ghost states taken afresh before every stage and the
+ * CFL time step recomputed from Q^n at every step.  Ghost cells of q_arena_dev
+ * are scratch: they are overwritten, but where the stages run as bricks on
+ * inviscid flow, which form the ghost states as they read them; what they hold
+ * afterwards means nothing (cfd_fill_ghosts fills them).  For inviscid flow the
+ * fill covers every face's ghost layers
  * over the face's own cells in one launch: the edge and corner ghost cells,
  * which no inviscid stencil reads, keep their values (cfd_fill_ghosts fills
  * them).  hist_dev (device, nullable) receives one row of 12 doubles

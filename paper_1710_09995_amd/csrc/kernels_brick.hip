@@ -18,7 +18,7 @@
 // primitives and expressions, with the direction as strides.
 //
 // 32^3 Euler, FP64: 7.5 us a launch against 11.5 with 64 x 4 x 1 marching tiles,
-// 37 us a step with its history row against 77; the dispatch rule has the sizes
+// 35 us a step with its history row against 77; the dispatch rule has the sizes
 // at which either is faster.
 #include <hip/hip_runtime.h>
 #include "cfd_internal.hpp"

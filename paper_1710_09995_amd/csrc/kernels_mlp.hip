@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256) k_mlp_mse_final(const double* __restrict_
 // against 64 bits at 8192 points: 3e-8 to 6e-8 of their norm (8e-8 to 1.3e-7
 // with the scalar FP32 sums it replaces).
 //
-// A minibatch of 8192 through the 5-128x4-5 net: k_mlp_dz 30 us, k_mlp_dw 24,
+// A minibatch of 8192 through the 5-128x4-5 net: k_mlp_dz 31 us, k_mlp_dw 25,
 // the sum 5; before, one thread per weight walked 256 points (547 us) and one
 // per point and input summed dZ W (178 us), in 21 launches.  Latency bounds the
 // new ones: 8192 points are half a wave a SIMD.
@@ -614,7 +614,8 @@ static void forward_launch(const MlpDims& D, const MlpStage& S, const uint16_t* 
                            int64_t n, float* y, float* cache, hipStream_t s) {
   constexpr int PTS = NT / 64 * M * 16;
   const int64_t rounds = (n + PTS - 1) / PTS;
-  // a workgroup that holds the net is resident alone on its CU: 256 of them
+  // one workgroup a CU where each stages the whole net (a wide net fills its LDS; a
+  // narrow one would hold more)
   const unsigned nwg = (unsigned)std::min<int64_t>(rounds, S.resident ? 256 : 1024);
   hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_forward<HT, M, CACHE, NT>),
                       hipFuncAttributeMaxDynamicSharedMemorySize, S.bytes);

@@ -36,14 +36,14 @@
 // which would spill (256 x 128 x 128 NS, stage 3: 585 us before, 619 with it, 533
 // without); and addresses are one 32-bit column offset beside scalar bases.  64-bit vector addresses per field,
 // hoisted out of the plane loop, filled the registers and spilled: FP64
-// Navier-Stokes 62 to 8 (stage 1) and 0 (stage 2) dwords.  256 x 128 x 128 NS
+// Navier-Stokes stage 1 62 dwords, now none (stage 3 four).  256 x 128 x 128 NS
 // 1577 -> 1500 us a step, 2 x 2 x (250 x 203 x 72) FP32 NS 5.07 -> 4.66 ms,
 // 128 x (48 x 24 x 24) Euler V-cycles 5.50 -> 5.19 ms; FP32 Euler as before.
 // FP64 Navier-Stokes on a grid past the caches runs at the rate of a copy (500 B
 // a cell and stage); face metrics, Q^n and the output, used once, then carry the
 // non-temporal hint (the face vectors not in stage 3, which reads them again)
 // so that the caches keep the halos: 2 x 2 x (512 x 512 x 144)
-// 56.0 -> 54.7 ms, 256 x 128 x 128 alike; FP32 NS would lose 2 % by it.
+// 55.6 -> 53.7 ms, 256 x 128 x 128 alike; FP32 NS would lose 2 % by it.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "cfd_internal.hpp"

@@ -560,7 +560,8 @@ double ring_cost(const std::vector<cfd_dims>& dims, const cfd_tuning& t, int64_t
 // 115, 112 x 56 x 56 (2744) 111 / 140, 160 x 64 x 40 (3200) 128 / 144, 128 x 64 x 64 161 /
 // 148; NS 135 / 182, 165 / 187, 184 / 191, 222 / 206.
 // FP32 Euler takes 256-column tiles (tile_j 4): chain of 40 uneven Euler blocks
-// 4.42 ms a step against 4.64 with 512 columns.  FP32 NS takes either by cost:
+// 4.42 ms a step against 4.64 with 512 columns, 192 x 96 x 96 386 us against 425,
+// 256 x 128 x 128 814 against 810.  FP32 NS takes either by cost:
 // 512 columns load fewer halo cells, which counts on a grid past the caches
 // (2 x 2 blocks of 512 x 512 x 144 44.6 ms against 49.5; of 250 x 203 x 72 4.47
 // against 4.44).  FP64 kernels take 512 columns on grids that
@@ -796,8 +797,8 @@ struct StepKind {
 //    have changed since) and not evaluated in the last (nobody reads it);
 //    otherwise a time-step pass first (k_dt writes partial rows [0, nwg_dt) of
 //    part_dt: min dt, sum V Q^n).
-//  - History: the plane-ring kernel's stage 1 reduces the norm partials of
-//    R(Q^n) itself; the other kernels write R(Q^n) to qb (free until stage 2
+//  - History: the plane-ring and brick kernels' stage 1 reduces the norm partials
+//    of R(Q^n) itself; the other kernels write R(Q^n) to qb (free until stage 2
 //    overwrites it) and the norms kernel adds the R rows after k_dt's (only
 //    when the step keeps a history: without one they skip both, and the
 //    finalize).
@@ -818,7 +819,7 @@ void enqueue_step(cfd_ctx* c, double* q, hipStream_t s, const StepKind& kind, do
   const bool fuse = fused_dt(c) && !no_fuse && !force;
   const int nwg_f = dt_nwg(c);
   // a multigrid level's forcing: each stage's output minus b dt F, applied
-  // by the tiled and simple stage kernels themselves, after the plane-ring
+  // by the brick, tiled and simple stage kernels themselves, after the plane-ring
   // kernel by a pass of its own (the same rounding either way)
   const double* force_in_stage = ring ? nullptr : force;
   auto forced = [&](double* out, double b) {
@@ -1135,8 +1136,10 @@ cfd_status cfd_create_blocks(const cfd_params* params, int32_t nblk, const cfd_d
       HIPCHK(hipGetDevice(&dev));
       HIPCHK(hipDeviceGetAttribute(&c->num_cu, hipDeviceAttributeMultiprocessorCount, dev));
     }
-    // planes a march of the implicit sweep: more waves than fit (three a SIMD, twice over): the last of them
-    // leave less idle (192 x 96 x 96: 4 planes 1.49 ms a step, 6 1.53, 9 1.60)
+    // planes a march of the implicit sweep: more waves than fit (three a SIMD, twice over), so that the last of
+    // them leave less idle (ms a step of eight sweeps, by the rule / best of 1 to 16 planes / worst: 96 x 48 x 48
+    // 0.288 / 0.288 / 0.63, 192 x 96 x 96 1.488 / 1.486 / 1.68, 256 x 128 x 128 3.32 / 3.22 / 3.32, 128 blocks of
+    // 48 x 24 x 24 3.44 / 3.44 / 3.97, 40 uneven blocks 8.8 / 8.5 / 9.2)
     c->sweep_kc = (int)std::max<int64_t>(1, std::min<int64_t>(16, c->nchunks / (24 * c->num_cu)));
     c->sweep_nwg = 0;
     for (BlockDesc& B : c->hblocks) {
@@ -1308,8 +1311,8 @@ cfd_status cfd_step(cfd_ctx* c, double* q, int32_t nsteps, double* hist, hipStre
           enqueue_step(c, q, st, k, row);
         }
       };
-      // a step of bricks is five short launches (four without a history): as a
-      // graph of its own it takes 54 us on 32^3 cells, launched one by one 43
+      // a step of inviscid bricks is five short launches (four without a history):
+      // on 32^3 cells 35 us launched one by one, a quarter more as a graph of its own
       if (graph && (run > 1 || !own_ghosts(c))) {
         cfd_ctx::StepGraph& g = c->step_graphs[run * 8 + kind.key()];
         if (!g.exec) {

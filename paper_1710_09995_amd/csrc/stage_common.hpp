@@ -2,7 +2,7 @@
 // different gathers (straight from global memory, or from LDS planes), the
 // cell update of Eqs. (4)-(6) and the norm partials.
 //
-// Both stage kernels call face_inviscid / face_viscous with bitwise identical
+// Every stage kernel calls face_inviscid / face_viscous with bitwise identical
 // inputs in the same order (the same
 // primitives from the same Q, the same metric loads, the same averaging
 // expressions), and the sources are built with -ffp-contract=on so the
